@@ -81,6 +81,7 @@ struct EncArgs {
     const uint64_t* x;
     int32_t stride;
     int32_t x16;  // x is 16-byte aligned (then even strides allow 16-byte loads of a query)
+    int32_t wide; // contexts of more than kLaneFW feature words may occur (by the declared width bound)
     int64_t nq;
     uint64_t* words;
     uint8_t* qflags;
@@ -88,7 +89,7 @@ struct EncArgs {
 
 constexpr uint32_t kBadCtx = F2_CTX_BAD_SEGMENT | F2_CTX_BAD_WIDTH | F2_CTX_BAD_OUTPUT | F2_CTX_SYNC_TIMEOUT;
 
-__device__ __forceinline__ int feat_words(int n) { return (n + 64) >> 6; }
+__host__ __device__ __forceinline__ int feat_words(int n) { return (n + 64) >> 6; }
 
 __device__ __forceinline__ uint64_t readlane64(uint64_t v, int lane) {
     const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(v), lane);
@@ -2202,6 +2203,155 @@ __device__ __forceinline__ uint8_t encode_one(const EncArgs& e, int c, int64_t q
     return fl;
 }
 
+// ---------------------------------------------------------------------------
+// queries of wide contexts (more than kLaneFW feature words: widths from 512 on): the whole wavefront
+// takes one query, lane w holding word w of phi.  One lane per query walks a wide
+// context's rows word by word behind dependent 8-byte loads; here a basis row, 64
+// map columns or a parity-check row is one coalesced load, and only the rows and
+// columns that phi selects are read.  It is bound by the latency of those loads
+// (one round trip for the scalars, one for x and the pivots, one per eight rows).
+// 20,000 queries on 96 contexts of 513-1,500 bits at ranks around 24: 1,090 us with
+// a lane per query, 36 us with a wavefront per query.
+// ---------------------------------------------------------------------------
+// The lanes of a wavefront take its queries of up to 8 words at once; one after the
+// other those would cost more (1M queries on 80,000 contexts of up to 5 words, 0.05%
+// of the contexts with 5: 188 us per lane, 310 us with a wavefront for each of those).
+constexpr int kLaneFW = 8;
+
+__device__ __forceinline__ uint32_t xor_lanes(uint32_t v) {
+    for (int o = 32; o > 0; o >>= 1) v ^= static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), o));
+    return v;
+}
+
+// query q of context c (both uniform; c valid): support in the return value, the word in every lane
+__device__ __forceinline__ bool encode_wave(const EncArgs& e, int c, int64_t q, uint64_t& z0, uint64_t& z1) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t* xq = e.x + q * e.stride;
+    const int n = e.n_bits[c], d = n + 1, r0 = e.rank[c];
+    const int64_t bo = e.basis_off[c], po = e.piv_off[c], mo = e.map_off[c];
+    const int r = r0 < 0 ? 0 : (r0 > d ? d : r0);
+    const int fw = feat_words(n), W = fw + F2_Y_WORDS, cw = n >> 6;
+    const uint64_t xw = lane < e.stride ? xq[lane] : 0ull;
+    bool outside = lane > cw ? xw != 0 : (lane == cw && (xw >> (n & 63)) != 0);  // x bits at or above n
+    for (int w = 64 + lane; w < e.stride; w += 64) outside |= xq[w] != 0;
+    z0 = z1 = 0;
+    if (__ballot(outside)) return false;
+    const uint64_t ph = xw | (lane == cw ? 1ull << (n & 63) : 0ull);  // zero past word cw = fw - 1
+    // the basis rows that phi selects (r / 2 or so) sum to [phi | T(phi)] exactly inside
+    // the span; the t = d - r parity-check rows are all read, so they serve while t <= r / 2
+    if (2 * (d - r) > r) {
+        const uint64_t* B = e.basis + bo;
+        uint64_t acc = ph, y = 0;
+        const int fl = lane < fw ? lane : 0, yl = fw + (lane & 1);
+        for (int k0 = 0; k0 < r; k0 += 64) {
+            const bool has = k0 + lane < r;
+            const int p = has ? e.pivots[po + k0 + lane] : 0;
+            const uint64_t pw = shfl64(ph, (p >> 6) & 63);
+            uint64_t sel = __ballot(has && ((pw >> (p & 63)) & 1ull));
+            while (sel) {  // eight rows in flight; a missing one re-reads the first and is masked off
+                int k[8];
+                uint64_t f[8], v[8], mk[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    mk[u] = sel ? ~0ull : 0ull;
+                    k[u] = sel ? ffs64(sel) : k[0];
+                    sel &= sel - 1;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const uint64_t* row = B + static_cast<int64_t>(k0 + k[u]) * W;
+                    f[u] = row[fl];
+                    v[u] = row[yl];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    acc ^= f[u] & mk[u];
+                    y ^= v[u] & mk[u];
+                }
+            }
+        }
+        z0 = readlane64(y, 0);
+        z1 = readlane64(y, 1);
+        return __ballot(lane < fw && acc != 0) == 0;
+    }
+    // T(phi): the map columns of phi's set bits, 64 columns (a word of phi) per step
+    uint64_t a0 = 0, a1 = 0;
+    const Word2* M = reinterpret_cast<const Word2*>(e.maps + mo);
+    for (int w0 = 0; w0 < fw; w0 += 4) {
+        Word2 col[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint64_t pw = readlane64(ph, (w0 + u) & 63);  // (past the last word: zero, or masked by the bound)
+            const bool set = w0 + u < fw && ((pw >> lane) & 1ull);
+            col[u].x = col[u].y = 0;
+            if (set) col[u] = M[64 * (w0 + u) + lane];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            a0 ^= col[u].x;
+            a1 ^= col[u].y;
+        }
+    }
+    // support: even overlap with every parity-check row, the lanes' partial overlaps counted by a ballot
+    const uint64_t* H = e.tables + bo;
+    const int t = d - r;
+    int odd = 0;
+    for (int f0 = 0; f0 < t; f0 += 8) {
+        uint64_t h[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) h[u] = (lane < fw && f0 + u < t) ? H[static_cast<int64_t>(f0 + u) * fw + lane] : 0ull;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) odd |= __popcll(__ballot(__popcll(h[u] & ph) & 1));
+    }
+    if (odd & 1) return false;
+    z0 = (static_cast<uint64_t>(xor_lanes(static_cast<uint32_t>(a0 >> 32))) << 32) | xor_lanes(static_cast<uint32_t>(a0));
+    z1 = (static_cast<uint64_t>(xor_lanes(static_cast<uint32_t>(a1 >> 32))) << 32) | xor_lanes(static_cast<uint32_t>(a1));
+    return true;
+}
+
+// context c valid, in good order and wide
+__device__ __forceinline__ bool wide_ctx(const EncArgs& e, int c) {
+    return c >= 0 && c < e.num_ctx && !(e.ctx_flags[c] & kBadCtx) && feat_words(e.n_bits[c]) > kLaneFW;
+}
+
+// one query per live lane (context c, query q), the wide ones a wavefront each (no lane may be inactive here)
+template <bool WIDE>
+__device__ __forceinline__ uint8_t encode_lanes(const EncArgs& e, bool live, int c, int64_t q, Word2& out) {
+    uint8_t fl = 0;
+    const bool wide = WIDE && live && wide_ctx(e, c);
+    if (live && !wide) fl = encode_one(e, c, q, out.x, out.y);
+    if constexpr (WIDE) {
+        for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
+            const int j = ffs64(todo);
+            const int cj = __builtin_amdgcn_readlane(c, j);
+            uint64_t z0, z1;
+            const bool in = encode_wave(e, cj, static_cast<int64_t>(readlane64(static_cast<uint64_t>(q), j)), z0, z1);
+            if ((threadIdx.x & 63) == j) {
+                fl = ((e.ctx_flags[cj] & F2_CTX_CONTRADICTION) ? F2_Q_CTX_CONTRADICTORY : 0) | (in ? 0 : F2_Q_OUT_OF_SPAN);
+                out.x = in ? z0 : 0;
+                out.y = in ? z1 : 0;
+            }
+        }
+    }
+    return fl;
+}
+
+// small batches that may hold wide contexts: qpw queries per wavefront, few enough
+// that the chip is full of wavefronts (each takes its wide queries one by one)
+constexpr int kWideWaves = 8192;  // eight per SIMD
+__global__ __launch_bounds__(kEncThreads) void k_encode_wide(EncArgs e, int qpw) {
+    const int lane = threadIdx.x & 63;
+    const int64_t q0 = (static_cast<int64_t>(blockIdx.x) * (kEncThreads / 64) + (threadIdx.x >> 6)) * qpw;
+    const int64_t q = q0 + lane;
+    const bool live = lane < qpw && q < e.nq;
+    Word2 out;
+    out.x = out.y = 0;
+    const uint8_t fl = encode_lanes<true>(e, live, live ? e.ctx_id[q] : -1, q, out);
+    if (!live) return;
+    *reinterpret_cast<Word2*>(e.words + 2 * q) = out;
+    e.qflags[q] = fl;
+}
+
 __global__ __launch_bounds__(kEncThreads) void k_encode(EncArgs e) {
     const int64_t q = static_cast<int64_t>(blockIdx.x) * kEncThreads + threadIdx.x;
     if (q >= e.nq) return;
@@ -2812,6 +2962,7 @@ constexpr int kRestCtxPerWave = 64;  // contexts of a wavefront considered for t
 constexpr int kRestGrid = 2048;     // workgroups of the listed-group pass (100M queries: 0.50 ms; 1,024: 0.54)
 
 // one wavefront: the lanes of bits among positions i0 .. i0 + 63
+template <bool WIDE>
 __device__ __forceinline__ void rest_group(const EncArgs& e, const SortArgs& s, uint64_t* st, int64_t i0,
                                            uint64_t bits) {
     const int lane = threadIdx.x & 63;
@@ -2853,12 +3004,14 @@ __device__ __forceinline__ void rest_group(const EncArgs& e, const SortArgs& s, 
         }
         wave_sync();  // the stage is rewritten for the next context
     }
-    if (!done) fl = encode_one(e, qc.y, qc.x, out.x, out.y);
+    const uint8_t lf = encode_lanes<WIDE>(e, !done, qc.y, qc.x, out);
+    if (!done) fl = lf;
     if (!live) return;
     *reinterpret_cast<Word2*>(e.words + 2 * static_cast<int64_t>(qc.x)) = out;
     if (fl) e.qflags[qc.x] = fl;
 }
 
+template <bool WIDE>
 __global__ __launch_bounds__(kEncThreads) void k_encode_rest(EncArgs e, SortArgs s) {
     __shared__ EncStageWide sStage;
     const int wave = threadIdx.x >> 6;
@@ -2867,19 +3020,21 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_rest(EncArgs e, SortArgs
     const int waves = static_cast<int>(gridDim.x) * (kEncThreads / 64);
     for (int k = static_cast<int>(blockIdx.x) * (kEncThreads / 64) + wave; k < cnt; k += waves) {
         const int g = __builtin_amdgcn_readfirstlane(s.rest_list[k]);
-        rest_group(e, s, st, static_cast<int64_t>(g) * 64, s.rest[g]);
+        rest_group<WIDE>(e, s, st, static_cast<int64_t>(g) * 64, s.rest[g]);
     }
 }
 
 // grouped order without the staged pass (bins of several contexts, not
 // regrouped): every position per lane, the lanes of a wavefront gathering from
 // the few maps of its bins
+template <bool WIDE>
 __global__ __launch_bounds__(kEncThreads) void k_encode_lanes(EncArgs e, SortArgs s) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kEncThreads + threadIdx.x;
-    if (i >= e.nq) return;
-    const int2 qc = s.perm[i];
+    const bool live = i < e.nq;
+    const int2 qc = live ? s.perm[i] : make_int2(0, -1);
     Word2 out;
-    const uint8_t fl = encode_one(e, qc.y, qc.x, out.x, out.y);
+    const uint8_t fl = encode_lanes<WIDE>(e, live, qc.y, qc.x, out);
+    if (!live) return;
     *reinterpret_cast<Word2*>(e.words + 2 * static_cast<int64_t>(qc.x)) = out;
     if (fl) e.qflags[qc.x] = fl;
 }
@@ -3764,6 +3919,15 @@ int encode_range(const f2_model* m, const int32_t* ctx_id, const uint64_t* x, in
     const int64_t blocks = (num_queries + kEncThreads - 1) / kEncThreads;
     if (blocks > 0x7fffffff) return F2_EINVAL;
     EncPlan p = encode_workspace(m->num_ctx, num_queries);
+    e.wide = m->max_n_bits < 0 || feat_words(m->max_n_bits) > kLaneFW;
+    if (!p.sorted && e.wide) {
+        int qpw = 1;
+        while (qpw < 64 && num_queries / (2 * qpw) >= kWideWaves) qpw *= 2;
+        const int64_t per_block = static_cast<int64_t>(kEncThreads / 64) * qpw;
+        hipLaunchKernelGGL(k_encode_wide, dim3(static_cast<unsigned>((num_queries + per_block - 1) / per_block)),
+                           dim3(kEncThreads), 0, s, e, qpw);
+        return hipGetLastError() == hipSuccess ? F2_OK : F2_EDEVICE;
+    }
     if (!p.sorted) {
         hipLaunchKernelGGL(k_encode, dim3(static_cast<unsigned>(blocks)), dim3(kEncThreads), 0, s, e);
         return hipGetLastError() == hipSuccess ? F2_OK : F2_EDEVICE;
@@ -3785,10 +3949,10 @@ int encode_range(const f2_model* m, const int32_t* ctx_id, const uint64_t* x, in
                            dim3(kRegroupThreads), 0, s, e, p.s);
     if (p.s.staged) {
         hipLaunchKernelGGL(k_encode_sorted, dim3(static_cast<unsigned>(blocks)), dim3(kEncThreads), 0, s, e, p.s);
-        hipLaunchKernelGGL(k_encode_rest, dim3(static_cast<unsigned>(blocks < kRestGrid ? blocks : kRestGrid)),
+        hipLaunchKernelGGL(e.wide ? k_encode_rest<true> : k_encode_rest<false>, dim3(static_cast<unsigned>(blocks < kRestGrid ? blocks : kRestGrid)),
                            dim3(kEncThreads), 0, s, e, p.s);
     } else {
-        hipLaunchKernelGGL(k_encode_lanes, dim3(static_cast<unsigned>(blocks)), dim3(kEncThreads), 0, s, e, p.s);
+        hipLaunchKernelGGL(e.wide ? k_encode_lanes<true> : k_encode_lanes<false>, dim3(static_cast<unsigned>(blocks)), dim3(kEncThreads), 0, s, e, p.s);
     }
     return hipGetLastError() == hipSuccess ? F2_OK : F2_EDEVICE;
 }
