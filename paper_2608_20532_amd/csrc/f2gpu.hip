@@ -37,8 +37,8 @@
 
 namespace {
 
-constexpr int kLargeRows = 64;       // rows per block, large path
-constexpr int kLargeThreads = 512;
+constexpr int kSmallWaves = 8;  // small-batch fit
+constexpr int kSmallThreads = 64 * kSmallWaves;
 constexpr int kEncThreads = 256;
 
 struct FitArgs {
@@ -195,8 +195,8 @@ __device__ __forceinline__ void write_bad_context(const FitArgs& a, const CtxDes
 // histograms; a scatter that scans them) with no device-wide atomics: on a chip
 // of eight dies those serialise far from the compute units.
 // Workspace (int32): [0, 5) list offsets per class, [kPivNext] the work counter
-// of the LDS-basis kernel, [kBarHead, kPlanHead) barrier counters of workgroup
-// groups, [kPlanHead, kPlanHead + C) the lists, then C sort keys and a
+// of the LDS-basis kernel, [kBarHead, kPlanHead) progress of the wide kernel's
+// workgroups, [kPlanHead, kPlanHead + C) the lists, then C sort keys and a
 // kPlanBins histogram per plan block.
 // ---------------------------------------------------------------------------
 constexpr int kRegMaxFW = 3;
@@ -204,9 +204,9 @@ constexpr int kPivMaxFW = 8;
 constexpr int kLongRows = 256;  // contexts with more rows take the multi-wavefront kernel
 enum { kClsReg = 0, kClsPiv = 1, kClsPivLong = 2, kClsLarge = 3, kNumCls = 4 };
 constexpr int kPivNext = 8;                 // plan word: next list position for the LDS-basis kernel
-constexpr int kBarHead = 16;                // plan words kBarHead ..: barrier counters of workgroup groups
-constexpr int kMaxGroups = 128;
-constexpr int kPlanHead = kBarHead + kMaxGroups;
+constexpr int kBarHead = 16;                // plan words kBarHead ..: progress of the wide kernel's workgroups (64 bits each)
+constexpr int kMaxMembers = 256;
+constexpr int kPlanHead = kBarHead + 2 * kMaxMembers;
 constexpr int kBuckets = 256;
 constexpr int kPlanBins = kNumCls * kBuckets;
 constexpr int kPlanThreads = 1024;  // one context per thread; one bin per thread in the scan
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(FitArgs a) {
     const int tid = threadIdx.x;
     sBin[tid] = 0;
     __syncthreads();
-    if (blockIdx.x == 0 && tid < kMaxGroups) a.plan[kBarHead + tid] = 0;
+    if (blockIdx.x == 0 && tid < 2 * kMaxMembers) a.plan[kBarHead + tid] = 0;
     if (blockIdx.x == 0 && tid == 0) a.plan[kPivNext] = 0;
     const int64_t c = static_cast<int64_t>(blockIdx.x) * kPlanThreads + tid;
     if (c < a.num_ctx) {
@@ -265,8 +265,12 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(FitArgs a) {
             const int cls = fit_class(ds);
             k = cls * kBuckets + (kBuckets - 1 - cost_bucket(ds));
             atomicAdd(&sBin[k], 1);
-            // the workgroups of a wide context OR their flags in (contradiction, wait timeout)
-            if (cls == kClsLarge) a.ctx_flags[c] = 0u;
+            if (cls == kClsLarge) {  // the workgroups of a wide context add their counts and flags, and share a list
+                a.ctx_flags[c] = 0u;
+                a.n_contra[c] = 0;
+                a.first_contra[c] = -1;
+                a.pivots[ds.po] = 0;
+            }
         }
         P.key[c] = k;
     }
@@ -1136,753 +1140,945 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
 }
 
 // ---------------------------------------------------------------------------
-// large-context fit (fw > 8): one workgroup of 8 wavefronts per context.  Lanes
-// span the feature words of a row (lane w holds word w); the two output words of
-// the 8 rows a wavefront holds sit in lanes 2k, 2k+1 of one more register.  The
-// working basis lives in the caller's basis buffer, one slot per priority
-// position (slot t holds the row whose pivot is the t-th highest-priority
-// feature), and is kept fully reduced, so the final descending-priority order is
-// an in-place compaction.  Rows go in blocks of 64, rows 8w .. 8w+7 of a block
-// held by wavefront w:
-//   (1) block reduce with Four-Russians tables (the method of Arlazarov, Dinic,
-//       Kronrod and Faradzev): the retained rows of four consecutive pivot
-//       positions give a 16-entry LDS table of all their XOR combinations, and a
-//       row's own four bits at those positions (unchanged by the other retained
-//       rows, the basis being fully reduced) select the entry to add.  Eight
-//       tables (32 pivot positions) are built per round while the previous
-//       round's tables are read;
-//   (2) in-block elimination in stream order, one wavefront at a time over its
-//       own eight rows, each new pivot cleared from that wavefront's other rows at
-//       once and from the other wavefronts' rows after a barrier (earlier new rows
-//       included, so the block's new rows end fully reduced);
-//   (3) back-substitution: the new rows, in descending priority, form tables of
-//       four rows each, and every retained row adds the entry its bits at those
-//       pivots select; (4) the new rows are stored at their priority slots.
-// A feature word whose columns are all retained pivots is zero in every reduced
-// row and in every new row, so steps (1) and (3) read and write only the other
-// words (the "active" lanes); the words left alone keep the unreduced bits the
-// selections are read from.  Once the rank reaches d every later row lies in the
-// span and the basis is the identity on the features, so a row's residual is
-// y + M phi (the canonical map, staged in LDS): those rows are only checked for
-// contradictions.
+// large-context fit (fw > 8): G workgroups of 16 wavefronts per context (G a power of
+// two, all resident: a cooperative launch), one compute unit each.  The rows go in
+// blocks of 64; member g takes blocks g, g + G, ...
+//
+// The working basis is a list of batches in insertion order: the new rows of one
+// block, fully reduced among themselves and against every earlier batch (but not
+// against later ones).  A later batch has no bit at an earlier batch's pivots, so
+// adding, batch by batch in insertion order, the rows that a vector's own bits at the
+// batch's pivots select leaves the one representative of its coset that is zero at
+// every pivot: the same residual that a fully reduced basis gives, hence the same
+// pivots, kept rows and contradictions.  Nothing that was inserted is ever rewritten
+// (a basis kept fully reduced rewrites every retained row for every block: its stores,
+// and reading the rewritten rows back, took half the time of a block), and members
+// read each other's batches as they appear, without barriers.  The fully reduced
+// basis is made once, at the end.
+//
+// The list lives in the context's tables area (capacity d rows of fw + 2 words), its
+// pivots, with the block they come from, in the context's pivots area; both are final
+// outputs only later.
+//
+//   (1) block reduce, 32 basis rows (half a batch) per round, with Four-Russians tables
+//       (the method of Arlazarov, Dinic, Kronrod and Faradzev): four rows give a
+//       16-entry LDS table of their XOR combinations, and a row's four bits at their
+//       pivots select the entry to add.  A half wavefront holds one row, two feature
+//       words per lane, so that one 16-byte LDS read serves two rows;
+//   (2) a block whose residuals are all zero is done whatever the blocks before it
+//       still add.  Otherwise the member waits for them, reduces by what they added, and
+//   (3) eliminates in stream order on panels: one wavefront, a row per lane, works on
+//       the two highest feature words that hold a bit (128 columns) and notes which rows
+//       were added to which (a 64 x 64 matrix T); then all wavefronts apply T to the
+//       whole rows.  Rows that the panel reduces to zero go on to the next panel;
+//   (4) the new rows are published.
+// Once the rank reaches d the basis is the identity on the features and the map alone
+// remains: a triangular solve of the output words, word by word from the lowest
+// priority up, then every remaining row is checked against the map.  Below d each
+// batch is reduced by the later ones as in (1).
+//
+// 64 contexts, n = 4095, 8,192 rows: 10.27 ms with a basis kept fully
+// reduced (groups of 4 workgroups exchanging partial sums), 4.26 ms.  Bound by LDS
+// bandwidth: a table lookup moves 512 bytes for four basis rows.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int prio_slot(int p, int n) { return p < n ? n - 1 - p : n; }
-__device__ __forceinline__ int slot_pivot(int t, int n) { return t < n ? n - 1 - t : n; }
+constexpr int kWdWaves = 16;
+constexpr int kWdThreads = 64 * kWdWaves;
+constexpr int kWdRows = 64;                   // rows per block
+constexpr int kWdMaxBlocks = (1 << 19) - 2;   // block numbers in a pivot's tag; contexts of more rows take one member
+constexpr int kWdBar = 1 << 30;               // progress values from here on: past the blocks
+constexpr int kPivLast = 1 << 12;             // the last pivot of a batch
+constexpr int kRowPitch = 33;                 // elimination: 16-byte units per row in LDS (33: no bank conflicts down a column)
 
-constexpr int kLargeWaves = kLargeThreads / 64;      // 8
-constexpr int kLgSlots = kLargeRows / kLargeWaves;   // block rows per wavefront: 8
-constexpr int kLgEnt = 16;                           // entries of a 4-bit table
-constexpr int kLgRoundTables = kLargeWaves;          // reduce: one table per wavefront per round
-constexpr int kLgBuf = kLgRoundTables * kLgEnt;      // entries of one round's tables
-static_assert(kLgSlots == 8, "a wavefront's output words occupy lanes 0-15");
-static_assert(kLgRoundTables * 4 == 32, "a round covers half a pivot word");
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));  // rows are 8-byte aligned
 
-struct LargeShared {
-    uint64_t tf[2 * kLgBuf][64];  // table entries, feature words (lane = word); the map in the full-rank phase
-    uint64_t tz[2 * kLgBuf][2];   // table entries, output words
-    int pubP[2][kLgSlots];        // in-block elimination: pivots published by one wavefront (tables in tf)
-    int pubN[2];
-    int rowPiv[kLargeRows];       // pivot of each block row that became a basis row, else -1
-    int nsorted[kLargeRows];      // the block's new pivots in descending priority
-    int above[64];                // new pivots (constant excluded) in feature words above w
-    uint64_t pm[64];              // pivot columns of the retained basis
-    uint64_t npm[64];             // pivot columns found in the current block
-    int contra, nnew;
-    int timeout;                  // a group barrier of this context gave up
-    long long firstMin;
+struct WideShared {
+    u32x4 tab[2][128][32];             // [buffer][16 table + entry][word pair]; other phases lay out their own data here
+    uint32_t sel[kWdWaves][2][128];    // selection: two rows of a wavefront, as words
+    uint16_t piv[4096];                // the list's pivots, insertion order, kPivLast on the last of each batch
+    u32x4 ys[64];                      // output words: two rounds of 32 rows, or the block's 64 rows
+    uint64_t T[kWdRows];               // elimination: block rows added into each row
+    uint64_t pm[64];                   // pivot columns
+    int above[64];                     // pivots (constant excluded) in words above w
+    uint32_t wm[kWdWaves][2];          // nonzero even and odd words of each wavefront's rows
+    uint64_t ins;                      // block rows that became basis rows
+    uint64_t panel;                    // the ones of the current panel
+    int more;                          // another panel follows
+    int any[2];                        // nonzero residuals in the block (alternating)
+    int nrows, next;                   // list length; every block below `next` is done
+    int timeout;                       // a wait of this context gave up
 };
 
-// per-lane value of slot lane/2 for lanes 0-15 (the output-word lanes), 0 elsewhere
-template <typename T>
-__device__ __forceinline__ T spread_slots(const T (&v)[kLgSlots], int lane) {
-    T r = 0;
-#pragma unroll
-    for (int k = 0; k < kLgSlots; ++k) r = ((lane >> 1) == k) ? v[k] : r;
+__device__ __forceinline__ u32x4 xor_and4(u32x4 f, uint32_t m, u32x4 d) {
+    u32x4 r;
+    r.x = __builtin_amdgcn_bitop3_b32(f.x, m, d.x, 0x78);
+    r.y = __builtin_amdgcn_bitop3_b32(f.y, m, d.y, 0x78);
+    r.z = __builtin_amdgcn_bitop3_b32(f.z, m, d.z, 0x78);
+    r.w = __builtin_amdgcn_bitop3_b32(f.w, m, d.w, 0x78);
     return r;
 }
-
-// all-ones in the lanes whose bit is set in the 64-bit mask e
-__device__ __forceinline__ uint32_t lanes_of(uint64_t e, int lane) {
-    return 0u - static_cast<uint32_t>((e >> lane) & 1ull);
+__device__ __forceinline__ u32x4 xor3_4(u32x4 a, u32x4 b, u32x4 c) {
+    u32x4 r;
+    r.x = __builtin_amdgcn_bitop3_b32(a.x, b.x, c.x, 0x96);
+    r.y = __builtin_amdgcn_bitop3_b32(a.y, b.y, c.y, 0x96);
+    r.z = __builtin_amdgcn_bitop3_b32(a.z, b.z, c.z, 0x96);
+    r.w = __builtin_amdgcn_bitop3_b32(a.w, b.w, c.w, 0x96);
+    return r;
+}
+__device__ __forceinline__ bool any4(u32x4 v) { return (v.x | v.y | v.z | v.w) != 0; }
+__device__ __forceinline__ u32x4 shfl_xor4(u32x4 v, int o) {
+    return u32x4{static_cast<uint32_t>(__shfl_xor(static_cast<int>(v.x), o)), static_cast<uint32_t>(__shfl_xor(static_cast<int>(v.y), o)),
+                 static_cast<uint32_t>(__shfl_xor(static_cast<int>(v.z), o)), static_cast<uint32_t>(__shfl_xor(static_cast<int>(v.w), o))};
 }
 
-// the next half pivot word (2 pw + h) after r that holds retained pivots and
-// belongs to member g of a group of G (a power of 2; pivot words pw = g mod G), or -1
-__device__ __forceinline__ int next_round(const LargeShared& L, int fw, int r, int G, int g) {
-    for (int t = r + 1; t < 2 * fw; ++t) {
-        if (((t >> 1) & (G - 1)) != g) continue;
-        const uint64_t v = L.pm[t >> 1];
-        if ((t & 1) ? (v >> 32) != 0 : (v & 0xffffffffull) != 0) return t;
+// device-scope (sc1) accesses through a buffer resource: what members exchange while
+// the kernel runs goes past the caches that other dies do not see
+constexpr int kDevScope = 16;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t dev_rsrc(const void* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, static_cast<int>(bytes), 0x00020000);
+}
+template <bool DEV>
+__device__ __forceinline__ u32x4 load16(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, DEV ? kDevScope : 0);
+}
+
+// progress of a group's members: (context sequence number, blocks done, or kWdBar + k
+// past barrier k), one 64-bit word per member, stored only by it
+__device__ __forceinline__ void put_progress(uint64_t* prog, int g, int seq, int done) {
+    __hip_atomic_store(prog + g, (static_cast<uint64_t>(static_cast<uint32_t>(seq)) << 32) | static_cast<uint32_t>(done),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// one wavefront: the lowest block not known to be done (own blocks below blk are)
+__device__ __forceinline__ int lowest_open(const uint64_t* prog, int G, int g, int seq, int blk) {
+    const int lane = threadIdx.x & 63;
+    int nb = 0x7fffffff;
+    if (lane < G && lane != g) {
+        const uint64_t v = __hip_atomic_load(prog + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int s = static_cast<int>(v >> 32), dn = static_cast<int>(v);
+        if (s < seq) nb = lane;
+        else if (s == seq && dn < kWdBar) nb = lane + G * dn;
     }
-    return -1;
+    if (lane == g) nb = blk;
+    for (int o = 4; o > 0; o >>= 1) {  // G <= 8
+        const int t = __shfl_xor(nb, o);
+        nb = t < nb ? t : nb;
+    }
+    return __builtin_amdgcn_readfirstlane(nb);
 }
 
-// barrier of the G workgroups that fit one context together (all resident: the
-// launch is cooperative); counter `bar` only grows, epoch counts this member's
-// arrivals.  The wait is bounded (spin_limit polls) so that a kernel can never
-// hang on it; a wait that gives up sets *timed_out (LDS, read after the
-// workgroup barrier that ends this call), and the context is reported
-// F2_CTX_SYNC_TIMEOUT.  spin_limit 0 never waits: every call gives up.
-// full: release and acquire fences around it (every earlier global write of the
-// group visible after it); otherwise only the arrival order: the data exchanged
-// across it must be written and read with device-scope atomic stores and loads.
-__device__ __forceinline__ void group_barrier(int* bar, int& epoch, int G, int spin_limit, int* timed_out,
-                                              bool full = true) {
-    if (full) __threadfence();
-    __builtin_amdgcn_s_waitcnt(0);  // this thread's stores performed before the arrival is counted
-    __syncthreads();
-    ++epoch;
-    if (threadIdx.x == 0) {
-        __hip_atomic_fetch_add(bar, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int target = G * epoch;
-        bool arrived = false;
-        for (int spin = 0; spin < spin_limit; ++spin) {
-            if (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target) {
-                arrived = true;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(2);
+// one wavefront: take the list entries of blocks below `open` (all published) into LDS;
+// returns the new length.  A pivot's entry holds its block number + 1 above bit 13; the
+// entry after the last one published holds zero there (the plan clears entry 0).
+__device__ __forceinline__ int take_entries(WideShared& L, const int32_t* ent, int nrows, int d, int open) {
+    const int lane = threadIdx.x & 63;
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the progress is in before the entries are read
+    for (;;) {
+        const int i = nrows + lane;
+        uint32_t v = 0;
+        if (i < d) v = static_cast<uint32_t>(__hip_atomic_load(ent + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const int blk1 = static_cast<int>(v >> 13);
+        const uint64_t ok = __ballot(blk1 >= 1 && blk1 <= open);
+        const int cnt = ok == ~0ull ? 64 : ffs64(~ok);
+        if (lane < cnt) {
+            int p = static_cast<int>(v & (kPivLast - 1));
+            if (p >= d) p = d - 1;  // (only after a wait that gave up)
+            L.piv[i] = static_cast<uint16_t>(p | (v & kPivLast));
         }
-        if (!arrived) *timed_out = 1;
-        if (full) __threadfence();
+        nrows += cnt;
+        if (cnt < 64 || nrows >= d) return nrows;
     }
-    __syncthreads();
 }
 
-__device__ __forceinline__ void put_dev(uint64_t* p, uint64_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// device-scope (sc1) loads through a buffer resource: the same coherence as a
-// device-scope atomic load, but the compiler keeps many of them in flight
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t dev_rsrc(const uint64_t* base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t*>(base), 0, static_cast<int>(bytes), 0x00020000);
-}
-__device__ __forceinline__ uint64_t get_dev(__amdgpu_buffer_rsrc_t r, uint32_t word) {
-    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r, static_cast<int>(8 * word), 0, 16 /* sc1 */);
-    return (static_cast<uint64_t>(v.y) << 32) | v.x;
+// the basis rows of one round: rows 4 t .. 4 t + 3 of it (t = wavefront / 2)
+struct RoundRows {
+    u32x4 f[4];  // two words per lane, the same in both half wavefronts
+    u32x4 y;     // output words of row lane & 3
+};
+template <bool DEV>
+__device__ __forceinline__ void load_rows(__amdgpu_buffer_rsrc_t X, int W, int fw, int start, int cnt, int t, bool hb,
+                                          int voff, int lane, RoundRows& r) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (i == 3 && !hb) break;  // its combinations are the other wavefront's
+        const int row = start + (4 * t + i < cnt ? 4 * t + i : cnt - 1);
+        r.f[i] = load16<DEV>(X, voff, row * W * 8);
+    }
+    const int k = 4 * t + (lane & 3);
+    r.y = load16<DEV>(X, ((start + (k < cnt ? k : cnt - 1)) * W + fw) * 8, 0);
 }
 
-struct GroupRows {
-    uint64_t f[4];     // feature word `lane` of four retained rows, as loaded
-    uint64_t z[4];     // output word (lane & 1) of the same rows, as loaded
-    uint32_t present;  // rows that exist (bit i), wavefront-uniform
+// block rows: wavefront w holds rows 4 w .. 4 w + 3, row 4 w + 2 i + h in half h of acc[i];
+// the output words of row 4 w + (lane & 3) are the XOR of y over the lanes of equal lane & 3
+struct BlockRows {
+    u32x4 acc[2];
+    u32x4 y;
 };
 
-// retained rows of pivot positions q0 .. q0+3 of round r (pivot word r/2).  The
-// loads are unconditional (in-bounds addresses) and their values are masked only
-// where they are used, so that they stay in flight across the preceding round.
-__device__ __forceinline__ void load_group(const LargeShared& L, const uint64_t* B, int W, int fw, int n, int r,
-                                           int wave, int lane, GroupRows& gr) {
-    const int pw = r >> 1, q0 = 32 * (r & 1) + 4 * wave;
-    gr.present = static_cast<uint32_t>((L.pm[pw] >> q0) & 15ull);
-    const int fl = lane < fw ? lane : 0, zl = fw + (lane & 1);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint64_t* row = B + static_cast<int64_t>(prio_slot(64 * pw + q0 + i, n)) * W;
-        gr.f[i] = row[fl];
-        gr.z[i] = row[zl];
-    }
-}
-
-// the 16 XOR combinations of four rows, entry e = rows of the set bits of e
-__device__ __forceinline__ void write_table(LargeShared& L, int base, const GroupRows& gr, int lane, bool act) {
-    const uint64_t f1 = (act && (gr.present & 1u)) ? gr.f[0] : 0ull, f2 = (act && (gr.present & 2u)) ? gr.f[1] : 0ull;
-    const uint64_t f4 = (act && (gr.present & 4u)) ? gr.f[2] : 0ull, f8 = (act && (gr.present & 8u)) ? gr.f[3] : 0ull;
-    const uint64_t f3 = f1 ^ f2, f5 = f4 ^ f1, f6 = f4 ^ f2, f7 = f6 ^ f1;
-    {  // inactive lanes get zero entries, so that adding an entry leaves them unchanged
-        uint64_t (*T)[64] = L.tf + base;
-        T[0][lane] = 0ull;
-        T[1][lane] = f1;
-        T[2][lane] = f2;
-        T[3][lane] = f3;
-        T[4][lane] = f4;
-        T[5][lane] = f5;
-        T[6][lane] = f6;
-        T[7][lane] = f7;
-        T[8][lane] = f8;
-        T[9][lane] = f8 ^ f1;
-        T[10][lane] = f8 ^ f2;
-        T[11][lane] = f8 ^ f3;
-        T[12][lane] = f8 ^ f4;
-        T[13][lane] = f8 ^ f5;
-        T[14][lane] = f8 ^ f6;
-        T[15][lane] = f8 ^ f7;
-    }
-    // output words: lane l < 32 writes word l & 1 of entry l >> 1
-    const int e = lane >> 1, q = lane & 1;
-    uint64_t z = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint64_t zi = ((gr.present >> i) & 1u) ? (q ? readlane64(gr.z[i], 1) : readlane64(gr.z[i], 0)) : 0ull;
-        z ^= ((e >> i) & 1) ? zi : 0ull;
-    }
-    if (lane < 32) L.tz[base + e][q] = z;
-}
-
-// reduce the wavefront's block rows by the tables of round r in buffer buf
-__device__ __forceinline__ void apply_round(const LargeShared& L, int r, int buf, uint64_t (&acc)[kLgSlots],
-                                            uint64_t& yv, int lane, bool act) {
-    const int pw = r >> 1, h = r & 1;
-    const uint64_t pmw = L.pm[pw];
-    uint32_t s[kLgSlots];
-#pragma unroll
-    for (int k = 0; k < kLgSlots; ++k) s[k] = static_cast<uint32_t>((readlane64(acc[k], pw) & pmw) >> (32 * h));
-    const uint32_t sy = spread_slots(s, lane);
-    const uint32_t present = static_cast<uint32_t>(pmw >> (32 * h));
-#pragma unroll
-    for (int g = 0; g < kLgRoundTables; g += 2) {  // two tables at a time, one three-input XOR
-        if (((present >> (4 * g)) & 0xffu) == 0) continue;
-        const int b0 = buf * kLgBuf + kLgEnt * g, b1 = b0 + kLgEnt;
-        // all reads issued before the first use (entries are zero in the inactive lanes,
-        // and every table of the round is written, absent rows as zero)
-        uint64_t t0[kLgSlots], t1[kLgSlots];
-#pragma unroll
-        for (int k = 0; k < kLgSlots; ++k) {
-            t0[k] = L.tf[b0 + ((s[k] >> (4 * g)) & 15u)][lane];
-            t1[k] = L.tf[b1 + ((s[k] >> (4 * g + 4)) & 15u)][lane];
+// reduce the block by list rows pos .. nrows - 1 (pos starts a batch)
+__device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_t X, int W, int fw, int pos, int nrows,
+                                            BlockRows& b) {
+    const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = wave >> 1;
+    const bool hb = wave & 1;
+    const int voff = 16 * (2 * j < fw ? j : 0);
+    char* const tab = reinterpret_cast<char*>(&L.tab[0][0][0]);
+    const int wbase = ((16 * t + (hb ? 8 : 0) + 4 * h) * 32 + j) * 16;
+    auto batch_len = [&](int p0) {
+        const bool in = p0 + lane < nrows;
+        const uint64_t last = __ballot(in && (L.piv[in ? p0 + lane : 0] & kPivLast));
+        const int left = nrows - p0 < 64 ? nrows - p0 : 64;
+        const int k = last ? ffs64(last) + 1 : 64;
+        return k < left ? k : left;
+    };
+    auto fetch = [&](int start, int cnt, bool fresh, RoundRows& r) {
+        if (4 * (t & ~1) >= cnt) return;
+        // the first rows of a batch may share a cache line with the batch before it, read
+        // before they were written
+        if (fresh && t == 0) load_rows<true>(X, W, fw, start, cnt, t, hb, voff, lane, r);
+        else load_rows<false>(X, W, fw, start, cnt, t, hb, voff, lane, r);
+    };
+    auto store_tables = [&](int buf, int cnt, const RoundRows& r) {
+        if (4 * (t & ~1) >= cnt) return;
+        const uint32_t mh = h ? ~0u : 0u;
+        u32x4 base = {r.f[2].x & mh, r.f[2].y & mh, r.f[2].z & mh, r.f[2].w & mh};
+        if (hb) base ^= r.f[3];
+        char* e = tab + 65536 * buf + wbase;
+        *reinterpret_cast<u32x4*>(e) = base;
+        *reinterpret_cast<u32x4*>(e + 512) = base ^ r.f[0];
+        *reinterpret_cast<u32x4*>(e + 1024) = base ^ r.f[1];
+        *reinterpret_cast<u32x4*>(e + 1536) = xor3_4(base, r.f[0], r.f[1]);
+        if (!hb && lane < 4) L.ys[32 * buf + 4 * t + lane] = r.y;
+    };
+    int K = batch_len(pos), half = 0, cnt = K < 32 ? K : 32, buf = 0;
+    RoundRows rr;
+    fetch(pos, cnt, true, rr);
+    store_tables(0, cnt, rr);
+    __syncthreads();
+    uint64_t s[4];
+    for (;;) {
+        // the next round: the batch's second half, or the next batch
+        int npos = pos, nK = K, nhalf = 1, ncnt = 0;
+        if (half == 0 && K > 32) {
+            ncnt = K - 32;
+        } else {
+            npos = pos + K;
+            nhalf = 0;
+            if (npos < nrows) {
+                nK = batch_len(npos);
+                ncnt = nK < 32 ? nK : 32;
+            }
         }
-        const uint64_t ty0 = L.tz[b0 + ((sy >> (4 * g)) & 15u)][lane & 1];
-        const uint64_t ty1 = L.tz[b1 + ((sy >> (4 * g + 4)) & 15u)][lane & 1];
+        if (ncnt) fetch(npos + 32 * nhalf, ncnt, nhalf == 0, rr);
+        if (half == 0) {  // the rows' bits at the batch's pivots: bit i of s[k] selects batch row i for row 4 w + k
+            const int p = lane < K ? (L.piv[pos + lane] & (kPivLast - 1)) : 0;
 #pragma unroll
-        for (int k = 0; k < kLgSlots; ++k) acc[k] = xor3(acc[k], t0[k], t1[k]);
-        yv = xor3(yv, ty0, ty1);
+            for (int i = 0; i < 2; ++i) {
+                *reinterpret_cast<u32x4*>(&L.sel[wave][h][4 * j]) = b.acc[i];
+                wave_sync();
+                const uint32_t d0 = L.sel[wave][0][p >> 5], d1 = L.sel[wave][1][p >> 5];
+                s[2 * i] = __ballot(lane < K && ((d0 >> (p & 31)) & 1u));
+                s[2 * i + 1] = __ballot(lane < K && ((d1 >> (p & 31)) & 1u));
+                wave_sync();
+            }
+        }
+        uint32_t sv[2], sy;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t s0 = static_cast<uint32_t>(half ? s[2 * i] >> 32 : s[2 * i]);
+            const uint32_t s1 = static_cast<uint32_t>(half ? s[2 * i + 1] >> 32 : s[2 * i + 1]);
+            sv[i] = h ? s1 : s0;
+            if (i == 0) sy = (lane & 1) ? s1 : s0;
+            else sy = (lane & 2) ? ((lane & 1) ? s1 : s0) : sy;
+        }
+        const char* lb = tab + 65536 * buf + 16 * j;
+#pragma unroll
+        for (int g = 0; g < 8; g += 2) {
+            if (4 * g >= cnt) break;
+            u32x4 t0[2], t1[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                t0[i] = *reinterpret_cast<const u32x4*>(lb + (__builtin_amdgcn_ubfe(sv[i], 4 * g, 4) << 9) + g * 8192);
+                t1[i] = *reinterpret_cast<const u32x4*>(lb + (__builtin_amdgcn_ubfe(sv[i], 4 * g + 4, 4) << 9) + (g + 1) * 8192);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) b.acc[i] = xor3_4(b.acc[i], t0[i], t1[i]);
+        }
+        {  // output words: lane (table, row) adds the table's selected rows
+            const int ty = (lane >> 2) & 7;
+            const uint32_t nib = lane < 32 ? sy >> (4 * ty) : 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                b.y = xor_and4(b.y, static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(nib), i, 1)),
+                               L.ys[32 * buf + 4 * ty + i]);
+        }
+        if (ncnt) store_tables(buf ^ 1, ncnt, rr);
+        __syncthreads();
+        if (!ncnt) break;
+        pos = npos;
+        K = nK;
+        half = nhalf;
+        cnt = ncnt;
+        buf ^= 1;
     }
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) b.y ^= shfl_xor4(b.y, o);  // every lane: the whole of its row
 }
 
-// new pivot of a row (lane = word): highest-priority set feature, the constant last; -1 if none
-__device__ __forceinline__ int row_pivot(uint64_t F, int n, int cw, uint64_t cbit, int lane) {
-    const uint64_t Fx = (lane == cw) ? (F & ~cbit) : F;
-    const uint64_t nzx = __ballot(Fx != 0);
-    if (nzx) {
-        const int top = msb64(nzx);
-        return 64 * top + msb64(readlane64(Fx, top));
-    }
-    return (readlane64(F, cw) & cbit) ? n : -1;
-}
-
-// G workgroups may fit one context together (member g): each reduces the block
-// by the tables of its own pivot words and the partial sums are exchanged
-// through the context's tables buffer (free until the outputs are written); the
-// in-block elimination runs in every member on identical data; each member
-// back-substitutes and stores the rows of its own pivot words; member 0 writes
-// the outputs.
-__device__ __forceinline__ void fit_ctx_large(const FitArgs& a, const CtxDesc& ds, LargeShared& L, int G, int g,
-                                              int* bar, int& epoch) {
+// full rank: the map by a triangular solve.  Row p (of pivot p) has its highest bit at p,
+// so from the lowest-priority word up: the 64 rows of a word are solved in order by one
+// wavefront, then every row above adds the solved rows that its bits in that word
+// select, through 16 tables of 16 entries.  Thread (tid, r) holds row p = tid + 1024 r.
+// One 32-bit column u of the four of the output word (they are independent: the members
+// share them out).  Latency-bound: two barriers per word.
+__device__ __forceinline__ void solve_map(const FitArgs& a, const CtxDesc& ds, WideShared& L, const uint64_t* X, int u) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = ds.c;
-    const int n = ds.n;
-    const int fw = feat_words(n), W = fw + F2_Y_WORDS, d = n + 1;
-    const int64_t m = ds.m;
-    const uint64_t* R = a.rows + ds.row0;
-    const uint64_t tmask = top_mask(n, fw);
-    const uint64_t lmask = lane < fw ? (lane == fw - 1 ? tmask : ~0ull) : 0ull;  // valid bits of word `lane`
-    const int cw = n >> 6;
+    const int n = ds.n, d = n + 1, fw = feat_words(n), W = fw + F2_Y_WORDS, cw = n >> 6;
     const uint64_t cbit = 1ull << (n & 63);
-    uint64_t* B = a.basis + a.basis_off[c];
-    constexpr long long kNone = 0x7fffffffffffffffll;
-
-    if (tid < 64) L.pm[tid] = 0;
-    if (tid == 0) {
-        L.contra = 0;
-        L.timeout = 0;
-        L.firstMin = kNone;
+    uint16_t* inv = reinterpret_cast<uint16_t*>(&L.tab[0][0][0]);              // [4096] list index of pivot p
+    uint32_t* zs = reinterpret_cast<uint32_t*>(&L.tab[0][16][0]);              // [2][64]
+    uint32_t* zt = reinterpret_cast<uint32_t*>(&L.tab[0][20][0]);              // [2][256]
+    __syncthreads();
+    for (int i = tid; i < d; i += kWdThreads) inv[L.piv[i] & (kPivLast - 1)] = static_cast<uint16_t>(i);
+    __syncthreads();
+    const uint64_t* row[4];
+    uint32_t z[4];
+    bool has[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int p = tid + kWdThreads * r;
+        has[r] = p < n;
+        const int idx = inv[p < d ? p : 0];
+        row[r] = X + static_cast<int64_t>(idx < d ? idx : 0) * W;
+        z[r] = reinterpret_cast<const uint32_t*>(row[r] + fw)[u];
+        if (p == n) zs[0] = z[r];  // the constant's row: its features are the constant alone
     }
-    int rank = 0;
-    int64_t b0 = 0;
-    for (int blk = 0; b0 < m && rank < d; b0 += kLargeRows, ++blk) {
-        const int nb = static_cast<int>((m - b0) < kLargeRows ? (m - b0) : kLargeRows);
-        if (tid < 64) {
-            L.npm[tid] = 0;
-            L.rowPiv[tid] = -1;
-        }
-        // block rows: slot k of wavefront w is block row 8w + k
-        uint64_t acc[kLgSlots], yv;
+    __syncthreads();
 #pragma unroll
-        for (int k = 0; k < kLgSlots; ++k) {
-            const int i = kLgSlots * wave + k;
-            acc[k] = (i < nb && lane < fw) ? (R[(b0 + i) * W + lane] & lmask) : 0ull;
-        }
-        {
-            const int i = kLgSlots * wave + (lane >> 1);
-            yv = (lane < 2 * kLgSlots && i < nb) ? R[(b0 + i) * W + fw + (lane & 1)] : 0ull;
-        }
-        // drain the row loads here: left outstanding, they would make every later wait
-        // inside the reduce loop a wait for all memory operations
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        // active lanes: feature words with at least one column that is not a retained pivot
-        const bool act = lane < fw && (L.pm[lane] | ~lmask) != ~0ull;
-
-        // (1) block reduce against the retained basis, half a pivot word per round
-        if (rank > 0) {
-            GroupRows gA, gB;
-            int r = next_round(L, fw, -1, G, g);
-            if (r >= 0) {
-                load_group(L, B, W, fw, n, r, wave, lane, gA);
-                write_table(L, kLgEnt * wave, gA, lane, act);
-            }
-            int rn = r >= 0 ? next_round(L, fw, r, G, g) : -1;
-            if (rn >= 0) load_group(L, B, W, fw, n, rn, wave, lane, gA);
-            __syncthreads();
-            int buf = 0;
-            while (r >= 0) {
-                const int rnn = rn >= 0 ? next_round(L, fw, rn, G, g) : -1;
-                if (rnn >= 0) load_group(L, B, W, fw, n, rnn, wave, lane, gB);
-                apply_round(L, r, buf, acc, yv, lane, act);
-                if (rn >= 0) write_table(L, (buf ^ 1) * kLgBuf + kLgEnt * wave, gA, lane, act);
-                __syncthreads();
-                r = rn;
-                rn = rnn;
-                gA = gB;
-                buf ^= 1;
-            }
-            if (G > 1) {
-                // member o holds X + P_o (X the unreduced rows, P_o its tables' sum); the
-                // reduced rows are X + sum P_o = X + sum (X + P_o) for an even G
-                uint64_t* X = a.tables + a.basis_off[c];
-                const int64_t xs = static_cast<int64_t>(kLargeRows) * W;  // one member's block
-                uint64_t* mine = X + ((blk & 1) * G + g) * xs;
-                const int yi = kLgSlots * wave + (lane >> 1);
+    for (int r = 0; r < 4; ++r) {
+        z[r] ^= has[r] && (row[r][cw] & cbit) ? zs[0] : 0u;
+    }
+    __syncthreads();
+    for (int w0 = 0; w0 < fw; w0 += 4) {
+        uint64_t uw[4][4];  // words w0 .. w0 + 3 of the rows (past a row's end: not used)
 #pragma unroll
-                for (int k = 0; k < kLgSlots; ++k)
-                    if (act) put_dev(mine + (kLgSlots * wave + k) * W + lane, acc[k]);
-                if (lane < 2 * kLgSlots) put_dev(mine + yi * W + fw + (lane & 1), yv);
-                group_barrier(bar, epoch, G, a.spin_limit, &L.timeout, false);
-                // reads past a partial's rows land in another partial or past the
-                // resource (zero); their values are masked off
-                const __amdgpu_buffer_rsrc_t xr = dev_rsrc(X + (blk & 1) * G * xs, static_cast<uint32_t>(8 * G * xs));
-                for (int o = 0; o < G; ++o) {
-                    if (o == g) continue;
-                    const uint32_t ob = static_cast<uint32_t>(o * xs);
-                    uint64_t v[kLgSlots];
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int k = 0; k < kLgSlots; ++k) v[k] = get_dev(xr, ob + (kLgSlots * wave + k) * W + lane);
-                    const uint64_t vy = get_dev(xr, ob + yi * W + fw + (lane & 1));
-#pragma unroll
-                    for (int k = 0; k < kLgSlots; ++k) acc[k] ^= act ? v[k] : 0ull;
-                    yv ^= lane < 2 * kLgSlots ? vy : 0ull;
-                }
-#pragma unroll
-                for (int k = 0; k < kLgSlots; ++k) {  // + X, reloaded
-                    const int i = kLgSlots * wave + k;
-                    if (act && i < nb) acc[k] ^= R[(b0 + i) * W + lane] & lmask;
-                }
-                if (lane < 2 * kLgSlots && yi < nb) yv ^= R[(b0 + yi) * W + fw + (lane & 1)];
+            for (int i = 0; i < 4; ++i) {
+                const int w = w0 + i;
+                uw[r][i] = (has[r] && w < fw && w <= ((tid + kWdThreads * r) >> 6)) ? row[r][w] & (w == cw ? cbit - 1 : ~0ull) : 0ull;
             }
 #pragma unroll
-            for (int k = 0; k < kLgSlots; ++k) acc[k] = act ? acc[k] : 0ull;
-        }
-
-        // (2) in-block elimination.  Rows whose features reduced to zero are
-        //     redundant or contradictory whatever the other block rows hold.
-        int ncon = 0;
-        long long firstc = kNone;
-        unsigned long long mine = 0;
-#pragma unroll
-        for (int k = 0; k < kLgSlots; ++k) {
-            const int i = kLgSlots * wave + k;
-            if (__ballot(acc[k] != 0)) {
-                mine |= 1ull << k;
-            } else if (i < nb) {
-                if ((readlane64(yv, 2 * k) | readlane64(yv, 2 * k + 1)) != 0) {
-                    ++ncon;
-                    if (firstc == kNone) firstc = b0 + i;
+        for (int i = 0; i < 4; ++i) {
+            const int w = w0 + i;
+            if (w >= fw) break;
+            uint32_t* zw = zs + 64 * (i & 1);
+            uint32_t* tw = zt + 256 * (i & 1);
+            if (wave == (w & 15)) {  // the word's own rows, lowest first
+                const int rr = w >> 4;
+                uint64_t v = rr == 0 ? uw[0][i] : rr == 1 ? uw[1][i] : rr == 2 ? uw[2][i] : uw[3][i];
+                v &= ~(1ull << lane);
+                uint32_t q = rr == 0 ? z[0] : rr == 1 ? z[1] : rr == 2 ? z[2] : z[3];
+#pragma unroll 8
+                for (int bb = 0; bb < 64; ++bb) {
+                    const uint32_t vh = bb < 32 ? static_cast<uint32_t>(v) : static_cast<uint32_t>(v >> 32);
+                    const uint32_t m = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(vh), bb & 31, 1));
+                    q = __builtin_amdgcn_bitop3_b32(q, m, __builtin_amdgcn_readlane(q, bb), 0x78);
                 }
-            }
-        }
-        for (int ph = 0; ph < kLargeWaves; ++ph) {
-            const int bq = ph & 1;
-            const int tb = kLgSlots * bq;  // this phase's published rows in tf (the reduce is done with it)
-            if (wave == ph) {  // this wavefront's rows in order; earlier wavefronts' pivots already applied
-                unsigned newSlots = 0;
+                zw[lane] = 64 * w + lane < n ? q : 0u;
 #pragma unroll
-                for (int s = 0; s < kLgSlots; ++s) {
-                    if (!((mine >> s) & 1ull)) continue;
-                    const int i = kLgSlots * ph + s;
-                    const uint64_t F = acc[s];
-                    const int p = row_pivot(F, n, cw, cbit, lane);
-                    const uint64_t Y0 = readlane64(yv, 2 * s), Y1 = readlane64(yv, 2 * s + 1);
-                    if (p < 0) {  // dependent on the earlier rows: redundant, or contradictory
-                        if ((Y0 | Y1) != 0) {
-                            ++ncon;
-                            if (firstc > b0 + i) firstc = b0 + i;
-                        }
-                        continue;
-                    }
-                    const int pw = p >> 6, pb = p & 63;
-                    // bit p of the wavefront's rows: gathered in every lane, read from lane pw
-                    uint32_t bits = 0;
-#pragma unroll
-                    for (int t = 0; t < kLgSlots; ++t) bits |= static_cast<uint32_t>((acc[t] >> pb) & 1ull) << t;
-                    const uint32_t hits = __builtin_amdgcn_readlane(bits, pw) & ~(1u << s);
-#pragma unroll
-                    for (int t = 0; t < kLgSlots; ++t) acc[t] = xor_and(acc[t], ((hits >> t) & 1u) ? ~0u : 0u, F);
-                    uint32_t em = hits;  // slot t -> output-word lanes 2t, 2t+1
-                    em = (em | (em << 4)) & 0x0f0fu;
-                    em = (em | (em << 2)) & 0x3333u;
-                    em = (em | (em << 1)) & 0x5555u;
-                    em |= em << 1;
-                    yv = xor_and(yv, lanes_of(em, lane), (lane & 1) ? Y1 : Y0);
-                    newSlots |= 1u << s;
-                    if (lane == 0) {
-                        L.rowPiv[i] = p;
-                        atomicOr(reinterpret_cast<unsigned long long*>(&L.npm[pw]), 1ull << pb);
-                    }
-                }
-                // publish the new rows, now fully reduced among themselves, in slot order
-                const int np = __popc(newSlots);
-#pragma unroll
-                for (int s = 0; s < kLgSlots; ++s) {
-                    if (!((newSlots >> s) & 1u)) continue;
-                    const int q = __popc(newSlots & ((1u << s) - 1u));
-                    L.tf[tb + q][lane] = acc[s];
-                    if ((lane >> 1) == s) L.tz[tb + q][lane & 1] = yv;
-                    if (lane == 0) L.pubP[bq][q] = L.rowPiv[kLgSlots * ph + s];
-                }
-                if (lane == 0) L.pubN[bq] = np;
+                for (int k = 0; k < 4; ++k) z[k] = rr == k ? q : z[k];
             }
             __syncthreads();
-            const int np = L.pubN[bq];
-            if (wave != ph && np > 0) {  // the published rows: selection bits at their pivots, then the rows
-                const int pk = lane < np ? L.pubP[bq][lane] : 0;
-                const int pkw = pk >> 6, pkb = pk & 63;
-                uint32_t sel[kLgSlots];
-                uint64_t wv[kLgSlots];
+            if (tid < 256) {
+                uint32_t v = 0;
 #pragma unroll
-                for (int k = 0; k < kLgSlots; ++k) wv[k] = shfl64(acc[k], pkw);
-#pragma unroll
-                for (int k = 0; k < kLgSlots; ++k)
-                    sel[k] = static_cast<uint32_t>(__ballot(lane < np && ((wv[k] >> pkb) & 1ull)));
-                const uint32_t sy = spread_slots(sel, lane);
-                for (int q = 0; q < np; ++q) {
-                    const uint64_t Fv = L.tf[tb + q][lane];
-                    const uint64_t Zv = L.tz[tb + q][lane & 1];
-#pragma unroll
-                    for (int k = 0; k < kLgSlots; ++k) acc[k] = xor_and(acc[k], ((sel[k] >> q) & 1u) ? ~0u : 0u, Fv);
-                    yv = xor_and(yv, 0u - ((sy >> q) & 1u), Zv);
-                }
-            }
-        }
-        if (lane == 0 && ncon) {
-            atomicAdd(&L.contra, ncon);
-            atomicMin(&L.firstMin, firstc);
-        }
-        __syncthreads();
-
-        // (3) new rows in descending priority: position = new pivots above it
-        if (wave == 0) {
-            const uint64_t v = L.npm[lane] & ((lane == cw) ? ~cbit : ~0ull);
-            const int cnt = lane < fw ? __popcll(v) : 0;
-            int x = cnt;  // inclusive scan from the top word down
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_down(x, o);
-                if (lane + o < 64) x += t;
-            }
-            L.above[lane] = x - cnt;
-            const int total = __shfl(x, 0) + ((L.npm[cw] & cbit) ? 1 : 0);
-            if (lane == 0) L.nnew = total;
-        }
-        __syncthreads();
-        const int K = L.nnew;
-        if (K > 0) {
-#pragma unroll
-            for (int k = 0; k < kLgSlots; ++k) {
-                const int i = kLgSlots * wave + k;
-                const int p = L.rowPiv[i];
-                if (p < 0) continue;
-                int pos = K - 1;
-                if (p != n) {
-                    uint64_t v = L.npm[p >> 6];
-                    if ((p >> 6) == cw) v &= ~cbit;
-                    v &= (p & 63) == 63 ? 0ull : (~0ull << ((p & 63) + 1));
-                    pos = L.above[p >> 6] + __popcll(v);
-                }
-                const int e = kLgEnt * (pos >> 2) + (1 << (pos & 3));
-                L.tf[e][lane] = acc[k];
-                if ((lane >> 1) == k) L.tz[e][lane & 1] = yv;
-                if (lane == 0) L.nsorted[pos] = p;
+                for (int q = 0; q < 4; ++q) v ^= ((tid >> q) & 1) ? zw[4 * (tid >> 4) + q] : 0u;
+                tw[tid] = v;
             }
             __syncthreads();
-            // complete the tables: groups w and w + 8, missing rows of the last group are zero
-            const int NG = (K + 3) >> 2;
-            for (int g = wave; g < NG; g += kLargeWaves) {
-                GroupRows gr;
-                gr.present = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (!has[r] || ((tid + kWdThreads * r) >> 6) <= w) continue;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    const uint32_t vh = q < 8 ? static_cast<uint32_t>(uw[r][i]) : static_cast<uint32_t>(uw[r][i] >> 32);
+                    z[r] ^= tw[16 * q + __builtin_amdgcn_ubfe(vh, 4 * (q & 7), 4)];
+                }
+            }
+        }
+    }
+    // columns of the map, and the output words of the basis rows (unit vectors, written by all members)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int p = tid + kWdThreads * r;
+        if (p >= d) continue;
+        reinterpret_cast<uint32_t*>(a.maps + ds.mo + 2 * p)[u] = z[r];
+        reinterpret_cast<uint32_t*>(a.basis + ds.bo + static_cast<int64_t>(p < n ? n - 1 - p : n) * W + fw)[u] = z[r];
+    }
+    __syncthreads();
+}
+
+// full rank: this member's remaining blocks (blk, blk + G, ...) lie in the span; a row's
+// residual is y + M phi, from tables of the map's columns, four columns each, 32 words
+// of phi (128 KB of tables) at a time.  Each thread takes up to four rows.
+__device__ __forceinline__ void check_rows(const FitArgs& a, const CtxDesc& ds, WideShared& L, int blk, int G, int nblk,
+                                           int& ncon, long long& firstc) {
+    const int tid = threadIdx.x;
+    const int n = ds.n, d = n + 1, fw = feat_words(n), W = fw + F2_Y_WORDS;
+    const uint64_t tmask = top_mask(n, fw);
+    const u32x4_a8* M = reinterpret_cast<const u32x4_a8*>(a.maps + ds.mo);
+    u32x4* tab = &L.tab[0][0][0];  // [512][16]
+    for (int b0 = blk; b0 < nblk; b0 += 64 * G) {  // up to 64 blocks: 4,096 rows
+        const uint64_t* row[4];
+        int64_t ri[4];
+        u32x4 z[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int bk = b0 + G * (16 * k + (tid >> 6));
+            ri[k] = bk < nblk ? static_cast<int64_t>(bk) * kWdRows + (tid & 63) : ds.m;
+            row[k] = a.rows + ds.row0 + (ri[k] < ds.m ? ri[k] : 0) * W;
+            z[k] = *reinterpret_cast<const u32x4_a8*>(row[k] + fw);
+        }
+        for (int w0 = 0; w0 < fw; w0 += 32) {
+            __syncthreads();
+            if (tid < 512 && 64 * w0 + 4 * tid < d) {
+                u32x4 c[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const bool has = 4 * g + q < K;
-                    gr.present |= has ? (1u << q) : 0u;
-                    gr.f[q] = has ? L.tf[kLgEnt * g + (1 << q)][lane] : 0ull;
-                    gr.z[q] = has ? L.tz[kLgEnt * g + (1 << q)][lane & 1] : 0ull;
+                    const int col = 64 * w0 + 4 * tid + q;
+                    c[q] = u32x4{0, 0, 0, 0};
+                    if (col < d) c[q] = M[col];
                 }
-                __builtin_amdgcn_wave_barrier();
-                write_table(L, kLgEnt * g, gr, lane, true);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    u32x4 v = {0, 0, 0, 0};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if ((e >> q) & 1) v ^= c[q];
+                    tab[16 * tid + (e ^ (tid & 15))] = v;  // entries rotated by the table: fewer bank conflicts
+                }
             }
             __syncthreads();
-
-            // (3') clear the new pivots from the retained rows: positions wave, wave + 8, ...
-            //      of every retained pivot word, one register per row, the next word's rows
-            //      loaded while this word's are updated
-            const int pk = lane < K ? L.nsorted[lane] : 0;
-            const int pkw = pk >> 6, pkb = pk & 63;
-            const uint64_t mineBits = 0x0101010101010101ull << wave;
-            auto next_word = [&](int pw) {  // this member's pivot words only
-                for (++pw; pw < fw; ++pw)
-                    if ((pw & (G - 1)) == g && (L.pm[pw] & mineBits)) return pw;
-                return -1;
-            };
-            auto load_rows = [&](int pw, uint64_t (&Bv)[kLgSlots], uint64_t& yb) {  // raw: masked where used
 #pragma unroll
-                for (int q = 0; q < kLgSlots; ++q) {
-                    const int b = wave + kLargeWaves * q;
-                    Bv[q] = B[static_cast<int64_t>(prio_slot(64 * pw + b, n)) * W + (lane < fw ? lane : 0)];
-                }
-                const int b = wave + kLargeWaves * ((lane >> 1) & 7);
-                yb = B[static_cast<int64_t>(prio_slot(64 * pw + b, n)) * W + fw + (lane & 1)];
-            };
-            uint64_t Bv[kLgSlots], yb, Bn[kLgSlots], ybn;
-            int pw = next_word(-1);
-            if (pw >= 0) load_rows(pw, Bv, yb);
-            while (pw >= 0) {
-                const int pwn = next_word(pw);
-                if (pwn >= 0) load_rows(pwn, Bn, ybn);
-                const uint64_t pmw = L.pm[pw];
-#pragma unroll
-                for (int q = 0; q < kLgSlots; ++q) Bv[q] = (act && ((pmw >> (wave + kLargeWaves * q)) & 1ull)) ? Bv[q] : 0ull;
-                yb = (lane < 2 * kLgSlots && ((pmw >> (wave + kLargeWaves * (lane >> 1))) & 1ull)) ? yb : 0ull;
-                uint64_t sv[kLgSlots], wv[kLgSlots];
-#pragma unroll
-                for (int q = 0; q < kLgSlots; ++q) wv[q] = shfl64(Bv[q], pkw);  // all exchanges in flight together
-#pragma unroll
-                for (int q = 0; q < kLgSlots; ++q) sv[q] = __ballot(lane < K && ((wv[q] >> pkb) & 1ull));
-                const uint64_t svy = spread_slots(sv, lane);
-                for (int g = 0; g < NG; g += 2) {  // two tables at a time (the second may not exist)
-                    const bool two = g + 1 < NG;
-                    uint64_t t0[kLgSlots], t1[kLgSlots];
-#pragma unroll
-                    for (int q = 0; q < kLgSlots; ++q) {
-                        t0[q] = L.tf[kLgEnt * g + ((sv[q] >> (4 * g)) & 15u)][lane];
-                        t1[q] = two ? L.tf[kLgEnt * (g + 1) + ((sv[q] >> (4 * g + 4)) & 15u)][lane] : 0ull;
-                    }
-                    const uint64_t ty0 = L.tz[kLgEnt * g + ((svy >> (4 * g)) & 15u)][lane & 1];
-                    const uint64_t ty1 = two ? L.tz[kLgEnt * (g + 1) + ((svy >> (4 * g + 4)) & 15u)][lane & 1] : 0ull;
-#pragma unroll
-                    for (int q = 0; q < kLgSlots; ++q) Bv[q] = xor3(Bv[q], t0[q], t1[q]);
-                    yb = xor3(yb, ty0, ty1);
-                }
-#pragma unroll
-                for (int q = 0; q < kLgSlots; ++q) {
-                    const int b = wave + kLargeWaves * q;
-                    if (!((pmw >> b) & 1ull)) continue;
-                    uint64_t* row = B + static_cast<int64_t>(prio_slot(64 * pw + b, n)) * W;
-                    if (act) row[lane] = Bv[q];
-                    if ((lane >> 1) == q) row[fw + (lane & 1)] = yb;
-                }
-                pw = pwn;
-#pragma unroll
-                for (int q = 0; q < kLgSlots; ++q) Bv[q] = Bn[q];
-                yb = ybn;
-            }
-            // (4) insert the new rows at their priority slots (every word: fresh slots)
-            for (int pos = wave; pos < K; pos += kLargeWaves) {
-                if (((L.nsorted[pos] >> 6) & (G - 1)) != g) continue;  // another member's pivot word
-                const int e = kLgEnt * (pos >> 2) + (1 << (pos & 3));
-                uint64_t* row = B + static_cast<int64_t>(prio_slot(L.nsorted[pos], n)) * W;
-                if (lane < fw) row[lane] = L.tf[e][lane];
-                if (lane < 2) row[fw + lane] = L.tz[e][lane];
-            }
-            __syncthreads();
-            if (tid < 64) L.pm[tid] |= L.npm[tid];
-        }
-        __syncthreads();
-        rank += K;
-    }
-
-    if (G > 1) group_barrier(bar, epoch, G, a.spin_limit, &L.timeout);  // every member's basis rows written
-    if (b0 < m) {
-        // full rank: every remaining row lies in the span; its residual is y + M phi
-        // (members of a group take every G-th 512-row chunk)
-        uint64_t (*sZ)[2] = reinterpret_cast<uint64_t (*)[2]>(&L.tf[0][0]);
-        long long firstCons = kNone;
-        int ncons = 0;
-        for (int jj = tid; jj < d; jj += kLargeThreads) {
-            const uint64_t* row = B + static_cast<int64_t>(prio_slot(jj, n)) * W;
-            sZ[jj][0] = row[fw];
-            sZ[jj][1] = row[fw + 1];
-        }
-        __syncthreads();
-        for (int64_t r0 = b0 + static_cast<int64_t>(g) * kLargeThreads; r0 < m; r0 += static_cast<int64_t>(G) * kLargeThreads) {
-            const int64_t i = r0 + tid;
-            if (i < m) {
-                const uint64_t* row = R + i * W;
-                uint64_t z0 = row[fw], z1 = row[fw + 1];
-                for (int w = 0; w < fw; ++w) {
-                    uint64_t v = row[w];
+            for (int k = 0; k < 4; ++k) {
+                if (ri[k] >= ds.m) continue;
+                for (int w = w0; w < fw && w < w0 + 32; ++w) {
+                    uint64_t v = row[k][w];
                     if (w == fw - 1) v &= tmask;
-                    while (v) {
-                        const int jj = 64 * w + ffs64(v);
-                        v &= v - 1;
-                        z0 ^= sZ[jj][0];
-                        z1 ^= sZ[jj][1];
-                    }
-                }
-                if (z0 | z1) {
-                    ++ncons;
-                    if (firstCons == kNone) firstCons = i;
-                }
-            }
-        }
-        if (G == 1) {
-            if (ncons) {
-                atomicAdd(&L.contra, ncons);
-                atomicMin(&L.firstMin, firstCons);
-            }
-            __syncthreads();
-        } else {  // members' counts through the exchange area, combined by member 0
-            __shared__ int sCnt;
-            __shared__ long long sFirst;
-            if (tid == 0) {
-                sCnt = 0;
-                sFirst = kNone;
-            }
-            __syncthreads();
-            if (ncons) {
-                atomicAdd(&sCnt, ncons);
-                atomicMin(&sFirst, firstCons);
-            }
-            __syncthreads();
-            int64_t* X = reinterpret_cast<int64_t*>(a.tables + a.basis_off[c]);
-            if (tid == 0) {
-                X[2 * g] = sCnt;
-                X[2 * g + 1] = sFirst;
-            }
-            group_barrier(bar, epoch, G, a.spin_limit, &L.timeout);
-            if (g == 0 && tid == 0) {
-                for (int o = 1; o < G; ++o) {
-                    L.contra += static_cast<int>(X[2 * o]);
-                    if (X[2 * o + 1] < L.firstMin) L.firstMin = X[2 * o + 1];
-                }
-                L.contra += sCnt;
-                if (sFirst < L.firstMin) L.firstMin = sFirst;
-            }
-            __syncthreads();
-        }
-    }
-    // the rank as the pivot set holds it: equal to the running count unless a
-    // timed-out exchange left members with different data, and then it keeps
-    // every output position below d
-    if (tid == 0) L.nnew = 0;
-    __syncthreads();
-    if (wave == 0 && lane < fw) atomicAdd(&L.nnew, __popcll(L.pm[lane] & lmask));
-    __syncthreads();
-    rank = L.nnew;
-    if (g != 0) {  // member 0 writes the outputs; the others only report a wait that gave up
-        if (tid == 0 && L.timeout) atomicOr(&a.ctx_flags[c], F2_CTX_SYNC_TIMEOUT);
-        return;
-    }
-
-    // outputs: canonical map and encode table from the slots, then compaction into descending priority
-    const int64_t po = a.piv_off[c], mo = a.map_off[c];
-    for (int jj = tid; jj < d; jj += kLargeThreads) {
-        const bool present = (L.pm[jj >> 6] >> (jj & 63)) & 1ull;
-        const uint64_t* row = B + static_cast<int64_t>(prio_slot(jj, n)) * W;
-        a.maps[mo + 2 * jj] = present ? row[fw] : 0ull;
-        a.maps[mo + 2 * jj + 1] = present ? row[fw + 1] : 0ull;
-    }
-    {  // parity-check rows of the free columns: per word pair (w, v), taken by wavefront
-       // v mod 8, a bit-matrix transpose of word w of the retained rows of pivots
-       // 64 v .. 64 v + 63 (zero for free columns) gives lane f word v of the row of
-       // free column 64 w + f
-        uint64_t* H = a.tables + a.basis_off[c];
-        if (has_parity_rows(d, rank)) {
-            const uint64_t lane_lt = (1ull << lane) - 1;
-            int base = 0;  // free columns in the words before w
-            for (int w = 0; w < fw; ++w) {
-                const uint64_t fr = ~L.pm[w] & (w == fw - 1 ? tmask : ~0ull);
-                if (!fr) continue;  // no free column in this word
-                const bool mine = (fr >> lane) & 1ull;
-                const int64_t i = base + __popcll(fr & lane_lt);
-                for (int v = wave; v < fw; v += kLargeWaves) {
-                    const int p = 64 * v + lane;
-                    const bool piv = (L.pm[v] >> lane) & 1ull;
-                    const uint64_t col = transpose64(piv ? B[static_cast<int64_t>(prio_slot(p, n)) * W + w] : 0ull, lane);
-                    if (mine) H[i * fw + v] = col | (v == w ? (1ull << lane) : 0ull);
-                }
-                base += __popcll(fr);
-            }
-        }
-    }
-    // pivots, and the basis rows moved from their slots to positions 0 .. rank-1: the
-    // row of slot t goes to position (present slots before t) <= t, so slots are moved
-    // in increasing order, 64 at a time (read all, barrier, write all)
-    if (wave == 0) {  // present slots in words above w (slot order = descending feature index, constant last)
-        const uint64_t v = L.pm[lane] & ((lane == cw) ? ~cbit : ~0ull);
-        const int cnt = lane < fw ? __popcll(v) : 0;
-        int x = cnt;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_down(x, o);
-            if (lane + o < 64) x += t;
-        }
-        L.above[lane] = x - cnt;
-    }
-    __syncthreads();
-    if (rank < d) {
-        for (int t0 = 0; t0 < d; t0 += kLargeRows) {
-            uint64_t w0[kLgSlots], w1[kLgSlots];
-            int kk[kLgSlots];
+                    const int nt = 64 * w + 64 <= d ? 16 : (d - 64 * w + 3) / 4;  // tables of this word
+                    const u32x4* tw = tab + 256 * (w - w0);
+                    if (nt == 16) {
 #pragma unroll
-            for (int q = 0; q < kLgSlots; ++q) {
-                const int t = t0 + kLgSlots * wave + q;
-                const int pt = t < d ? slot_pivot(t, n) : 0;
-                const bool present = t < d && ((L.pm[pt >> 6] >> (pt & 63)) & 1ull);
-                kk[q] = -1;
-                w0[q] = w1[q] = 0;
-                if (present) {
-                    const uint64_t* row = B + static_cast<int64_t>(t) * W;
-                    if (lane < W) w0[q] = row[lane];
-                    if (64 + lane < W) w1[q] = row[64 + lane];
-                    if (pt == n) {
-                        kk[q] = rank - 1;
+                        for (int q = 0; q < 16; q += 2)
+                            z[k] = xor3_4(z[k], tw[16 * q + ((static_cast<uint32_t>(v >> (4 * q)) & 15u) ^ q)],
+                                          tw[16 * q + 16 + ((static_cast<uint32_t>(v >> (4 * q + 4)) & 15u) ^ (q + 1))]);
                     } else {
-                        uint64_t v = L.pm[pt >> 6];
-                        if ((pt >> 6) == cw) v &= ~cbit;
-                        v &= (pt & 63) == 63 ? 0ull : (~0ull << ((pt & 63) + 1));
-                        kk[q] = L.above[pt >> 6] + __popcll(v);
+                        for (int q = 0; q < nt; ++q) z[k] ^= tw[16 * q + ((static_cast<uint32_t>(v >> (4 * q)) & 15u) ^ q)];
                     }
                 }
             }
-            __syncthreads();
+        }
 #pragma unroll
-            for (int q = 0; q < kLgSlots; ++q) {
-                if (kk[q] < 0) continue;
-                uint64_t* out = B + static_cast<int64_t>(kk[q]) * W;
-                if (lane < W) out[lane] = w0[q];
-                if (64 + lane < W) out[64 + lane] = w1[q];
+        for (int k = 0; k < 4; ++k)
+            if (ri[k] < ds.m && any4(z[k])) {
+                ++ncon;
+                if (ri[k] < firstc) firstc = ri[k];
+            }
+    }
+}
+
+// member g of the G workgroups that fit context ds together; seq numbers the group's contexts from 1
+__device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds, WideShared& L, int G, int g, uint64_t* prog,
+                                             int seq) {
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = ds.c, n = ds.n, d = n + 1, fw = feat_words(n), W = fw + F2_Y_WORDS, cw = n >> 6;
+    const int64_t m = ds.m;
+    const uint64_t* R = a.rows + ds.row0;
+    const uint64_t tmask = top_mask(n, fw), cbit = 1ull << (n & 63);
+    uint64_t* Xp = a.tables + ds.bo;
+    const __amdgpu_buffer_rsrc_t X = dev_rsrc(Xp, static_cast<uint32_t>(8 * d * W));
+    int32_t* ent = a.pivots + ds.po;
+    constexpr long long kNone = 0x7fffffffffffffffll;
+    const int nblk = m > static_cast<int64_t>(kWdMaxBlocks) * kWdRows ? 0x7fffffff : static_cast<int>((m + kWdRows - 1) / kWdRows);
+    if (nblk > kWdMaxBlocks) {  // block numbers past the tags: one member, which reads no tags
+        if (g != 0) {
+            if (tid == 0) put_progress(prog, g, seq, kWdBar + 2);
+            return;
+        }
+        G = 1;
+    }
+    const int64_t blocks = (m + kWdRows - 1) / kWdRows;
+    // valid bits of words 2 j and 2 j + 1, and the constant's bit
+    const uint64_t v0 = 2 * j < fw ? (2 * j == fw - 1 ? tmask : ~0ull) : 0ull;
+    const uint64_t v1 = 2 * j + 1 < fw ? (2 * j + 1 == fw - 1 ? tmask : ~0ull) : 0ull;
+    const u32x4 vm = {static_cast<uint32_t>(v0), static_cast<uint32_t>(v0 >> 32), static_cast<uint32_t>(v1),
+                      static_cast<uint32_t>(v1 >> 32)};
+    if (tid == 0) {
+        L.timeout = 0;
+        L.nrows = 0;
+        L.next = 0;
+        L.any[0] = L.any[1] = 0;
+    }
+    __syncthreads();
+    int nrows = 0;
+    int ncon = 0;
+    long long firstc = kNone;
+    int flip = 0;
+    // one pass of this loop: a block of this member (phase 0), then, below full rank, a
+    // batch of the list (phase 1) to be reduced by the later ones
+    int phase = 0, bpos = 0, bidx = 0, bK = 0;
+    int64_t blk = g;
+    bool full = false;
+    // wavefront 0: wait until every block below `until` is done (or, with bar > 0, every member
+    // past that barrier), then take the list's new entries
+    auto wait_for = [&](int64_t until, int bar) {
+        if (wave == 0) {
+            int open = 0;
+            bool ok = false;
+            if (!L.timeout) {
+                for (int spin = 0; spin < a.spin_limit; ++spin) {
+                    if (bar) {
+                        bool behind = false;
+                        if (lane < G && lane != g) {
+                            const uint64_t v = __hip_atomic_load(prog + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            const int s = static_cast<int>(v >> 32);
+                            behind = s < seq || (s == seq && static_cast<int>(v) < kWdBar + bar);
+                        }
+                        ok = __ballot(behind) == 0;
+                    } else {
+                        open = lowest_open(prog, G, g, seq, static_cast<int>(until));
+                        ok = open >= until;
+                    }
+                    if (ok) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                if (!ok && lane == 0) L.timeout = 1;
+            }
+            if (bar) open = 0x7fffffff;
+            if (bar != 2) {
+                const int k = take_entries(L, ent, nrows, d, open);
+                if (lane == 0) L.nrows = k;
+            }
+        }
+        __syncthreads();
+        nrows = __builtin_amdgcn_readfirstlane(L.nrows);
+    };
+    for (;;) {
+        if (phase == 0 && (blk >= blocks || nrows >= d)) {
+            if (G > 1) {  // every member past its blocks: the list is complete
+                __syncthreads();
+                if (tid == 0) put_progress(prog, g, seq, kWdBar + 1);
+                wait_for(0, 1);
+            }
+            __threadfence();  // no line of the list read before it was whole is read again
+            phase = 1;
+            full = nrows >= d;
+            // pivot columns and the counts above each word (descending-priority positions)
+            if (tid < 64) L.pm[tid] = 0;
+            __syncthreads();
+            for (int i = tid; i < nrows; i += kWdThreads) {
+                const int p = L.piv[i] & (kPivLast - 1);
+                atomicOr(reinterpret_cast<unsigned long long*>(&L.pm[p >> 6]), 1ull << (p & 63));
             }
             __syncthreads();
+            if (wave == 0) {
+                const uint64_t v = L.pm[lane] & ((lane == cw) ? ~cbit : ~0ull);
+                const int cnt = lane < fw ? __popcll(v) : 0;
+                int x = cnt;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int t = __shfl_down(x, o);
+                    if (lane + o < 64) x += t;
+                }
+                L.above[lane] = x - cnt;
+            }
+            __syncthreads();
+            if (full) break;
+        }
+        if (phase == 1) {  // the next batch of this member: every G-th
+            bool found = false;
+            while (bpos < nrows) {
+                const bool in = bpos + lane < nrows;
+                const uint64_t last = __ballot(in && (L.piv[in ? bpos + lane : 0] & kPivLast));
+                const int left = nrows - bpos < 64 ? nrows - bpos : 64;
+                const int k = last ? ffs64(last) + 1 : 64;
+                bK = k < left ? k : left;
+                if (bidx % G == g) {
+                    found = true;
+                    break;
+                }
+                bpos += bK;
+                ++bidx;
+            }
+            if (!found) break;
+        }
+        BlockRows b;
+        const int nb = phase == 1 ? bK : (m - blk * kWdRows < kWdRows ? static_cast<int>(m - blk * kWdRows) : kWdRows);
+        if (phase == 0) {
+            const uint64_t* rb = R + blk * kWdRows * W;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int r = 4 * wave + 2 * i + h;
+                const uint64_t* row = rb + static_cast<int64_t>(r < nb ? r : 0) * W;
+                b.acc[i] = *reinterpret_cast<const u32x4_a8*>(row + (2 * j < fw ? 2 * j : 0));
+                b.acc[i] &= vm & (r < nb ? ~0u : 0u);
+            }
+            const int r = 4 * wave + (lane & 3);
+            b.y = *reinterpret_cast<const u32x4_a8*>(rb + static_cast<int64_t>(r < nb ? r : 0) * W + fw);
+            b.y &= lane < 4 && r < nb ? ~0u : 0u;
+        } else {
+            const int voff = 16 * (2 * j < fw ? j : 0);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int r = 4 * wave + 2 * i + h;
+                b.acc[i] = load16<true>(X, (bpos + (r < nb ? r : 0)) * W * 8 + voff, 0);
+                b.acc[i] &= vm & (r < nb ? ~0u : 0u);
+            }
+            const int r = 4 * wave + (lane & 3);
+            b.y = load16<true>(X, ((bpos + (r < nb ? r : 0)) * W + fw) * 8, 0);
+            b.y &= lane < 4 && r < nb ? ~0u : 0u;
+        }
+        if (phase == 0 && G > 1) {  // what the other members have added meanwhile
+            if (wave == 0) {
+                const int open = lowest_open(prog, G, g, seq, static_cast<int>(blk));
+                const int k = take_entries(L, ent, nrows, d, open);
+                if (lane == 0) {
+                    L.nrows = k;
+                    L.next = open;
+                }
+            }
+            __syncthreads();
+            nrows = __builtin_amdgcn_readfirstlane(L.nrows);
+        }
+        int pos = phase == 1 ? bpos + bK : 0;
+        int open = G > 1 && phase == 0 ? __builtin_amdgcn_readfirstlane(L.next) : 0x7fffffff;
+        bool anynz = false;
+        for (;;) {
+            if (pos < nrows) {
+                wide_reduce(L, X, W, fw, pos, nrows, b);
+                pos = nrows;
+            } else {
+#pragma unroll
+                for (int o = 4; o < 64; o <<= 1) b.y ^= shfl_xor4(b.y, o);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) b.acc[i] &= vm;  // (the lanes past the row collected other words)
+            if (phase == 1) break;
+            if (__ballot(any4(b.acc[0]) || any4(b.acc[1])) && lane == 0) L.any[flip] = 1;
+            if (tid == 0) L.any[flip ^ 1] = 0;
+            __syncthreads();
+            anynz = __builtin_amdgcn_readfirstlane(L.any[flip]) != 0;
+            flip ^= 1;
+            if (!anynz || open >= blk) break;
+            wait_for(blk, 0);  // (ends the phase: every earlier block is done)
+            open = 0x7fffffff;
+            if (pos == nrows) break;
+            b.y &= lane < 4 ? ~0u : 0u;
+        }
+        if (phase == 1) {  // fully reduced rows to their final places
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int r = 4 * wave + 2 * i + h;
+                if (r < nb) {
+                    const int p = L.piv[bpos + r] & (kPivLast - 1);
+                    int k = nrows - 1;
+                    if (p != n) {
+                        uint64_t v = L.pm[p >> 6];
+                        if ((p >> 6) == cw) v &= ~cbit;
+                        v &= (p & 63) == 63 ? 0ull : (~0ull << ((p & 63) + 1));
+                        k = L.above[p >> 6] + __popcll(v);
+                    }
+                    uint64_t* out = a.basis + ds.bo + static_cast<int64_t>(k) * W;
+                    if (2 * j < fw) out[2 * j] = (static_cast<uint64_t>(b.acc[i].y) << 32) | b.acc[i].x;
+                    if (2 * j + 1 < fw) out[2 * j + 1] = (static_cast<uint64_t>(b.acc[i].w) << 32) | b.acc[i].z;
+                }
+            }
+            const int r = 4 * wave + lane;
+            if (lane < 4 && r < nb) {
+                const int p = L.piv[bpos + r] & (kPivLast - 1);
+                int k = nrows - 1;
+                if (p != n) {
+                    uint64_t v = L.pm[p >> 6];
+                    if ((p >> 6) == cw) v &= ~cbit;
+                    v &= (p & 63) == 63 ? 0ull : (~0ull << ((p & 63) + 1));
+                    k = L.above[p >> 6] + __popcll(v);
+                }
+                uint64_t* out = a.basis + ds.bo + static_cast<int64_t>(k) * W + fw;
+                const uint64_t y0 = (static_cast<uint64_t>(b.y.y) << 32) | b.y.x, y1 = (static_cast<uint64_t>(b.y.w) << 32) | b.y.z;
+                out[0] = y0;
+                out[1] = y1;
+                a.maps[ds.mo + 2 * p] = y0;
+                a.maps[ds.mo + 2 * p + 1] = y1;
+            }
+            bpos += bK;
+            ++bidx;
+            __syncthreads();
+            continue;
+        }
+        // (3) elimination in stream order on panels
+        uint64_t ins = 0;
+        if (anynz && nrows < d) {
+            u32x4* const Rm = &L.tab[0][0][0];                         // [64][kRowPitch]
+            u32x4* const ET = &L.tab[0][0][0] + kWdRows * kRowPitch;   // [128][32]: 8 tables
+            uint64_t pend = ~0ull;  // wavefront 0: rows not yet basis rows
+            int mypiv = 0;
+            for (;;) {
+                // the rows, and which words the pending ones hold (the constant apart)
+                uint32_t ev = 0, od = 0;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int r = 4 * wave + 2 * i + h;
+                    Rm[r * kRowPitch + j] = b.acc[i];
+                    const bool pe = !((ins >> r) & 1ull);
+                    const uint64_t w0 = ((static_cast<uint64_t>(b.acc[i].y) << 32) | b.acc[i].x) & (2 * j == cw ? ~cbit : ~0ull);
+                    const uint64_t w1 = ((static_cast<uint64_t>(b.acc[i].w) << 32) | b.acc[i].z) & (2 * j + 1 == cw ? ~cbit : ~0ull);
+                    const uint64_t be = __ballot(pe && w0 != 0), bo = __ballot(pe && w1 != 0);
+                    ev |= static_cast<uint32_t>(be) | static_cast<uint32_t>(be >> 32);
+                    od |= static_cast<uint32_t>(bo) | static_cast<uint32_t>(bo >> 32);
+                }
+                if (lane < 4) L.ys[4 * wave + lane] = b.y;
+                if (lane == 0) {
+                    L.wm[wave][0] = ev;
+                    L.wm[wave][1] = od;
+                }
+                __syncthreads();
+                if (wave == 0) {
+                    uint32_t v = lane < 2 * kWdWaves ? (&L.wm[0][0])[lane] : 0u;
+                    for (int o = 2; o < 32; o <<= 1) v |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), o));
+                    uint32_t ue = __builtin_amdgcn_readlane(v, 0), uo = __builtin_amdgcn_readlane(v, 1);
+                    auto top_word = [&]() {  // the highest nonzero word, taken out; -1: none
+                        const int te = ue ? 2 * (31 - __builtin_clz(ue)) : -1, to = uo ? 2 * (31 - __builtin_clz(uo)) + 1 : -1;
+                        if (te > to) ue &= ~(1u << (te >> 1));
+                        else if (to >= 0) uo &= ~(1u << (to >> 1));
+                        return te > to ? te : to;
+                    };
+                    const uint64_t* Rw = reinterpret_cast<const uint64_t*>(Rm) + lane * (2 * kRowPitch);
+                    const int wa = top_word(), wb = top_word();
+                    uint64_t va, vb = 0;
+                    if (wa >= 0) {
+                        va = Rw[wa] & (wa == cw ? ~cbit : ~0ull);
+                        if (wb >= 0) vb = Rw[wb];
+                    } else {
+                        va = (Rw[cw] & cbit) ? 1ull : 0ull;  // only the constant is left
+                    }
+                    uint64_t T = 1ull << lane, now = 0;
+                    for (;;) {
+                        const uint64_t nz = __ballot((va | vb) != 0) & pend;
+                        if (!nz) break;
+                        const int q = ffs64(nz);  // the earliest row with a bit in the panel
+                        const uint64_t fa = readlane64(va, q), fb = readlane64(vb, q), ft = readlane64(T, q);
+                        const bool in_a = fa != 0;
+                        const int bit = msb64(in_a ? fa : fb);
+                        const uint32_t mk = bit_mask(in_a ? va : vb, bit) & (lane == q ? 0u : ~0u);
+                        va = xor_and(va, mk, fa);
+                        vb = xor_and(vb, mk, fb);
+                        T = xor_and(T, mk, ft);
+                        if (lane == q) mypiv = wa < 0 ? n : 64 * (in_a ? wa : wb) + bit;
+                        now |= 1ull << q;
+                        pend &= ~(1ull << q);
+                    }
+                    L.T[lane] = T;
+                    if (lane == 0) {
+                        L.panel = now;
+                        L.more = now != 0;  // (zero: no pending row holds a bit any more)
+                    }
+                }
+                __syncthreads();
+                if (!__builtin_amdgcn_readfirstlane(L.more)) break;
+                const uint64_t now = L.panel;
+                const uint64_t nowu = readlane64(now, 0);
+                uint64_t tl[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) tl[i] = L.T[4 * wave + 2 * i + h];
+                const uint64_t ty = L.T[4 * wave + (lane & 3)];
+                if (__popcll(nowu) <= 12) {  // few new rows: each added where T says so
+                    uint64_t left = nowu;
+                    u32x4 na[2], ny = b.y & bit_mask(ty, 4 * wave + (lane & 3));
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) na[i] = b.acc[i] & bit_mask(tl[i], 4 * wave + 2 * i + h);
+                    while (left) {
+                        const int q = ffs64(left);
+                        left &= left - 1;
+                        const u32x4 f = Rm[q * kRowPitch + j], z = L.ys[q];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)  // (the row itself is in already)
+                            na[i] = xor_and4(na[i], (4 * wave + 2 * i + h == q) ? 0u : bit_mask(tl[i], q), f);
+                        ny = xor_and4(ny, (4 * wave + (lane & 3) == q) ? 0u : bit_mask(ty, q), z);
+                    }
+                    b.acc[0] = na[0];
+                    b.acc[1] = na[1];
+                    b.y = ny;
+                } else {
+                    u32x4 na[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, ny = {0, 0, 0, 0};
+                    const int t = wave >> 1;
+                    const bool hb = wave & 1;
+#pragma unroll 1
+                    for (int hf = 0; hf < 2; ++hf) {
+                        const u32x4* f = Rm + (32 * hf + 4 * t) * kRowPitch + j;
+                        const u32x4 f0 = f[0], f1 = f[kRowPitch];
+                        const uint32_t mh = h ? ~0u : 0u;
+                        u32x4 base = f[2 * kRowPitch] & mh;
+                        if (hb) base ^= f[3 * kRowPitch];
+                        u32x4* e = ET + (16 * t + (hb ? 8 : 0) + 4 * h) * 32 + j;
+                        e[0] = base;
+                        e[32] = base ^ f0;
+                        e[64] = base ^ f1;
+                        e[96] = xor3_4(base, f0, f1);
+                        __syncthreads();
+                        uint32_t th[2];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) th[i] = static_cast<uint32_t>(hf ? tl[i] >> 32 : tl[i]);
+#pragma unroll
+                        for (int q = 0; q < 8; q += 2)
+#pragma unroll
+                            for (int i = 0; i < 2; ++i)
+                                na[i] = xor3_4(na[i], ET[(16 * q + __builtin_amdgcn_ubfe(th[i], 4 * q, 4)) * 32 + j],
+                                               ET[(16 * q + 16 + __builtin_amdgcn_ubfe(th[i], 4 * q + 4, 4)) * 32 + j]);
+                        const int ly = (lane >> 2) & 7;
+                        const uint32_t nib = lane < 32 ? static_cast<uint32_t>(hf ? ty >> 32 : ty) >> (4 * ly) : 0u;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            ny = xor_and4(ny, static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(nib), i, 1)),
+                                          L.ys[32 * hf + 4 * ly + i]);
+                        __syncthreads();
+                    }
+                    b.acc[0] = na[0];
+                    b.acc[1] = na[1];
+#pragma unroll
+                    for (int o = 4; o < 64; o <<= 1) ny ^= shfl_xor4(ny, o);
+                    b.y = ny;
+                }
+                ins |= nowu;
+                __syncthreads();  // the rows are rewritten for the next panel
+            }
+            // (4) publish: pivots and rows behind the list
+            int K = __popcll(ins);
+            if (K > d - nrows) K = d - nrows;  // (only after a wait that gave up)
+            if (wave == 0) {
+                const int i = __popcll(ins & ((1ull << lane) - 1));
+                if (((ins >> lane) & 1ull) && i < K) {
+                    const int v = mypiv | (i == K - 1 ? kPivLast : 0);
+                    L.piv[nrows + i] = static_cast<uint16_t>(v);
+                    if (G > 1)
+                        __hip_atomic_store(ent + nrows + i, v | (static_cast<int>(blk + 1) << 13), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (G > 1 && lane == 0 && nrows + K < d)
+                    __hip_atomic_store(ent + nrows + K, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int r = 4 * wave + 2 * i + h;
+                const int k = __popcll(ins & ((1ull << r) - 1));
+                if (((ins >> r) & 1ull) && k < K) {
+                    const int off = (nrows + k) * W * 8 + 16 * j;
+                    if (2 * j + 1 < fw) __builtin_amdgcn_raw_buffer_store_b128(b.acc[i], X, off, 0, kDevScope);
+                    else if (2 * j < fw) __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{b.acc[i].x, b.acc[i].y}, X, off, 0, kDevScope);
+                }
+            }
+            {
+                const int r = 4 * wave + lane;
+                const int k = lane < 4 ? __popcll(ins & ((1ull << r) - 1)) : K;
+                if (lane < 4 && ((ins >> r) & 1ull) && k < K)
+                    __builtin_amdgcn_raw_buffer_store_b128(b.y, X, ((nrows + k) * W + fw) * 8, 0, kDevScope);
+            }
+            __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's stores performed
+            nrows += K;
+        }
+        {  // the other rows: redundant, or contradictory when an output bit is left
+            const int r = 4 * wave + lane;
+            const uint64_t cm = __ballot(lane < 4 && r < nb && !((ins >> r) & 1ull) && any4(b.y));
+            if (cm) {
+                ncon += lane == 0 ? __popcll(cm) : 0;
+                const long long f = blk * kWdRows + 4 * wave + ffs64(cm);
+                if (lane == 0 && f < firstc) firstc = f;
+            }
+        }
+        if (tid == 0) L.nrows = nrows;
+        __syncthreads();
+        blk += G;
+        if (G > 1 && tid == 0) put_progress(prog, g, seq, static_cast<int>((blk - g) / G));
+    }
+    // outputs
+    const int64_t po = ds.po, mo = ds.mo;
+    const int rank = nrows;
+    if (full) {
+        for (int u = g; u < 4; u += G) solve_map(a, ds, L, Xp, u);
+        uint64_t* B = a.basis + ds.bo;
+        for (int k = kWdWaves * g + wave; k < d; k += kWdWaves * G) {
+            const int p = k < n ? n - 1 - k : n;
+            if (lane < fw) B[static_cast<int64_t>(k) * W + lane] = lane == (p >> 6) ? 1ull << (p & 63) : 0ull;
+        }
+    } else {
+        for (int p = kWdThreads * g + tid; p < d; p += kWdThreads * G)
+            if (!((L.pm[p >> 6] >> (p & 63)) & 1ull)) {
+                a.maps[mo + 2 * p] = 0;
+                a.maps[mo + 2 * p + 1] = 0;
+            }
+    }
+    // every member's part of the map and the basis written; the list is dead
+    __threadfence();
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (G > 1) {
+        if (tid == 0) put_progress(prog, g, seq, kWdBar + 2);
+        wait_for(0, 2);
+    }
+    __threadfence();
+    if (full) {
+        if (blk < blocks) check_rows(a, ds, L, static_cast<int>(blk), G, static_cast<int>(blocks), ncon, firstc);
+    } else if (has_parity_rows(d, rank)) {
+        // parity-check rows of the free columns: per word pair (w, v), a bit-matrix transpose of
+        // word w of the basis rows of pivots 64 v .. 64 v + 63 (zero for free columns) gives lane f
+        // word v of the row of free column 64 w + f
+        const uint64_t lane_lt = (1ull << lane) - 1;
+        const uint64_t* B = a.basis + ds.bo;
+        int base = 0;  // free columns in the words before w
+        for (int w = 0; w < fw; ++w) {
+            const uint64_t fr = ~L.pm[w] & (w == fw - 1 ? tmask : ~0ull);
+            if (!fr) continue;
+            const bool mine = (fr >> lane) & 1ull;
+            const int64_t i = base + __popcll(fr & lane_lt);
+            for (int v = kWdWaves * g + wave; v < fw; v += kWdWaves * G) {
+                const uint64_t pv = L.pm[v];
+                const bool piv = (pv >> lane) & 1ull;
+                int k = rank - 1;
+                if (64 * v + lane != n) {
+                    uint64_t hi = pv & (v == cw ? ~cbit : ~0ull);
+                    hi &= lane == 63 ? 0ull : (~0ull << (lane + 1));
+                    k = L.above[v] + __popcll(hi);
+                }
+                const uint64_t col = transpose64(piv ? B[static_cast<int64_t>(k) * W + w] : 0ull, lane);
+                if (mine) Xp[i * fw + v] = col | (v == w ? (1ull << lane) : 0ull);
+            }
+            base += __popcll(fr);
         }
     }
-    for (int t = tid; t < d; t += kLargeThreads) {  // full rank: every slot present, position = slot
-        const int pt = slot_pivot(t, n);
-        if (!((L.pm[pt >> 6] >> (pt & 63)) & 1ull)) continue;
-        int k = rank - 1;
-        if (pt != n) {
-            uint64_t v = L.pm[pt >> 6];
-            if ((pt >> 6) == cw) v &= ~cbit;
-            v &= (pt & 63) == 63 ? 0ull : (~0ull << ((pt & 63) + 1));
-            k = L.above[pt >> 6] + __popcll(v);
+    if (g == 0) {
+        for (int i = tid; i < rank; i += kWdThreads) {
+            const int p = L.piv[i] & (kPivLast - 1);
+            int k = rank - 1;
+            if (p != n) {
+                uint64_t v = L.pm[p >> 6];
+                if ((p >> 6) == cw) v &= ~cbit;
+                v &= (p & 63) == 63 ? 0ull : (~0ull << ((p & 63) + 1));
+                k = L.above[p >> 6] + __popcll(v);
+            }
+            if (k < d) a.pivots[po + k] = p;
         }
-        a.pivots[po + k] = pt;
+        if (tid == 0) a.rank[c] = rank;
     }
-    if (tid == 0) {
-        a.rank[c] = rank;
-        a.n_contra[c] = L.contra;
-        a.first_contra[c] = L.firstMin == kNone ? -1 : L.firstMin;
-        // OR: the other members may report a timeout (the plan cleared the word)
-        atomicOr(&a.ctx_flags[c], (L.contra ? F2_CTX_CONTRADICTION : 0u) | (L.timeout ? F2_CTX_SYNC_TIMEOUT : 0u));
+    // contradictions: counted by every member (the plan cleared the words)
+    if (ncon) {
+        atomicAdd(&a.n_contra[c], ncon);
+        atomicMin(reinterpret_cast<unsigned long long*>(&a.first_contra[c]), static_cast<unsigned long long>(firstc));
+        atomicOr(&a.ctx_flags[c], F2_CTX_CONTRADICTION);
     }
+    if (tid == 0 && L.timeout) atomicOr(&a.ctx_flags[c], F2_CTX_SYNC_TIMEOUT);
     __syncthreads();
 }
 
@@ -1928,7 +2124,7 @@ union SmallShared {
     PivShared piv;
 };
 
-__global__ __launch_bounds__(kLargeThreads) void k_fit_small(FitArgs a) {
+__global__ __launch_bounds__(kSmallThreads) void k_fit_small(FitArgs a) {
     __shared__ SmallShared U;
     const CtxDesc ds = readlane_desc(load_desc(a, blockIdx.x), 0);
     if (ds.c < 0) return;
@@ -1949,35 +2145,34 @@ __global__ __launch_bounds__(kLargeThreads) void k_fit_small(FitArgs a) {
             break;
         default:
             switch (fw) {
-                case 1: fit_ctx_piv<1, kLargeWaves>(a, ds, U.piv); break;
-                case 2: fit_ctx_piv<2, kLargeWaves>(a, ds, U.piv); break;
-                case 3: case 4: fit_ctx_piv<4, kLargeWaves>(a, ds, U.piv); break;
-                default: fit_ctx_piv<8, kLargeWaves>(a, ds, U.piv); break;
+                case 1: fit_ctx_piv<1, kSmallWaves>(a, ds, U.piv); break;
+                case 2: fit_ctx_piv<2, kSmallWaves>(a, ds, U.piv); break;
+                case 3: case 4: fit_ctx_piv<4, kSmallWaves>(a, ds, U.piv); break;
+                default: fit_ctx_piv<8, kSmallWaves>(a, ds, U.piv); break;
             }
             break;
     }
 }
 
-// Wide contexts (class 3): with few of them (as many as a quarter of the
-// workgroups or fewer) each is fitted by a group of 4 workgroups, by 2 with up to
-// half, else by one.  Under a cooperative launch every workgroup is resident,
-// which the group barriers need; otherwise groups are single workgroups.  A
-// group's workgroups are blockIdx values congruent mod 8, which the dispatcher
-// places on one die (shared L2 for the exchange).
-__global__ __launch_bounds__(kLargeThreads) void k_fit_wide(FitArgs a) {
-    __shared__ LargeShared U;
+// Wide contexts (class 3): the fewer there are, the more workgroups fit one together
+// (8, 4 or 2, while every context then has its own).  Under a cooperative launch every
+// workgroup is resident, which the waits for one another need; otherwise every context
+// takes one.  A group's workgroups are blockIdx values congruent mod 8, which the
+// dispatcher places on one die (a shared L2 for the list they all read).
+__global__ __launch_bounds__(kWdThreads) void k_fit_wide(FitArgs a) {
+    __shared__ WideShared U;
     const int nl = a.plan[kClsLarge + 1] - a.plan[kClsLarge];
     const int nwg = static_cast<int>(gridDim.x);
     int G = 1;
-    if (a.coop && nwg % 32 == 0 && nwg / 4 <= kMaxGroups && 4 * nl <= nwg) G = 4;
-    else if (a.coop && nwg % 16 == 0 && nwg / 2 <= kMaxGroups && 2 * nl <= nwg) G = 2;
+    if (a.coop && nwg <= kMaxMembers)
+        for (int k = 2; k <= 8 && k * nl <= nwg && nwg % (8 * k) == 0; k *= 2) G = k;
     const int x = static_cast<int>(blockIdx.x), idx = x / 8;
     const int g = idx % G, grp = (x % 8) + 8 * (idx / G), ngrp = nwg / G;
-    int epoch = 0;
+    uint64_t* prog = reinterpret_cast<uint64_t*>(a.plan + kBarHead) + (G > 1 ? grp * G : 0);
     for (int i = 0;; ++i) {
         const int c = __builtin_amdgcn_readfirstlane(class_ctx(a, kClsLarge, i, -1, ngrp, grp));
         if (c < 0) break;
-        fit_ctx_large(a, readlane_desc(load_desc(a, c), 0), U, G, g, a.plan + kBarHead + grp, epoch);
+        fit_ctx_wide(a, readlane_desc(load_desc(a, c), 0), U, G, g, prog, i + 1);
     }
 }
 
@@ -3732,7 +3927,7 @@ int wide_resident_workgroups() {
     int r = 0;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k_fit_wide), kLargeThreads,
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k_fit_wide), kWdThreads,
                                                      0) == hipSuccess)
         r = cus * per_cu;
     (void)hipGetLastError();
@@ -3748,7 +3943,7 @@ void launch_fit(FitArgs a, hipStream_t s) {
     const int32_t C = a.num_ctx;
     if (C <= kSmallBatch && a.max_n >= 0 && a.max_n < 512) {
         a.coop = 0;
-        hipLaunchKernelGGL(k_fit_small, dim3(static_cast<unsigned>(C)), dim3(kLargeThreads), 0, s, a);
+        hipLaunchKernelGGL(k_fit_small, dim3(static_cast<unsigned>(C)), dim3(kSmallThreads), 0, s, a);
         return;
     }
     const int plan_blocks = static_cast<int>((static_cast<int64_t>(C) + kPlanThreads - 1) / kPlanThreads);
@@ -3763,13 +3958,13 @@ void launch_fit(FitArgs a, hipStream_t s) {
     if (res >= 32) {
         a.coop = 1;
         void* args[] = {&a};
-        if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_fit_wide), dim3(res < 1024 ? res : 1024),
-                                       dim3(kLargeThreads), args, 0, s) == hipSuccess)
+        if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_fit_wide), dim3(res < kMaxMembers ? res : kMaxMembers),
+                                       dim3(kWdThreads), args, 0, s) == hipSuccess)
             return;
         (void)hipGetLastError();
     }
     a.coop = 0;
-    hipLaunchKernelGGL(k_fit_wide, dim3(fit_grid(C, 256)), dim3(kLargeThreads), 0, s, a);
+    hipLaunchKernelGGL(k_fit_wide, dim3(fit_grid(C, 256)), dim3(kWdThreads), 0, s, a);
 }
 
 }  // namespace
