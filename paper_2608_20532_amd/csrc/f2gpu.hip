@@ -32,6 +32,7 @@
 #include <stdlib.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "../../include/f2gpu.h"
 
@@ -1140,7 +1141,7 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
 }
 
 // ---------------------------------------------------------------------------
-// large-context fit (fw > 8): G workgroups of 16 wavefronts per context (G a power of
+// large-context fit (fw > 8): G workgroups of 8 wavefronts per context (G a power of
 // two, all resident: a cooperative launch), one compute unit each.  The rows go in
 // blocks of 64; member g takes blocks g, g + G, ...
 //
@@ -1167,7 +1168,7 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
 //       words per lane, so that one 16-byte LDS read serves two rows;
 //   (2) a block whose residuals are all zero is done whatever the blocks before it
 //       still add.  Otherwise the member waits for them, reduces by what they added, and
-//   (3) eliminates in stream order on panels: one wavefront, a row per lane, works on
+//   (3) eliminates in stream order on panels: one wavefront, a column per lane, works on
 //       the two highest feature words that hold a bit (128 columns) and notes which rows
 //       were added to which (a 64 x 64 matrix T); then all wavefronts apply T to the
 //       whole rows.  Rows that the panel reduces to zero go on to the next panel;
@@ -1177,11 +1178,14 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
 // priority up, then every remaining row is checked against the map.  Below d each
 // batch is reduced by the later ones as in (1).
 //
-// 64 contexts, n = 4095, 8,192 rows: 10.27 ms with a basis kept fully
-// reduced (groups of 4 workgroups exchanging partial sums), 4.26 ms.  Bound by LDS
-// bandwidth: a table lookup moves 512 bytes for four basis rows.
+// 64 contexts, n = 4095, 8,192 rows: 10.27 ms with a basis kept fully reduced (groups
+// of 4 workgroups exchanging partial sums), 4.25 ms with 16 wavefronts of 4 rows and
+// loads one round ahead, 3.36 ms.  A round of 32 basis rows takes about 4,200 cycles:
+// 2,700 of LDS bandwidth (a table lookup moves 512 bytes for four basis rows) and 2,000
+// of VALU issue that two wavefronts per SIMD do not overlap further.
 // ---------------------------------------------------------------------------
-constexpr int kWdWaves = 16;
+constexpr int kWdWaves = 8;  // 256 registers each: loads two rounds ahead
+constexpr int kWdPairs = 64 / kWdWaves / 2;  // pairs of block rows per wavefront
 constexpr int kWdThreads = 64 * kWdWaves;
 constexpr int kWdRows = 64;                   // rows per block
 constexpr int kWdMaxBlocks = (1 << 19) - 2;   // block numbers in a pivot's tag; contexts of more rows take one member
@@ -1195,7 +1199,7 @@ typedef unsigned int u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));  
 
 struct WideShared {
     u32x4 tab[2][128][32];             // [buffer][16 table + entry][word pair]; other phases lay out their own data here
-    uint32_t sel[kWdWaves][2][128];    // selection: two rows of a wavefront, as words
+    uint32_t sel[kWdWaves][4][128];    // selection: four rows of a wavefront, as words
     uint16_t piv[4096];                // the list's pivots, insertion order, kPivLast on the last of each batch
     u32x4 ys[64];                      // output words: two rounds of 32 rows, or the block's 64 rows
     uint64_t T[kWdRows];               // elimination: block rows added into each row
@@ -1204,7 +1208,7 @@ struct WideShared {
     uint32_t wm[kWdWaves][2];          // nonzero even and odd words of each wavefront's rows
     uint64_t ins;                      // block rows that became basis rows
     uint64_t panel;                    // the ones of the current panel
-    int more;                          // another panel follows
+    int more;                          // a pending row holds a bit: another panel follows
     int any[2];                        // nonzero residuals in the block (alternating)
     int nrows, next;                   // list length; every block below `next` is done
     int timeout;                       // a wait of this context gave up
@@ -1242,6 +1246,16 @@ template <bool DEV>
 __device__ __forceinline__ u32x4 load16(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, DEV ? kDevScope : 0);
 }
+
+__device__ __forceinline__ void put_dev(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void put_dev32(uint32_t* p, uint32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// v with the rows of `rows` flipped where row q's bit is set (a column per lane)
+__device__ __forceinline__ uint64_t xor_sel(uint64_t v, int q, uint64_t rows) { return xor_and(v, bit_mask(v, q), rows); }
 
 // progress of a group's members: (context sequence number, blocks done, or kWdBar + k
 // past barrier k), one 64-bit word per member, stored only by it
@@ -1291,240 +1305,295 @@ __device__ __forceinline__ int take_entries(WideShared& L, const int32_t* ent, i
     }
 }
 
-// the basis rows of one round: rows 4 t .. 4 t + 3 of it (t = wavefront / 2)
+// the basis rows of one round: wavefront t takes rows 4 t .. 4 t + 3 of it
 struct RoundRows {
-    u32x4 f[4];  // two words per lane, the same in both half wavefronts
+    u32x4 f[2];  // two words per lane of row 2 i + h in half wavefront h
     u32x4 y;     // output words of row lane & 3
 };
 template <bool DEV>
-__device__ __forceinline__ void load_rows(__amdgpu_buffer_rsrc_t X, int W, int fw, int start, int cnt, int t, bool hb,
-                                          int voff, int lane, RoundRows& r) {
+__device__ __forceinline__ void load_rows(__amdgpu_buffer_rsrc_t X, int W, int fw, int start, int cnt, int t, int voff,
+                                          int lane, RoundRows& r) {
+    const int soff = start * W * 8;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (i == 3 && !hb) break;  // its combinations are the other wavefront's
-        const int row = start + (4 * t + i < cnt ? 4 * t + i : cnt - 1);
-        r.f[i] = load16<DEV>(X, voff, row * W * 8);
+    for (int i = 0; i < 2; ++i) {
+        const int k = 4 * t + 2 * i + (lane >> 5);
+        r.f[i] = load16<DEV>(X, (k < cnt ? k : cnt - 1) * W * 8 + voff, soff);
     }
     const int k = 4 * t + (lane & 3);
-    r.y = load16<DEV>(X, ((start + (k < cnt ? k : cnt - 1)) * W + fw) * 8, 0);
+    r.y = load16<DEV>(X, ((k < cnt ? k : cnt - 1) * W + fw) * 8, soff);
 }
 
-// block rows: wavefront w holds rows 4 w .. 4 w + 3, row 4 w + 2 i + h in half h of acc[i];
-// the output words of row 4 w + (lane & 3) are the XOR of y over the lanes of equal lane & 3
+// lower and upper half of v, each in both half wavefronts
+__device__ __forceinline__ void spread_halves(u32x4 v, u32x4& lo, u32x4& hi) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v[k], v[k], false, false);
+        lo[k] = r[0];
+        hi[k] = r[1];
+    }
+}
+
+// block rows: wavefront w holds rows 8 w .. 8 w + 7, row 8 w + 2 i + h in half h of acc[i];
+// the output words of row 8 w + (lane & 7) are the XOR of y over the lanes of equal lane & 7
 struct BlockRows {
-    u32x4 acc[2];
+    u32x4 acc[kWdPairs];
     u32x4 y;
 };
 
-// reduce the block by list rows pos .. nrows - 1 (pos starts a batch)
+// rows [start, start + cnt) of the list: half `half` of the batch of K rows at pos; cnt 0: none
+struct Round {
+    int pos, K, half, cnt;
+};
+
+// reduce the block by list rows pos .. nrows - 1 (pos < nrows starts a batch)
 __device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_t X, int W, int fw, int pos, int nrows,
                                             BlockRows& b) {
     const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = wave >> 1;
-    const bool hb = wave & 1;
+    const int t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int voff = 16 * (2 * j < fw ? j : 0);
     char* const tab = reinterpret_cast<char*>(&L.tab[0][0][0]);
-    const int wbase = ((16 * t + (hb ? 8 : 0) + 4 * h) * 32 + j) * 16;
-    auto batch_len = [&](int p0) {
-        const bool in = p0 + lane < nrows;
-        const uint64_t last = __ballot(in && (L.piv[in ? p0 + lane : 0] & kPivLast));
-        const int left = nrows - p0 < 64 ? nrows - p0 : 64;
-        const int k = last ? ffs64(last) + 1 : 64;
-        return k < left ? k : left;
+    // the round after r, from the list entries behind r's batch (read ahead)
+    auto entry_after = [&](const Round& r) {
+        const int i = r.pos + r.K + lane;
+        return static_cast<int>(L.piv[i < nrows ? i : nrows - 1]);
     };
-    auto fetch = [&](int start, int cnt, bool fresh, RoundRows& r) {
-        if (4 * (t & ~1) >= cnt) return;
+    auto after = [&](const Round& r, int e) {
+        if (r.half == 0 && r.K > 32) return Round{r.pos, r.K, 1, r.K - 32};
+        const int p0 = r.pos + r.K;
+        if (p0 >= nrows) return Round{p0, 0, 0, 0};
+        const uint64_t last = __ballot(p0 + lane < nrows && (e & kPivLast));
+        const int left = nrows - p0 < 64 ? nrows - p0 : 64;
+        const int k = last ? ffs64(last) + 1 : 64, K = k < left ? k : left;
+        return Round{p0, K, 0, K < 32 ? K : 32};
+    };
+    // always the same number of loads (past the list, its last row): the wait for one
+    // round's rows then leaves the next round's in flight
+    auto fetch = [&](const Round& r, RoundRows& rr) {
+        const int start = r.cnt ? r.pos + 32 * r.half : nrows - 1, cnt = r.cnt ? r.cnt : 1;
         // the first rows of a batch may share a cache line with the batch before it, read
         // before they were written
-        if (fresh && t == 0) load_rows<true>(X, W, fw, start, cnt, t, hb, voff, lane, r);
-        else load_rows<false>(X, W, fw, start, cnt, t, hb, voff, lane, r);
+        if (r.half == 0 && t == 0) load_rows<true>(X, W, fw, start, cnt, t, voff, lane, rr);
+        else load_rows<false>(X, W, fw, start, cnt, t, voff, lane, rr);
     };
-    auto store_tables = [&](int buf, int cnt, const RoundRows& r) {
-        if (4 * (t & ~1) >= cnt) return;
-        const uint32_t mh = h ? ~0u : 0u;
-        u32x4 base = {r.f[2].x & mh, r.f[2].y & mh, r.f[2].z & mh, r.f[2].w & mh};
-        if (hb) base ^= r.f[3];
-        char* e = tab + 65536 * buf + wbase;
-        *reinterpret_cast<u32x4*>(e) = base;
-        *reinterpret_cast<u32x4*>(e + 512) = base ^ r.f[0];
-        *reinterpret_cast<u32x4*>(e + 1024) = base ^ r.f[1];
-        *reinterpret_cast<u32x4*>(e + 1536) = xor3_4(base, r.f[0], r.f[1]);
-        if (!hb && lane < 4) L.ys[32 * buf + 4 * t + lane] = r.y;
+    // absent rows are never selected, and entry 0 of an absent table must be zero
+    auto store_tables = [&](int buf, const RoundRows& r) {
+        u32x4 f0, f1, f2, f3;
+        spread_halves(r.f[0], f0, f1);
+        spread_halves(r.f[1], f2, f3);
+        const u32x4 b0 = f2 & (h ? ~0u : 0u), b1 = b0 ^ f3, f01 = f0 ^ f1;
+        char* e = tab + 65536 * buf + ((16 * t + 4 * h) * 32 + j) * 16;  // half h: entries 4 h .. and 8 + 4 h ..
+        *reinterpret_cast<u32x4*>(e) = b0;
+        *reinterpret_cast<u32x4*>(e + 512) = b0 ^ f0;
+        *reinterpret_cast<u32x4*>(e + 1024) = b0 ^ f1;
+        *reinterpret_cast<u32x4*>(e + 1536) = b0 ^ f01;
+        *reinterpret_cast<u32x4*>(e + 4096) = b1;
+        *reinterpret_cast<u32x4*>(e + 4608) = b1 ^ f0;
+        *reinterpret_cast<u32x4*>(e + 5120) = b1 ^ f1;
+        *reinterpret_cast<u32x4*>(e + 5632) = b1 ^ f01;
+        if (lane < 4) L.ys[32 * buf + 4 * t + lane] = r.y;
     };
-    int K = batch_len(pos), half = 0, cnt = K < 32 ? K : 32, buf = 0;
-    RoundRows rr;
-    fetch(pos, cnt, true, rr);
-    store_tables(0, cnt, rr);
-    __syncthreads();
-    uint64_t s[4];
-    for (;;) {
-        // the next round: the batch's second half, or the next batch
-        int npos = pos, nK = K, nhalf = 1, ncnt = 0;
-        if (half == 0 && K > 32) {
-            ncnt = K - 32;
-        } else {
-            npos = pos + K;
-            nhalf = 0;
-            if (npos < nrows) {
-                nK = batch_len(npos);
-                ncnt = nK < 32 ? nK : 32;
-            }
-        }
-        if (ncnt) fetch(npos + 32 * nhalf, ncnt, nhalf == 0, rr);
-        if (half == 0) {  // the rows' bits at the batch's pivots: bit i of s[k] selects batch row i for row 4 w + k
-            const int p = lane < K ? (L.piv[pos + lane] & (kPivLast - 1)) : 0;
+    uint32_t sl[kWdPairs], sh[kWdPairs], yl, yh;  // selections of this lane's rows: batch rows 0-31, 32-63
+    auto select = [&](const Round& r) {  // the rows' bits at the batch's pivots
+        const int p = lane < r.K ? (L.piv[r.pos + lane] & (kPivLast - 1)) : 0;
+        yl = yh = 0;
+        static_assert(kWdPairs % 2 == 0, "two pairs of rows at a time");
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                *reinterpret_cast<u32x4*>(&L.sel[wave][h][4 * j]) = b.acc[i];
-                wave_sync();
-                const uint32_t d0 = L.sel[wave][0][p >> 5], d1 = L.sel[wave][1][p >> 5];
-                s[2 * i] = __ballot(lane < K && ((d0 >> (p & 31)) & 1u));
-                s[2 * i + 1] = __ballot(lane < K && ((d1 >> (p & 31)) & 1u));
-                wave_sync();
-            }
-        }
-        uint32_t sv[2], sy;
+        for (int i0 = 0; i0 < kWdPairs; i0 += 2) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t s0 = static_cast<uint32_t>(half ? s[2 * i] >> 32 : s[2 * i]);
-            const uint32_t s1 = static_cast<uint32_t>(half ? s[2 * i + 1] >> 32 : s[2 * i + 1]);
-            sv[i] = h ? s1 : s0;
-            if (i == 0) sy = (lane & 1) ? s1 : s0;
-            else sy = (lane & 2) ? ((lane & 1) ? s1 : s0) : sy;
+            for (int i = 0; i < 2; ++i) *reinterpret_cast<u32x4*>(&L.sel[t][2 * i + h][4 * j]) = b.acc[i0 + i];
+            wave_sync();
+            uint32_t dw[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dw[i] = L.sel[t][i][p >> 5];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint64_t sr = __ballot(lane < r.K && ((dw[i] >> (p & 31)) & 1u));  // row 2 i0 + i of the wavefront
+                const int k = i0 + i / 2;
+                if (i % 2 == 0) {
+                    sl[k] = static_cast<uint32_t>(sr);
+                    sh[k] = static_cast<uint32_t>(sr >> 32);
+                } else {
+                    sl[k] = h ? static_cast<uint32_t>(sr) : sl[k];
+                    sh[k] = h ? static_cast<uint32_t>(sr >> 32) : sh[k];
+                }
+                yl = (lane & 7) == 2 * i0 + i ? static_cast<uint32_t>(sr) : yl;
+                yh = (lane & 7) == 2 * i0 + i ? static_cast<uint32_t>(sr >> 32) : yh;
+            }
+            wave_sync();
         }
+    };
+    auto apply = [&](const Round& r, int buf) {
+        uint32_t sv[kWdPairs];
+#pragma unroll
+        for (int i = 0; i < kWdPairs; ++i) sv[i] = r.half ? sh[i] : sl[i];
         const char* lb = tab + 65536 * buf + 16 * j;
+        auto two_tables = [&](int g) {
+            u32x4 t0[kWdPairs], t1[kWdPairs];
 #pragma unroll
-        for (int g = 0; g < 8; g += 2) {
-            if (4 * g >= cnt) break;
-            u32x4 t0[2], t1[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < kWdPairs; ++i) {
                 t0[i] = *reinterpret_cast<const u32x4*>(lb + (__builtin_amdgcn_ubfe(sv[i], 4 * g, 4) << 9) + g * 8192);
                 t1[i] = *reinterpret_cast<const u32x4*>(lb + (__builtin_amdgcn_ubfe(sv[i], 4 * g + 4, 4) << 9) + (g + 1) * 8192);
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i) b.acc[i] = xor3_4(b.acc[i], t0[i], t1[i]);
-        }
-        {  // output words: lane (table, row) adds the table's selected rows
-            const int ty = (lane >> 2) & 7;
-            const uint32_t nib = lane < 32 ? sy >> (4 * ty) : 0u;
+            for (int i = 0; i < kWdPairs; ++i) b.acc[i] = xor3_4(b.acc[i], t0[i], t1[i]);
+        };
+        // output words: lane (table, row) adds the table's selected rows
+        const int ty = lane >> 3;
+        const uint32_t nib = (r.half ? yh : yl) >> (4 * ty);
+        u32x4 yr[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                b.y = xor_and4(b.y, static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(nib), i, 1)),
-                               L.ys[32 * buf + 4 * ty + i]);
+        for (int i = 0; i < 4; ++i) yr[i] = L.ys[32 * buf + 4 * ty + i];
+        if (r.cnt > 24) {  // every table: no branches between the reads, so that they overlap
+            two_tables(0);
+            two_tables(2);
+            two_tables(4);
+            two_tables(6);
+        } else {
+            two_tables(0);
+            if (r.cnt > 8) two_tables(2);
+            if (r.cnt > 16) two_tables(4);
         }
-        if (ncnt) store_tables(buf ^ 1, ncnt, rr);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            b.y = xor_and4(b.y, static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(nib), i, 1)), yr[i]);
+    };
+    // rounds: tables of `cur` in LDS, rows of `nxt` in registers (or on their way), rows of
+    // `nn` fetched in this step.  Each SIMD holds one wavefront that builds the next tables
+    // before it applies the current ones and one that builds them after, so that the
+    // table reads of the one (LDS bandwidth) overlap the other's latencies.
+    Round cur = after(Round{pos, 0, 0, 0}, entry_after(Round{pos, 0, 0, 0}));
+    Round nxt = after(cur, entry_after(cur));
+    Round nn = after(nxt, entry_after(nxt));
+    RoundRows ra, rb;
+    fetch(cur, rb);
+    fetch(nxt, ra);
+    store_tables(0, rb);
+    __syncthreads();
+    const bool early = t >= kWdWaves / 2;
+    auto step = [&](int buf, const RoundRows& have, RoundRows& get) {
+        if (early) {
+            store_tables(buf ^ 1, have);
+            fetch(nn, get);
+        }
+        const int e = entry_after(nn);
+        if (cur.half == 0) select(cur);
+        apply(cur, buf);
+        if (!early) {
+            fetch(nn, get);
+            store_tables(buf ^ 1, have);
+        }
+        cur = nxt;
+        nxt = nn;
+        nn = after(nn, e);
         __syncthreads();
-        if (!ncnt) break;
-        pos = npos;
-        K = nK;
-        half = nhalf;
-        cnt = ncnt;
-        buf ^= 1;
+    };
+    for (;;) {
+        step(0, ra, rb);
+        if (!cur.cnt) break;
+        step(1, rb, ra);
+        if (!cur.cnt) break;
     }
 #pragma unroll
-    for (int o = 4; o < 64; o <<= 1) b.y ^= shfl_xor4(b.y, o);  // every lane: the whole of its row
+    for (int o = 8; o < 64; o <<= 1) b.y ^= shfl_xor4(b.y, o);  // every lane: the whole of its row
 }
 
-// full rank: the map by a triangular solve.  Row p (of pivot p) has its highest bit at p,
-// so from the lowest-priority word up: the 64 rows of a word are solved in order by one
-// wavefront, then every row above adds the solved rows that its bits in that word
-// select, through 16 tables of 16 entries.  Thread (tid, r) holds row p = tid + 1024 r.
-// One 32-bit column u of the four of the output word (they are independent: the members
-// share them out).  Latency-bound: two barriers per word.
+// full rank: the map by a triangular solve.  Row p (of pivot p) has its highest bit at p, so
+// words are solved from the lowest priority up: the 64 rows of a word add what their
+// bits in the words below select of the solved rows, through 16 tables of 16 entries per
+// word (kept in LDS), then among themselves, in order, in one wavefront.  One 32-bit
+// column u of the four of the output word (they are independent: the members share them
+// out).  Eight lanes share a row, so its words are read in order; the next word's rows
+// load meanwhile.  Bound by the latency of a word's steps.
 __device__ __forceinline__ void solve_map(const FitArgs& a, const CtxDesc& ds, WideShared& L, const uint64_t* X, int u) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = ds.n, d = n + 1, fw = feat_words(n), W = fw + F2_Y_WORDS, cw = n >> 6;
-    const uint64_t cbit = 1ull << (n & 63);
-    uint16_t* inv = reinterpret_cast<uint16_t*>(&L.tab[0][0][0]);              // [4096] list index of pivot p
-    uint32_t* zs = reinterpret_cast<uint32_t*>(&L.tab[0][16][0]);              // [2][64]
-    uint32_t* zt = reinterpret_cast<uint32_t*>(&L.tab[0][20][0]);              // [2][256]
+    uint32_t* zt = reinterpret_cast<uint32_t*>(&L.tab[0][0][0]);                // [64][kPitch] tables
+    constexpr int kPitch = 272;  // a word's tables start 16 banks after the last word's
+    uint32_t* zf = zt + 64 * kPitch;                                            // [4096] solved
+    uint64_t* ur = reinterpret_cast<uint64_t*>(zf + 4096);                      // [64] the word's own bits
+    uint32_t* zr = reinterpret_cast<uint32_t*>(ur + 64);                        // [64] before the word's own steps
+    uint16_t* inv = reinterpret_cast<uint16_t*>(zr + 64);                       // [4096] list index of pivot p
+    static_assert(64 * kPitch * 4 + 4096 * 4 + 64 * 12 + 4096 * 2 <= static_cast<int>(sizeof(L.tab)), "fits the tables' place");
     __syncthreads();
     for (int i = tid; i < d; i += kWdThreads) inv[L.piv[i] & (kPivLast - 1)] = static_cast<uint16_t>(i);
     __syncthreads();
-    const uint64_t* row[4];
-    uint32_t z[4];
-    bool has[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int p = tid + kWdThreads * r;
-        has[r] = p < n;
+    const int q = lane & 7, k = 8 * wave + (lane >> 3);  // words q, q + 8, .. of row k of the word
+    auto row_of = [&](int p) {
         const int idx = inv[p < d ? p : 0];
-        row[r] = X + static_cast<int64_t>(idx < d ? idx : 0) * W;
-        z[r] = reinterpret_cast<const uint32_t*>(row[r] + fw)[u];
-        if (p == n) zs[0] = z[r];  // the constant's row: its features are the constant alone
-    }
-    __syncthreads();
+        return X + static_cast<int64_t>(idx < d ? idx : 0) * W;
+    };
+    const uint32_t zc = reinterpret_cast<const uint32_t*>(row_of(n) + fw)[u];  // the constant's row: its features are the constant alone
+    if (tid == 0) zf[n] = zc;
+    uint64_t v[8];  // each word reloaded for the next row as soon as it is used
+    const uint64_t* row = row_of(k);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        z[r] ^= has[r] && (row[r][cw] & cbit) ? zs[0] : 0u;
-    }
-    __syncthreads();
-    for (int w0 = 0; w0 < fw; w0 += 4) {
-        uint64_t uw[4][4];  // words w0 .. w0 + 3 of the rows (past a row's end: not used)
+    for (int i = 0; i < 8; ++i) v[i] = row[0];
+    uint64_t cn = row[cw];
+    uint32_t yn = reinterpret_cast<const uint32_t*>(row + fw)[u];
+    for (int w = 0; w < fw; ++w) {
+        uint32_t z = q == 0 ? yn ^ (((cn >> (n & 63)) & 1ull) ? zc : 0u) : 0u;
+        uint64_t own = v[0];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int i = 1; i < 8; ++i) own = (w >> 3) == i ? v[i] : own;
+        const int wn = w + 1 < fw ? w + 1 : w;
+        row = row_of(64 * wn + k);
+        cn = row[cw];
+        yn = reinterpret_cast<const uint32_t*>(row + fw)[u];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int w = w0 + i;
-                uw[r][i] = (has[r] && w < fw && w <= ((tid + kWdThreads * r) >> 6)) ? row[r][w] & (w == cw ? cbit - 1 : ~0ull) : 0ull;
-            }
+        for (int i = 0; i < 8; ++i) {
+            const int ww = 8 * i + q;
+            if (8 * i > wn) break;
+            if (ww < w) {
+                const uint32_t* tw = zt + kPitch * ww;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int w = w0 + i;
-            if (w >= fw) break;
-            uint32_t* zw = zs + 64 * (i & 1);
-            uint32_t* tw = zt + 256 * (i & 1);
-            if (wave == (w & 15)) {  // the word's own rows, lowest first
-                const int rr = w >> 4;
-                uint64_t v = rr == 0 ? uw[0][i] : rr == 1 ? uw[1][i] : rr == 2 ? uw[2][i] : uw[3][i];
-                v &= ~(1ull << lane);
-                uint32_t q = rr == 0 ? z[0] : rr == 1 ? z[1] : rr == 2 ? z[2] : z[3];
-#pragma unroll 8
-                for (int bb = 0; bb < 64; ++bb) {
-                    const uint32_t vh = bb < 32 ? static_cast<uint32_t>(v) : static_cast<uint32_t>(v >> 32);
-                    const uint32_t m = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(vh), bb & 31, 1));
-                    q = __builtin_amdgcn_bitop3_b32(q, m, __builtin_amdgcn_readlane(q, bb), 0x78);
+                for (int e = 0; e < 16; ++e) {
+                    const uint32_t vh = e < 8 ? static_cast<uint32_t>(v[i]) : static_cast<uint32_t>(v[i] >> 32);
+                    z ^= tw[16 * e + __builtin_amdgcn_ubfe(vh, 4 * (e & 7), 4)];
                 }
-                zw[lane] = 64 * w + lane < n ? q : 0u;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) z[k] = rr == k ? q : z[k];
             }
-            __syncthreads();
-            if (tid < 256) {
-                uint32_t v = 0;
+            v[i] = row[ww <= wn ? ww : 0];
+        }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v ^= ((tid >> q) & 1) ? zw[4 * (tid >> 4) + q] : 0u;
-                tw[tid] = v;
+        for (int o = 1; o < 8; o <<= 1) z ^= static_cast<uint32_t>(__shfl_xor(static_cast<int>(z), o));
+        if (q == 0) zr[k] = z;
+        if (q == (w & 7)) ur[k] = own;
+        __syncthreads();
+        if (wave == 0) {
+            const bool in = 64 * w + lane < n;
+            const uint64_t own = in ? ur[lane] & ~(1ull << lane) & (w == cw ? (1ull << (n & 63)) - 1 : ~0ull) : 0ull;
+            uint32_t x = in ? zr[lane] : 0u;
+#pragma unroll 16
+            for (int bb = 0; bb < 64; ++bb) {  // bits above a row's own are zero
+                const uint32_t vh = bb < 32 ? static_cast<uint32_t>(own) : static_cast<uint32_t>(own >> 32);
+                const uint32_t m = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(vh), bb & 31, 1));
+                x = __builtin_amdgcn_bitop3_b32(x, m, __builtin_amdgcn_readlane(x, bb), 0x78);
             }
-            __syncthreads();
+            if (in) zf[64 * w + lane] = x;
+            zr[lane] = x;
+            wave_sync();
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (!has[r] || ((tid + kWdThreads * r) >> 6) <= w) continue;
+            for (int i = 0; i < 4; ++i) {  // entries 16 g + e of tables g = 4 i + lane / 16
+                const int g = 4 * i + (lane >> 4);
+                uint32_t e = 0;
 #pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const uint32_t vh = q < 8 ? static_cast<uint32_t>(uw[r][i]) : static_cast<uint32_t>(uw[r][i] >> 32);
-                    z[r] ^= tw[16 * q + __builtin_amdgcn_ubfe(vh, 4 * (q & 7), 4)];
-                }
+                for (int r = 0; r < 4; ++r) e ^= ((lane >> r) & 1) ? zr[4 * g + r] : 0u;
+                zt[kPitch * w + 64 * i + lane] = e;
             }
         }
+        __syncthreads();
     }
-    // columns of the map, and the output words of the basis rows (unit vectors, written by all members)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int p = tid + kWdThreads * r;
-        if (p >= d) continue;
-        reinterpret_cast<uint32_t*>(a.maps + ds.mo + 2 * p)[u] = z[r];
-        reinterpret_cast<uint32_t*>(a.basis + ds.bo + static_cast<int64_t>(p < n ? n - 1 - p : n) * W + fw)[u] = z[r];
+    // columns of the map, and the output words of the basis rows (device-scope: other members read them)
+    for (int p = tid; p < d; p += kWdThreads) {
+        put_dev32(reinterpret_cast<uint32_t*>(a.maps + ds.mo + 2 * p) + u, zf[p]);
+        reinterpret_cast<uint32_t*>(a.basis + ds.bo + static_cast<int64_t>(p < n ? n - 1 - p : n) * W + fw)[u] = zf[p];
     }
     __syncthreads();
 }
 
 // full rank: this member's remaining blocks (blk, blk + G, ...) lie in the span; a row's
 // residual is y + M phi, from tables of the map's columns, four columns each, 32 words
-// of phi (128 KB of tables) at a time.  Each thread takes up to four rows.
+// of phi (128 KB of tables) at a time.  Each thread takes up to two rows.
 __device__ __forceinline__ void check_rows(const FitArgs& a, const CtxDesc& ds, WideShared& L, int blk, int G, int nblk,
                                            int& ncon, long long& firstc) {
     const int tid = threadIdx.x;
@@ -1532,20 +1601,21 @@ __device__ __forceinline__ void check_rows(const FitArgs& a, const CtxDesc& ds, 
     const uint64_t tmask = top_mask(n, fw);
     const u32x4_a8* M = reinterpret_cast<const u32x4_a8*>(a.maps + ds.mo);
     u32x4* tab = &L.tab[0][0][0];  // [512][16]
-    for (int b0 = blk; b0 < nblk; b0 += 64 * G) {  // up to 64 blocks: 4,096 rows
-        const uint64_t* row[4];
-        int64_t ri[4];
-        u32x4 z[4];
+    constexpr int kRowsPer = 2, kStep = kRowsPer * kWdWaves;  // blocks per pass
+    for (int b0 = blk; b0 < nblk; b0 += kStep * G) {
+        const uint64_t* row[kRowsPer];
+        int64_t ri[kRowsPer];
+        u32x4 z[kRowsPer];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int bk = b0 + G * (16 * k + (tid >> 6));
+        for (int k = 0; k < kRowsPer; ++k) {
+            const int bk = b0 + G * (kWdWaves * k + (tid >> 6));
             ri[k] = bk < nblk ? static_cast<int64_t>(bk) * kWdRows + (tid & 63) : ds.m;
             row[k] = a.rows + ds.row0 + (ri[k] < ds.m ? ri[k] : 0) * W;
             z[k] = *reinterpret_cast<const u32x4_a8*>(row[k] + fw);
         }
         for (int w0 = 0; w0 < fw; w0 += 32) {
             __syncthreads();
-            if (tid < 512 && 64 * w0 + 4 * tid < d) {
+            if (64 * w0 + 4 * tid < d) {
                 u32x4 c[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -1561,29 +1631,33 @@ __device__ __forceinline__ void check_rows(const FitArgs& a, const CtxDesc& ds, 
                         if ((e >> q) & 1) v ^= c[q];
                     tab[16 * tid + (e ^ (tid & 15))] = v;  // entries rotated by the table: fewer bank conflicts
                 }
+            } else {
+                tab[16 * tid + (tid & 15)] = u32x4{0, 0, 0, 0};  // no columns: entry 0 is read all the same
             }
             __syncthreads();
+            const int wend = w0 + 32 < fw ? w0 + 32 : fw;
+            uint64_t nx[kRowsPer];
+            auto load_word = [&](int w) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (ri[k] >= ds.m) continue;
-                for (int w = w0; w < fw && w < w0 + 32; ++w) {
-                    uint64_t v = row[k][w];
-                    if (w == fw - 1) v &= tmask;
-                    const int nt = 64 * w + 64 <= d ? 16 : (d - 64 * w + 3) / 4;  // tables of this word
-                    const u32x4* tw = tab + 256 * (w - w0);
-                    if (nt == 16) {
+                for (int k = 0; k < kRowsPer; ++k) nx[k] = row[k][w] & (w == fw - 1 ? tmask : ~0ull);
+            };
+            load_word(w0);
+            for (int w = w0; w < wend; ++w) {  // (a row's cache line serves sixteen steps)
+                uint64_t v[kRowsPer];
 #pragma unroll
-                        for (int q = 0; q < 16; q += 2)
-                            z[k] = xor3_4(z[k], tw[16 * q + ((static_cast<uint32_t>(v >> (4 * q)) & 15u) ^ q)],
-                                          tw[16 * q + 16 + ((static_cast<uint32_t>(v >> (4 * q + 4)) & 15u) ^ (q + 1))]);
-                    } else {
-                        for (int q = 0; q < nt; ++q) z[k] ^= tw[16 * q + ((static_cast<uint32_t>(v >> (4 * q)) & 15u) ^ q)];
-                    }
-                }
+                for (int k = 0; k < kRowsPer; ++k) v[k] = nx[k];
+                load_word(w + 1 < wend ? w + 1 : w);
+                const u32x4* tw = tab + 256 * (w - w0);
+#pragma unroll
+                for (int q = 0; q < 16; q += 2)
+#pragma unroll
+                    for (int k = 0; k < kRowsPer; ++k)
+                        z[k] = xor3_4(z[k], tw[16 * q + ((static_cast<uint32_t>(v[k] >> (4 * q)) & 15u) ^ q)],
+                                      tw[16 * q + 16 + ((static_cast<uint32_t>(v[k] >> (4 * q + 4)) & 15u) ^ (q + 1))]);
             }
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < kRowsPer; ++k)
             if (ri[k] < ds.m && any4(z[k])) {
                 ++ncon;
                 if (ri[k] < firstc) firstc = ri[k];
@@ -1618,11 +1692,23 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
     const uint64_t v1 = 2 * j + 1 < fw ? (2 * j + 1 == fw - 1 ? tmask : ~0ull) : 0ull;
     const u32x4 vm = {static_cast<uint32_t>(v0), static_cast<uint32_t>(v0 >> 32), static_cast<uint32_t>(v1),
                       static_cast<uint32_t>(v1 >> 32)};
+    auto load_block = [&](int64_t bk, BlockRows& b) {
+        const uint64_t* rb = R + bk * kWdRows * W;
+        const int nb = m - bk * kWdRows < kWdRows ? static_cast<int>(m - bk * kWdRows) : kWdRows;
+#pragma unroll
+        for (int i = 0; i < kWdPairs; ++i) {
+            const int r = 8 * wave + 2 * i + h;
+            b.acc[i] = *reinterpret_cast<const u32x4_a8*>(rb + static_cast<int64_t>(r < nb ? r : 0) * W + (2 * j < fw ? 2 * j : 0));
+        }
+        const int r = 8 * wave + (lane & 7);
+        b.y = *reinterpret_cast<const u32x4_a8*>(rb + static_cast<int64_t>(r < nb ? r : 0) * W + fw);
+    };
     if (tid == 0) {
         L.timeout = 0;
         L.nrows = 0;
         L.next = 0;
         L.any[0] = L.any[1] = 0;
+        L.more = 0;
     }
     __syncthreads();
     int nrows = 0;
@@ -1634,6 +1720,8 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
     int phase = 0, bpos = 0, bidx = 0, bK = 0;
     int64_t blk = g;
     bool full = false;
+    BlockRows nextb;  // the next block's rows, loaded ahead
+    if (blk < blocks) load_block(blk, nextb);
     // wavefront 0: wait until every block below `until` is done (or, with bar > 0, every member
     // past that barrier), then take the list's new entries
     auto wait_for = [&](int64_t until, int bar) {
@@ -1675,7 +1763,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                 if (tid == 0) put_progress(prog, g, seq, kWdBar + 1);
                 wait_for(0, 1);
             }
-            __threadfence();  // no line of the list read before it was whole is read again
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // no line of the list read before it was whole is read again
             phase = 1;
             full = nrows >= d;
             // pivot columns and the counts above each word (descending-priority positions)
@@ -1719,29 +1807,20 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
         BlockRows b;
         const int nb = phase == 1 ? bK : (m - blk * kWdRows < kWdRows ? static_cast<int>(m - blk * kWdRows) : kWdRows);
         if (phase == 0) {
-            const uint64_t* rb = R + blk * kWdRows * W;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int r = 4 * wave + 2 * i + h;
-                const uint64_t* row = rb + static_cast<int64_t>(r < nb ? r : 0) * W;
-                b.acc[i] = *reinterpret_cast<const u32x4_a8*>(row + (2 * j < fw ? 2 * j : 0));
-                b.acc[i] &= vm & (r < nb ? ~0u : 0u);
-            }
-            const int r = 4 * wave + (lane & 3);
-            b.y = *reinterpret_cast<const u32x4_a8*>(rb + static_cast<int64_t>(r < nb ? r : 0) * W + fw);
-            b.y &= lane < 4 && r < nb ? ~0u : 0u;
+            b = nextb;
         } else {
             const int voff = 16 * (2 * j < fw ? j : 0);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int r = 4 * wave + 2 * i + h;
+            for (int i = 0; i < kWdPairs; ++i) {
+                const int r = 8 * wave + 2 * i + h;
                 b.acc[i] = load16<true>(X, (bpos + (r < nb ? r : 0)) * W * 8 + voff, 0);
-                b.acc[i] &= vm & (r < nb ? ~0u : 0u);
             }
-            const int r = 4 * wave + (lane & 3);
+            const int r = 8 * wave + (lane & 7);
             b.y = load16<true>(X, ((bpos + (r < nb ? r : 0)) * W + fw) * 8, 0);
-            b.y &= lane < 4 && r < nb ? ~0u : 0u;
         }
+#pragma unroll
+        for (int i = 0; i < kWdPairs; ++i) b.acc[i] &= vm & (8 * wave + 2 * i + h < nb ? ~0u : 0u);
+        b.y &= lane < 8 && 8 * wave + lane < nb ? ~0u : 0u;
         if (phase == 0 && G > 1) {  // what the other members have added meanwhile
             if (wave == 0) {
                 const int open = lowest_open(prog, G, g, seq, static_cast<int>(blk));
@@ -1763,12 +1842,15 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                 pos = nrows;
             } else {
 #pragma unroll
-                for (int o = 4; o < 64; o <<= 1) b.y ^= shfl_xor4(b.y, o);
+                for (int o = 8; o < 64; o <<= 1) b.y ^= shfl_xor4(b.y, o);
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i) b.acc[i] &= vm;  // (the lanes past the row collected other words)
+            for (int i = 0; i < kWdPairs; ++i) b.acc[i] &= vm;  // (the lanes past the row collected other words)
             if (phase == 1) break;
-            if (__ballot(any4(b.acc[0]) || any4(b.acc[1])) && lane == 0) L.any[flip] = 1;
+            bool mine = false;
+#pragma unroll
+            for (int i = 0; i < kWdPairs; ++i) mine |= any4(b.acc[i]);
+            if (__ballot(mine) && lane == 0) L.any[flip] = 1;
             if (tid == 0) L.any[flip ^ 1] = 0;
             __syncthreads();
             anynz = __builtin_amdgcn_readfirstlane(L.any[flip]) != 0;
@@ -1777,12 +1859,12 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
             wait_for(blk, 0);  // (ends the phase: every earlier block is done)
             open = 0x7fffffff;
             if (pos == nrows) break;
-            b.y &= lane < 4 ? ~0u : 0u;
+            b.y &= lane < 8 ? ~0u : 0u;
         }
         if (phase == 1) {  // fully reduced rows to their final places
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int r = 4 * wave + 2 * i + h;
+            for (int i = 0; i < kWdPairs; ++i) {
+                const int r = 8 * wave + 2 * i + h;
                 if (r < nb) {
                     const int p = L.piv[bpos + r] & (kPivLast - 1);
                     int k = nrows - 1;
@@ -1793,12 +1875,12 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                         k = L.above[p >> 6] + __popcll(v);
                     }
                     uint64_t* out = a.basis + ds.bo + static_cast<int64_t>(k) * W;
-                    if (2 * j < fw) out[2 * j] = (static_cast<uint64_t>(b.acc[i].y) << 32) | b.acc[i].x;
-                    if (2 * j + 1 < fw) out[2 * j + 1] = (static_cast<uint64_t>(b.acc[i].w) << 32) | b.acc[i].z;
+                    if (2 * j < fw) put_dev(out + 2 * j, (static_cast<uint64_t>(b.acc[i].y) << 32) | b.acc[i].x);
+                    if (2 * j + 1 < fw) put_dev(out + 2 * j + 1, (static_cast<uint64_t>(b.acc[i].w) << 32) | b.acc[i].z);
                 }
             }
-            const int r = 4 * wave + lane;
-            if (lane < 4 && r < nb) {
+            const int r = 8 * wave + lane;
+            if (lane < 8 && r < nb) {
                 const int p = L.piv[bpos + r] & (kPivLast - 1);
                 int k = nrows - 1;
                 if (p != n) {
@@ -1830,8 +1912,8 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                 // the rows, and which words the pending ones hold (the constant apart)
                 uint32_t ev = 0, od = 0;
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int r = 4 * wave + 2 * i + h;
+                for (int i = 0; i < kWdPairs; ++i) {
+                    const int r = 8 * wave + 2 * i + h;
                     Rm[r * kRowPitch + j] = b.acc[i];
                     const bool pe = !((ins >> r) & 1ull);
                     const uint64_t w0 = ((static_cast<uint64_t>(b.acc[i].y) << 32) | b.acc[i].x) & (2 * j == cw ? ~cbit : ~0ull);
@@ -1839,13 +1921,15 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                     const uint64_t be = __ballot(pe && w0 != 0), bo = __ballot(pe && w1 != 0);
                     ev |= static_cast<uint32_t>(be) | static_cast<uint32_t>(be >> 32);
                     od |= static_cast<uint32_t>(bo) | static_cast<uint32_t>(bo >> 32);
+                    if (__ballot(pe && any4(b.acc[i])) && lane == 0) L.more = 1;
                 }
-                if (lane < 4) L.ys[4 * wave + lane] = b.y;
+                if (lane < 8) L.ys[8 * wave + lane] = b.y;
                 if (lane == 0) {
                     L.wm[wave][0] = ev;
                     L.wm[wave][1] = od;
                 }
                 __syncthreads();
+                if (!__builtin_amdgcn_readfirstlane(L.more)) break;  // no pending row holds a bit
                 if (wave == 0) {
                     uint32_t v = lane < 2 * kWdWaves ? (&L.wm[0][0])[lane] : 0u;
                     for (int o = 2; o < 32; o <<= 1) v |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), o));
@@ -1865,91 +1949,113 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                     } else {
                         va = (Rw[cw] & cbit) ? 1ull : 0ull;  // only the constant is left
                     }
+                    // a column per lane (bit q: row q), so that a row's bits are one ballot and the
+                    // rows that hold a pivot are one lane's word: row after row, a row with a bit in
+                    // the panel takes its highest as pivot and is added to the other rows that hold it
+                    const uint64_t todo = __ballot((va | vb) != 0) & pend;  // (rows without a bit get none)
+                    va = transpose64(va, lane);
+                    vb = transpose64(vb, lane);
                     uint64_t T = 1ull << lane, now = 0;
-                    for (;;) {
-                        const uint64_t nz = __ballot((va | vb) != 0) & pend;
-                        if (!nz) break;
-                        const int q = ffs64(nz);  // the earliest row with a bit in the panel
-                        const uint64_t fa = readlane64(va, q), fb = readlane64(vb, q), ft = readlane64(T, q);
-                        const bool in_a = fa != 0;
-                        const int bit = msb64(in_a ? fa : fb);
-                        const uint32_t mk = bit_mask(in_a ? va : vb, bit) & (lane == q ? 0u : ~0u);
-                        va = xor_and(va, mk, fa);
-                        vb = xor_and(vb, mk, fb);
-                        T = xor_and(T, mk, ft);
-                        if (lane == q) mypiv = wa < 0 ? n : 64 * (in_a ? wa : wb) + bit;
-                        now |= 1ull << q;
-                        pend &= ~(1ull << q);
-                    }
-                    L.T[lane] = T;
-                    if (lane == 0) {
-                        L.panel = now;
-                        L.more = now != 0;  // (zero: no pending row holds a bit any more)
-                    }
+                    auto half_rows = [&](uint32_t left, auto hi) {  // rows 0-31 or 32-63
+                        constexpr int sft = decltype(hi)::value ? 32 : 0;
+                        auto bit_of = [&](uint64_t v, int q) {
+                            return static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(static_cast<uint32_t>(v >> sft)), q, 1));
+                        };
+                        auto pivot = [&](int q, int word, uint64_t bits, uint64_t& v, uint64_t& v2) {
+                            const int bit = 63 - __builtin_clzll(bits);
+                            const uint64_t self = 1ull << (q + sft);
+                            const uint64_t col = readlane64(v, bit) & ~self;  // rows to clear
+                            const uint32_t m = bit_of(v, q), m2 = bit_of(v2, q), mt = bit_of(T, q);
+                            v = xor_and(v, m, col);
+                            v2 = xor_and(v2, m2, col);
+                            T = xor_and(T, mt, col);
+                            mypiv = lane == q + sft ? 64 * word + bit : mypiv;
+                            now |= self;
+                        };
+                        while (left) {  // (kept small: code run once is bound by its own fetch)
+                            const int q = __builtin_ctz(left);
+                            left &= left - 1;
+                            const uint64_t ra = __ballot(bit_of(va, q) != 0);
+                            if (ra) {
+                                pivot(q, wa, ra, va, vb);
+                            } else {
+                                const uint64_t rb = __ballot(bit_of(vb, q) != 0);
+                                if (rb) pivot(q, wb, rb, vb, va);
+                            }
+                        }
+                    };
+                    half_rows(static_cast<uint32_t>(todo), std::false_type{});
+                    half_rows(static_cast<uint32_t>(todo >> 32), std::true_type{});
+                    if (wa < 0) mypiv = ((now >> lane) & 1ull) ? n : mypiv;
+                    pend &= ~now;
+                    L.T[lane] = transpose64(T, lane);
+                    if (lane == 0) L.panel = now;
                 }
                 __syncthreads();
-                if (!__builtin_amdgcn_readfirstlane(L.more)) break;
+                if (tid == 0) L.more = 0;  // (read by all before the barrier above)
                 const uint64_t now = L.panel;
                 const uint64_t nowu = readlane64(now, 0);
-                uint64_t tl[2];
+                uint64_t tl[kWdPairs];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) tl[i] = L.T[4 * wave + 2 * i + h];
-                const uint64_t ty = L.T[4 * wave + (lane & 3)];
+                for (int i = 0; i < kWdPairs; ++i) tl[i] = L.T[8 * wave + 2 * i + h];
+                const uint64_t ty = L.T[8 * wave + (lane & 7)];
                 if (__popcll(nowu) <= 12) {  // few new rows: each added where T says so
                     uint64_t left = nowu;
-                    u32x4 na[2], ny = b.y & bit_mask(ty, 4 * wave + (lane & 3));
+                    u32x4 na[kWdPairs], ny = b.y & bit_mask(ty, 8 * wave + (lane & 7));
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) na[i] = b.acc[i] & bit_mask(tl[i], 4 * wave + 2 * i + h);
+                    for (int i = 0; i < kWdPairs; ++i) na[i] = b.acc[i] & bit_mask(tl[i], 8 * wave + 2 * i + h);
                     while (left) {
                         const int q = ffs64(left);
                         left &= left - 1;
                         const u32x4 f = Rm[q * kRowPitch + j], z = L.ys[q];
 #pragma unroll
-                        for (int i = 0; i < 2; ++i)  // (the row itself is in already)
-                            na[i] = xor_and4(na[i], (4 * wave + 2 * i + h == q) ? 0u : bit_mask(tl[i], q), f);
-                        ny = xor_and4(ny, (4 * wave + (lane & 3) == q) ? 0u : bit_mask(ty, q), z);
+                        for (int i = 0; i < kWdPairs; ++i)  // (the row itself is in already)
+                            na[i] = xor_and4(na[i], (8 * wave + 2 * i + h == q) ? 0u : bit_mask(tl[i], q), f);
+                        ny = xor_and4(ny, (8 * wave + (lane & 7) == q) ? 0u : bit_mask(ty, q), z);
                     }
-                    b.acc[0] = na[0];
-                    b.acc[1] = na[1];
+#pragma unroll
+                    for (int i = 0; i < kWdPairs; ++i) b.acc[i] = na[i];
                     b.y = ny;
                 } else {
-                    u32x4 na[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, ny = {0, 0, 0, 0};
-                    const int t = wave >> 1;
-                    const bool hb = wave & 1;
-#pragma unroll 1
-                    for (int hf = 0; hf < 2; ++hf) {
-                        const u32x4* f = Rm + (32 * hf + 4 * t) * kRowPitch + j;
-                        const u32x4 f0 = f[0], f1 = f[kRowPitch];
-                        const uint32_t mh = h ? ~0u : 0u;
-                        u32x4 base = f[2 * kRowPitch] & mh;
-                        if (hb) base ^= f[3 * kRowPitch];
-                        u32x4* e = ET + (16 * t + (hb ? 8 : 0) + 4 * h) * 32 + j;
-                        e[0] = base;
-                        e[32] = base ^ f0;
-                        e[64] = base ^ f1;
-                        e[96] = xor3_4(base, f0, f1);
-                        __syncthreads();
-                        uint32_t th[2];
+                    u32x4 na[kWdPairs], ny = {0, 0, 0, 0};
 #pragma unroll
-                        for (int i = 0; i < 2; ++i) th[i] = static_cast<uint32_t>(hf ? tl[i] >> 32 : tl[i]);
+                    for (int i = 0; i < kWdPairs; ++i) na[i] = u32x4{0, 0, 0, 0};
+#pragma unroll 1
+                    for (int hf = 0; hf < 2; ++hf) {  // 32 rows, 8 tables at a time
+                        const u32x4* f = Rm + (32 * hf + 4 * wave) * kRowPitch + j;
+                        const u32x4 f0 = f[0], f1 = f[kRowPitch], f01 = f0 ^ f1;
+                        const u32x4 b0 = f[2 * kRowPitch] & (h ? ~0u : 0u), b1 = b0 ^ f[3 * kRowPitch];
+                        u32x4* e = ET + (16 * wave + 4 * h) * 32 + j;
+                        e[0] = b0;
+                        e[32] = b0 ^ f0;
+                        e[64] = b0 ^ f1;
+                        e[96] = b0 ^ f01;
+                        e[256] = b1;
+                        e[288] = b1 ^ f0;
+                        e[320] = b1 ^ f1;
+                        e[352] = b1 ^ f01;
+                        __syncthreads();
+                        uint32_t th[kWdPairs];
+#pragma unroll
+                        for (int i = 0; i < kWdPairs; ++i) th[i] = static_cast<uint32_t>(hf ? tl[i] >> 32 : tl[i]);
 #pragma unroll
                         for (int q = 0; q < 8; q += 2)
 #pragma unroll
-                            for (int i = 0; i < 2; ++i)
+                            for (int i = 0; i < kWdPairs; ++i)
                                 na[i] = xor3_4(na[i], ET[(16 * q + __builtin_amdgcn_ubfe(th[i], 4 * q, 4)) * 32 + j],
                                                ET[(16 * q + 16 + __builtin_amdgcn_ubfe(th[i], 4 * q + 4, 4)) * 32 + j]);
-                        const int ly = (lane >> 2) & 7;
-                        const uint32_t nib = lane < 32 ? static_cast<uint32_t>(hf ? ty >> 32 : ty) >> (4 * ly) : 0u;
+                        const int ly = lane >> 3;
+                        const uint32_t nib = static_cast<uint32_t>(hf ? ty >> 32 : ty) >> (4 * ly);
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
                             ny = xor_and4(ny, static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(nib), i, 1)),
                                           L.ys[32 * hf + 4 * ly + i]);
                         __syncthreads();
                     }
-                    b.acc[0] = na[0];
-                    b.acc[1] = na[1];
 #pragma unroll
-                    for (int o = 4; o < 64; o <<= 1) ny ^= shfl_xor4(ny, o);
+                    for (int i = 0; i < kWdPairs; ++i) b.acc[i] = na[i];
+#pragma unroll
+                    for (int o = 8; o < 64; o <<= 1) ny ^= shfl_xor4(ny, o);
                     b.y = ny;
                 }
                 ins |= nowu;
@@ -1971,8 +2077,8 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                     __hip_atomic_store(ent + nrows + K, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int r = 4 * wave + 2 * i + h;
+            for (int i = 0; i < kWdPairs; ++i) {
+                const int r = 8 * wave + 2 * i + h;
                 const int k = __popcll(ins & ((1ull << r) - 1));
                 if (((ins >> r) & 1ull) && k < K) {
                     const int off = (nrows + k) * W * 8 + 16 * j;
@@ -1981,20 +2087,20 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                 }
             }
             {
-                const int r = 4 * wave + lane;
-                const int k = lane < 4 ? __popcll(ins & ((1ull << r) - 1)) : K;
-                if (lane < 4 && ((ins >> r) & 1ull) && k < K)
+                const int r = 8 * wave + lane;
+                const int k = lane < 8 ? __popcll(ins & ((1ull << r) - 1)) : K;
+                if (lane < 8 && ((ins >> r) & 1ull) && k < K)
                     __builtin_amdgcn_raw_buffer_store_b128(b.y, X, ((nrows + k) * W + fw) * 8, 0, kDevScope);
             }
             __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's stores performed
             nrows += K;
         }
         {  // the other rows: redundant, or contradictory when an output bit is left
-            const int r = 4 * wave + lane;
-            const uint64_t cm = __ballot(lane < 4 && r < nb && !((ins >> r) & 1ull) && any4(b.y));
+            const int r = 8 * wave + lane;
+            const uint64_t cm = __ballot(lane < 8 && r < nb && !((ins >> r) & 1ull) && any4(b.y));
             if (cm) {
                 ncon += lane == 0 ? __popcll(cm) : 0;
-                const long long f = blk * kWdRows + 4 * wave + ffs64(cm);
+                const long long f = blk * kWdRows + 8 * wave + ffs64(cm);
                 if (lane == 0 && f < firstc) firstc = f;
             }
         }
@@ -2002,6 +2108,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
         __syncthreads();
         blk += G;
         if (G > 1 && tid == 0) put_progress(prog, g, seq, static_cast<int>((blk - g) / G));
+        if (blk < blocks) load_block(blk, nextb);
     }
     // outputs
     const int64_t po = ds.po, mo = ds.mo;
@@ -2020,15 +2127,15 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                 a.maps[mo + 2 * p + 1] = 0;
             }
     }
-    // every member's part of the map and the basis written; the list is dead
-    __threadfence();
+    // every member's part of the map and the basis written (what others read of it at
+    // device scope: a release fence would write back a whole L2); the list is dead
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (G > 1) {
         if (tid == 0) put_progress(prog, g, seq, kWdBar + 2);
         wait_for(0, 2);
     }
-    __threadfence();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (full) {
         if (blk < blocks) check_rows(a, ds, L, static_cast<int>(blk), G, static_cast<int>(blocks), ncon, firstc);
     } else if (has_parity_rows(d, rank)) {
