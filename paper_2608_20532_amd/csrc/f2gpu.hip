@@ -3598,17 +3598,19 @@ __global__ __launch_bounds__(256) void k_pool_finish(PoolArgs P) {
 // ---------------------------------------------------------------------------
 // interleaved-stream ingestion: the rows of many contexts arrive mixed, in
 // stream order (Sec. 3: observations are gathered across a corpus); the fit takes
-// each context's rows contiguous and in stream order.  A stable LSD radix sort of
-// (context, row) pairs by context, 9 bits per pass (per-block LDS histograms, the
-// column scan of the encode sort, a stable scatter), then each context's rows are
-// copied, trimmed to its row width, to their offsets.  Rows of an out-of-range
-// context, of a width outside [0, F2_MAX_N_BITS], or wider than the stride sort
-// last and are dropped.
+// each context's rows contiguous and in stream order.  A stable LSD radix sort of the row
+// indices by context, 9 bits per pass (per-block LDS histograms, the column scan of the
+// encode sort, a stable scatter that sorts a tile in LDS and writes runs), then one gather
+// copies each row, trimmed to its context's row width, to its place.  Rows of an out-of-range
+// context sort last and are dropped; a context whose width is outside [0, F2_MAX_N_BITS] or
+// needs more words than the stride gives its rows no words.
 // ---------------------------------------------------------------------------
 constexpr int kGrpDigitBits = 9;  // two passes up to 2^18 - 1 contexts
 constexpr int kGrpBins = 1 << kGrpDigitBits;
 constexpr int kGrpThreads = 1024;
 constexpr int kGrpWaves = kGrpThreads / 64;
+constexpr int kGrpSteps = 16;  // scatter: 64-row steps per wavefront and tile
+constexpr int kGrpTile = kGrpThreads * kGrpSteps;
 
 struct GroupArgs {
     int32_t num_ctx;
@@ -3620,125 +3622,225 @@ struct GroupArgs {
     int32_t blocks;
     int64_t qc;             // rows per count / scatter block
     int32_t shift;          // digit of this pass: (key >> shift) & (kGrpBins - 1)
-    const int2* in;         // pairs (key, row) of the previous pass, or null (first pass: from ctx_id)
-    int2* out;
+    const int32_t* in;      // keys of the previous pass, or null (first pass: from ctx_id)
+    const int32_t* in_row;  // and their rows (first pass: in stream order)
+    int32_t* out;           // this pass's keys, sorted up to its digit
+    int32_t* out_row;       // and their rows
     int32_t* hist;          // [blocks][kGrpBins]
     int32_t* total;         // [kGrpBins]
-    int32_t* first;         // [num_ctx] first sorted position of each context
-    int32_t* count;         // [num_ctx] rows of each context
-    int64_t* blk;           // [ceil(num_ctx / 1024) + 1] words per block of contexts, then their offsets
+    int2* bound;            // [num_ctx] first sorted position and end (0: no rows) of each context;
+                            // then GroupDest
+    int64_t* blk;           // [ceil(num_ctx / 1024)] words per block of contexts (scanned: before it)
     uint64_t* rows_out;
     int64_t* row_off;       // [num_ctx + 1]
     int64_t* dropped;       // [1]
 };
 
-// the sort key of a row: its context, or num_ctx for a row that is dropped
+// the sort key of a row: its context, or num_ctx for a row of none.  (The width is left to the
+// kernels that work per context: a lookup per row here took 25 us of 41 in the first
+// count of 7.24M rows.)
 __device__ __forceinline__ int group_key(const GroupArgs& g, int64_t r) {
+    if (g.in) return g.in[r];
     const int c = g.ctx_id[r];
-    if (c < 0 || c >= g.num_ctx) return g.num_ctx;
+    return c < 0 || c >= g.num_ctx ? g.num_ctx : c;
+}
+
+// words of a row of context c, 0 where its rows are dropped
+__device__ __forceinline__ int group_width(const GroupArgs& g, int c) {
     const int n = g.n_bits[c];
-    if (n < 0 || n > F2_MAX_N_BITS || feat_words(n) + F2_Y_WORDS > g.stride) return g.num_ctx;
-    return c;
+    if (n < 0 || n > F2_MAX_N_BITS) return 0;
+    const int w = feat_words(n) + F2_Y_WORDS;
+    return w <= g.stride ? w : 0;
 }
 
-__device__ __forceinline__ int2 group_pair(const GroupArgs& g, int64_t r) {
-    return g.in ? g.in[r] : make_int2(group_key(g, r), static_cast<int>(r));
-}
-
+// per-block histogram of the pass's digit; the first pass also clears what the later
+// kernels write into.  Eight rows per thread and step, their loads in flight together.
 __global__ __launch_bounds__(kGrpThreads) void k_grp_count(GroupArgs g) {
     __shared__ int sBin[kGrpBins];
     const int tid = threadIdx.x;
     if (tid < kGrpBins) sBin[tid] = 0;
+    if (!g.in) {
+        for (int64_t c = static_cast<int64_t>(blockIdx.x) * kGrpThreads + tid; c < g.num_ctx;
+             c += static_cast<int64_t>(gridDim.x) * kGrpThreads)
+            g.bound[c] = make_int2(0, 0);
+        if (blockIdx.x == 0 && tid == 0) *g.dropped = 0;
+    }
     __syncthreads();
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * g.qc;
     const int64_t r1 = r0 + g.qc < g.nr ? r0 + g.qc : g.nr;
-    for (int64_t r = r0 + tid; r < r1; r += kGrpThreads)
-        atomicAdd(&sBin[(group_pair(g, r).x >> g.shift) & (kGrpBins - 1)], 1);
+    constexpr int U = 8;
+    for (int64_t r = r0 + tid; r < r1; r += U * kGrpThreads) {
+        int k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = r + u * kGrpThreads < r1 ? group_key(g, r + u * kGrpThreads) : -1;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k[u] >= 0) atomicAdd(&sBin[(k[u] >> g.shift) & (kGrpBins - 1)], 1);
+    }
     __syncthreads();
     if (tid < kGrpBins) g.hist[static_cast<int64_t>(blockIdx.x) * kGrpBins + tid] = sBin[tid];
 }
 
-// stable scatter: the block's rows in rounds of kGrpThreads, wavefront w taking
-// the round's w-th 64 rows; within a wavefront a row's rank among equal digits
-// comes from the ballots of the digit bits, across wavefronts from per-wavefront
-// digit counts, across rounds from the running cursor of each digit
+// a & ~(m ^ b): bit k of the truth table is the result for (a, m, b) = the bits of k
+__device__ __forceinline__ uint32_t same_bit(uint32_t a, uint32_t m, int b) {
+    return static_cast<uint32_t>(__builtin_amdgcn_bitop3_b32(static_cast<int>(a), static_cast<int>(m), b, 0x90));
+}
+
+// stable scatter of a block's rows, a tile of up to kGrpTile at a time: each wavefront
+// ranks a contiguous stretch of the tile, 64 rows a step (ballots of the digit bits give a
+// row's rank among equal digits of its 64, the wavefront's own counter those before
+// them), one scan over wavefronts and digits places them in LDS in sorted order, and the tile
+// goes out in runs of equal digits (a run is 32 keys, 128 bytes, when 512 digits are equally
+// common).  Bound by the chain of a step.  7.24M rows: 47 us a pass; scattering (key,
+// row) pairs straight from registers took 94 us (512 open lines per block, which the XCD's L2
+// evicts partly written).
 __global__ __launch_bounds__(kGrpThreads) void k_grp_scatter(GroupArgs g) {
-    __shared__ int sCur[kGrpBins];
-    __shared__ int sCnt[kGrpWaves][kGrpBins];
-    __shared__ int sBase[kGrpBins];
+    __shared__ int sKey[kGrpTile], sRow[kGrpTile];
+    __shared__ alignas(16) uint16_t sCnt[kGrpWaves][kGrpBins];  // at most kGrpTile: fits
+    __shared__ int sLoc[kGrpBins], sGlob[kGrpBins];
+    __shared__ int sSum[kGrpBins / 64], sTot[kGrpBins / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid < kGrpBins) {  // the bin's start: bins before it over every block, then the blocks before this one
-        int base = 0;
-        for (int b = 0; b < tid; ++b) base += g.total[b];
-        sCur[tid] = base + g.hist[static_cast<int64_t>(blockIdx.x) * kGrpBins + tid];
-    }
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * g.qc;
     const int64_t r1 = r0 + g.qc < g.nr ? r0 + g.qc : g.nr;
-    const uint64_t lt = (1ull << lane) - 1;
-    for (int64_t rb = r0; rb < r1; rb += kGrpThreads) {
-        for (int k = tid; k < kGrpWaves * kGrpBins; k += kGrpThreads) (&sCnt[0][0])[k] = 0;
-        const int64_t r = rb + 64 * wave + lane;
-        const bool live = r < r1;
-        const int2 pr = live ? group_pair(g, r) : make_int2(0, 0);
-        const int dg = (pr.x >> g.shift) & (kGrpBins - 1);
-        uint64_t peers = __ballot(live);
+    const int tiles = static_cast<int>((g.qc + kGrpTile - 1) / kGrpTile);
+    // 64-row steps of a wavefront per tile, equal over the tiles
+    const int steps = static_cast<int>(((g.qc + tiles - 1) / tiles + kGrpThreads - 1) / kGrpThreads);
+    const int tile = steps * kGrpThreads;
+    // a digit's next position: the digits before it over every block, then the blocks before this one
+    int next = 0, own = 0;
+    if (tid < kGrpBins) {
+        own = g.total[tid];
+        int x = own;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(x, o);
+            if (lane >= o) x += t;
+        }
+        if (lane == 63) sTot[wave] = x;
+        next = x - own + g.hist[static_cast<int64_t>(blockIdx.x) * kGrpBins + tid];
+    }
+    __syncthreads();
+    if (tid < kGrpBins)
+        for (int w = 0; w < wave; ++w) next += sTot[w];
+    uint16_t* cnt = sCnt[wave];
+    for (int64_t t0 = r0; t0 < r1; t0 += tile) {
+        const int n = static_cast<int>(r1 - t0 < tile ? r1 - t0 : tile);
+        const int e0 = wave * steps * 64 + lane;  // this lane's first element of the tile
+        int key[kGrpSteps];
+        int row[kGrpSteps];
+        int rank[kGrpSteps];
 #pragma unroll
-        for (int b = 0; b < kGrpDigitBits; ++b) {
-            const uint64_t m = __ballot(live && ((dg >> b) & 1));
-            peers &= ((dg >> b) & 1) ? m : ~m;
+        for (int u = 0; u < kGrpSteps; ++u) key[u] = u < steps && e0 + u * 64 < n ? group_key(g, t0 + e0 + u * 64) : -1;
+#pragma unroll
+        for (int u = 0; u < kGrpSteps; ++u) {
+            const int64_t r = t0 + e0 + u * 64;
+            row[u] = key[u] >= 0 && g.in ? g.in_row[r] : static_cast<int>(r);
         }
-        const int rank = __popcll(peers & lt);
-        __syncthreads();  // counts cleared
-        if (live && rank == __popcll(peers) - 1) sCnt[wave][dg] = __popcll(peers);  // the group's last lane
-        __syncthreads();
-        if (tid < kGrpBins) {  // per digit: exclusive prefix over the wavefronts, the round's count to the cursor
-            int run = sCur[tid];
-            for (int w = 0; w < kGrpWaves; ++w) {
-                const int c = sCnt[w][tid];
-                sCnt[w][tid] = run;
-                run += c;
+        *reinterpret_cast<uint4*>(&cnt[lane * 8]) = uint4{0, 0, 0, 0};
+        wave_sync();
+#pragma unroll
+        for (int u = 0; u < kGrpSteps; ++u) {
+            const bool live = key[u] >= 0;
+            const int dg = (key[u] >> g.shift) & (kGrpBins - 1);
+            const uint64_t alive = __ballot(live);
+            uint32_t lo = static_cast<uint32_t>(alive), hi = static_cast<uint32_t>(alive >> 32);
+#pragma unroll
+            for (int b = 0; b < kGrpDigitBits; ++b) {  // keep the lanes whose bit is this lane's
+                const int own_bit = (dg << (31 - b)) >> 31;
+                const uint64_t m = __ballot(own_bit != 0);
+                lo = same_bit(lo, static_cast<uint32_t>(m), own_bit);
+                hi = same_bit(hi, static_cast<uint32_t>(m >> 32), own_bit);
             }
-            sBase[tid] = run;
+            const int before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+            const int all = __popc(lo) + __popc(hi);
+            rank[u] = live ? cnt[dg] + before : 0;
+            wave_sync();
+            if (live && before == all - 1) cnt[dg] = static_cast<uint16_t>(rank[u] + 1);  // the digit's last lane
+            wave_sync();
         }
         __syncthreads();
-        if (live) g.out[sCnt[wave][dg] + rank] = pr;
+        int sum = 0, x = 0;
+        if (tid < kGrpBins) {
+#pragma unroll
+            for (int w = 0; w < kGrpWaves; ++w) {  // exclusive prefix over the wavefronts
+                const int c = sCnt[w][tid];
+                sCnt[w][tid] = static_cast<uint16_t>(sum);
+                sum += c;
+            }
+            x = sum;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(x, o);
+                if (lane >= o) x += t;
+            }
+            if (lane == 63) sSum[wave] = x;
+        }
         __syncthreads();
-        if (tid < kGrpBins) sCur[tid] = sBase[tid];
+        if (tid < kGrpBins) {
+            int loc = x - sum;
+            for (int w = 0; w < wave; ++w) loc += sSum[w];
+            sLoc[tid] = loc;
+            sGlob[tid] = next - loc;
+            next += sum;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kGrpSteps; ++u)
+            if (key[u] >= 0) {
+                const int dg = (key[u] >> g.shift) & (kGrpBins - 1);
+                const int i = sLoc[dg] + cnt[dg] + rank[u];
+                sKey[i] = key[u];
+                sRow[i] = row[u];
+            }
+        __syncthreads();
+        // (the next tile's first barrier stands between these reads and its writes)
+        for (int i = tid; i < n; i += kGrpThreads) {
+            const int k = sKey[i];
+            const int pos = sGlob[(k >> g.shift) & (kGrpBins - 1)] + i;
+            g.out[pos] = k;
+            g.out_row[pos] = sRow[i];
+        }
     }
 }
 
-// first position and row count of each context, rows dropped (contexts zeroed first)
-__global__ __launch_bounds__(256) void k_grp_clear(GroupArgs g) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c < g.num_ctx) {
-        g.first[c] = 0;
-        g.count[c] = 0;
-    }
-    if (c == 0) *g.dropped = 0;
-}
-
+// first position and end of each context, rows of none (cleared by the first count); four sorted positions per thread
 __global__ __launch_bounds__(256) void k_grp_bounds(GroupArgs g) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= g.nr) return;
-    const int k = g.in[i].x;
-    const bool start = i == 0 || g.in[i - 1].x != k;
-    if (k == g.num_ctx) {
-        if (start) *g.dropped = g.nr - i;
-        return;
+    const int64_t i0 = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * 4;
+    if (i0 >= g.nr) return;
+    int k[6];  // the positions before and after too
+    k[0] = i0 > 0 ? g.out[i0 - 1] : -1;
+#pragma unroll
+    for (int u = 0; u < 5; ++u) k[u + 1] = i0 + u < g.nr ? g.out[i0 + u] : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t i = i0 + u;
+        if (i >= g.nr) break;
+        const int c = k[u + 1];
+        const bool start = c != k[u];
+        if (c == g.num_ctx) {
+            if (start) *g.dropped = g.nr - i;
+            continue;
+        }
+        if (start) g.bound[c].x = static_cast<int32_t>(i);
+        if (c != k[u + 2]) g.bound[c].y = static_cast<int32_t>(i + 1);
     }
-    if (start) g.first[k] = static_cast<int32_t>(i);
-    if (i == g.nr - 1 || g.in[i + 1].x != k) g.count[k] = static_cast<int32_t>(i + 1);  // end, made a count below
 }
 
-// words per block of 1024 contexts (end positions made counts)
+// where a context's rows go: sorted position p lies at word base + p * width, kept as
+// base << 8 | width in the 8 bytes of its bounds.  base may be negative; |base| < 2^31 * 66.
+__device__ __forceinline__ int64_t group_dest(int64_t row_off, int first, int width) {
+    return ((row_off - static_cast<int64_t>(first) * width) << 8) | width;
+}
+
+// words per context (and the rows of contexts of a bad width, to the dropped) and per block of 1024 contexts
 __global__ __launch_bounds__(1024) void k_grp_words(GroupArgs g) {
     __shared__ int64_t sW[16];
     const int c = blockIdx.x * 1024 + threadIdx.x;
     int64_t v = 0;
     if (c < g.num_ctx) {
-        const int cnt = g.count[c] ? g.count[c] - g.first[c] : 0;
-        g.count[c] = cnt;
-        v = static_cast<int64_t>(cnt) * (feat_words(g.n_bits[c]) + F2_Y_WORDS);
+        const int2 b = g.bound[c];
+        const int w = group_width(g, c);
+        v = static_cast<int64_t>(b.y ? b.y - b.x : 0) * w;
+        if (w == 0 && b.y)
+            atomicAdd(reinterpret_cast<unsigned long long*>(g.dropped), static_cast<unsigned long long>(b.y - b.x));
         g.row_off[c] = v;
     }
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
@@ -3751,7 +3853,7 @@ __global__ __launch_bounds__(1024) void k_grp_words(GroupArgs g) {
     }
 }
 
-// one workgroup: exclusive scan of the blocks' words, the total last
+// one workgroup: exclusive scan of the blocks' words
 __global__ __launch_bounds__(1024) void k_grp_scan(GroupArgs g) {
     __shared__ int64_t sWave[16];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -3776,63 +3878,99 @@ __global__ __launch_bounds__(1024) void k_grp_scan(GroupArgs g) {
         carry += total;
         __syncthreads();
     }
-    if (tid == 0) g.blk[nblk] = carry;
 }
 
-// each context's word offset: its block's offset plus the scan within the block
-__global__ __launch_bounds__(1024) void k_grp_offsets(GroupArgs g) {
-    __shared__ int64_t sWave[16];
+// each context's word offset: the blocks before its own, plus the scan within the block; the
+// dropped-row count out.  Up to kGrpSumBlocks blocks (1M contexts) each sums those before it
+// itself: at most one load per thread, against the 4.8 us of a launch of the scan; beyond, the
+// sums would grow with the square of the contexts.
+constexpr int kGrpSumBlocks = 1024;
+__global__ __launch_bounds__(1024) void k_grp_offsets(GroupArgs g, bool scanned, int64_t* dropped_out) {
+    __shared__ int64_t sWave[16], sBase[16];
     const int tid = threadIdx.x, lane = tid & 63;
     const int c = blockIdx.x * 1024 + tid;
+    int64_t before = 0;
+    if (scanned) {
+        if (tid == 0) before = g.blk[blockIdx.x];
+    } else if (tid < static_cast<int>(blockIdx.x)) {
+        before = g.blk[tid];
+    }
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_down(before, o);
     const int64_t v = c < g.num_ctx ? g.row_off[c] : 0;
     int64_t x = v;
     for (int o = 1; o < 64; o <<= 1) {
         const int64_t t = __shfl_up(x, o);
         if (lane >= o) x += t;
     }
+    if (lane == 0) sBase[tid >> 6] = before;
     if (lane == 63) sWave[tid >> 6] = x;
     __syncthreads();
-    int64_t run = g.blk[blockIdx.x] + x - v;
-    for (int w = 0; w < (tid >> 6); ++w) run += sWave[w];
-    if (c < g.num_ctx) g.row_off[c] = run;
-    if (c == g.num_ctx - 1) g.row_off[g.num_ctx] = g.blk[(g.num_ctx + 1023) / 1024];
+    int64_t run = x - v;
+    for (int w = 0; w < 16; ++w) run += sBase[w] + (w < (tid >> 6) ? sWave[w] : 0);
+    if (c < g.num_ctx) {
+        g.row_off[c] = run;
+        reinterpret_cast<int64_t*>(g.bound)[c] = group_dest(run, g.bound[c].x, group_width(g, c));
+    }
+    if (c == g.num_ctx - 1) g.row_off[g.num_ctx] = run + v;
+    if (blockIdx.x == 0 && tid == 0) *dropped_out = g.nr > 0 ? *g.dropped : 0;
 }
 
-// the dropped-row count out, and row_off[0] = 0 when there are no contexts
-__global__ __launch_bounds__(64) void k_grp_finish(GroupArgs g, int64_t* dropped_out, int no_ctx) {
+// no contexts: every row is dropped
+__global__ __launch_bounds__(64) void k_grp_none(int64_t nr, int64_t* row_off, int64_t* dropped_out) {
     if (threadIdx.x == 0) {
-        *dropped_out = g.nr > 0 ? *g.dropped : 0;
-        if (no_ctx) g.row_off[0] = 0;
+        row_off[0] = 0;
+        *dropped_out = nr;
     }
 }
 
-// output rows: sorted position i copies its row, trimmed to the context's width
-// eight lanes per row: lane j copies words j, j + 8, ... of its row, so one
-// instruction moves up to 64 contiguous bytes of each of 8 rows and no lane waits on
-// a chain of single-word copies
-constexpr int kGrpCopyLanes = 8;
-constexpr int kGrpCopyRowsPerBlock = 256 / kGrpCopyLanes;
-__global__ __launch_bounds__(256) void k_grp_copy(GroupArgs g) {
-    const int j = threadIdx.x % kGrpCopyLanes;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kGrpCopyRowsPerBlock + threadIdx.x / kGrpCopyLanes;
-         i < g.nr; i += static_cast<int64_t>(gridDim.x) * kGrpCopyRowsPerBlock) {
-        const int2 pr = g.in[i];
-        if (pr.x >= g.num_ctx) continue;
-        const int W = feat_words(g.n_bits[pr.x]) + F2_Y_WORDS;
-        const uint64_t* __restrict__ src = g.rows + static_cast<int64_t>(pr.y) * g.stride;
-        uint64_t* __restrict__ dst = g.rows_out + g.row_off[pr.x] + static_cast<int64_t>(i - g.first[pr.x]) * W;
-        for (int w = j; w < W; w += kGrpCopyLanes) dst[w] = src[w];
+// output rows: a gather in sorted order, each row trimmed to its context's width.  A
+// wavefront takes 64 rows: a lane each finds source and destination, then LANES lanes per
+// row copy its words, every load in flight before the first store.  Bound by the lines that
+// the random rows touch (one or two of 128 bytes for the 24-40 that are kept).  7.24M rows
+// of 7 words: 205 us; eight lanes per row that each looked up context and offset took 340
+// us, and a copy in stream order with scattered writes 326 us (lines written in parts).
+template <int LANES>
+__global__ __launch_bounds__(256, 8) void k_grp_copy(GroupArgs g) {
+    __shared__ int64_t sDest[4][64];
+    __shared__ int sRow[4][64];
+    constexpr int RPS = 64 / LANES;  // rows per step
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int j = lane % LANES, k = lane / LANES;
+    const int64_t* __restrict__ dest = reinterpret_cast<const int64_t*>(g.bound);
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 256 + wave * 64;
+    if (i0 >= g.nr) return;
+    const int64_t i = i0 + lane;
+    const int c = i < g.nr ? g.out[i] : g.num_ctx;
+    sRow[wave][lane] = i < g.nr ? g.out_row[i] : 0;
+    const int64_t d = c < g.num_ctx ? dest[c] : 0;
+    sDest[wave][lane] = d + ((i * (d & 255)) << 8);
+    wave_sync();
+    const uint64_t* src[LANES];
+    int64_t e[LANES];
+    uint64_t v[LANES];
+#pragma unroll
+    for (int u = 0; u < LANES; ++u) {
+        e[u] = sDest[wave][u * RPS + k];
+        src[u] = g.rows + static_cast<int64_t>(sRow[wave][u * RPS + k]) * g.stride;
+        v[u] = j < static_cast<int>(e[u] & 255) ? src[u][j] : 0ull;
+    }
+#pragma unroll
+    for (int u = 0; u < LANES; ++u) {
+        const int W = static_cast<int>(e[u] & 255);
+        uint64_t* __restrict__ dst = g.rows_out + (e[u] >> 8);
+        if (j < W) dst[j] = v[u];
+        for (int w = j + LANES; w < W; w += LANES) dst[w] = src[u][w];
     }
 }
 
 inline size_t align256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
 
 
-// workspace of the grouping: two pair buffers, histograms, per-context bounds
+// workspace of the grouping: two buffers of keys and rows, histograms, per-context bounds
 struct GroupPlan {
     int blocks;
     int64_t qc;
-    size_t off_a, off_b, off_hist, off_total, off_first, off_count, off_blk, off_drop, bytes;
+    size_t off_a, off_b, off_hist, off_total, off_bound, off_blk, off_drop, bytes;
 };
 GroupPlan group_workspace(int32_t num_ctx, int64_t nr) {
     GroupPlan p{};
@@ -3845,19 +3983,17 @@ GroupPlan group_workspace(int32_t num_ctx, int64_t nr) {
     if (p.blocks < 1) p.blocks = 1;
     size_t o = 0;
     p.off_a = o;
-    o = align256(o + sizeof(int2) * static_cast<size_t>(nr));
+    o = align256(o + 2 * sizeof(int32_t) * static_cast<size_t>(nr));
     p.off_b = o;
-    o = align256(o + sizeof(int2) * static_cast<size_t>(nr));
+    o = align256(o + 2 * sizeof(int32_t) * static_cast<size_t>(nr));
     p.off_hist = o;
     o = align256(o + sizeof(int32_t) * static_cast<size_t>(p.blocks) * kGrpBins);
     p.off_total = o;
     o = align256(o + sizeof(int32_t) * kGrpBins);
-    p.off_first = o;
-    o = align256(o + sizeof(int32_t) * static_cast<size_t>(num_ctx));
-    p.off_count = o;
-    o = align256(o + sizeof(int32_t) * static_cast<size_t>(num_ctx));
+    p.off_bound = o;
+    o = align256(o + sizeof(int2) * static_cast<size_t>(num_ctx));
     p.off_blk = o;
-    o = align256(o + sizeof(int64_t) * (static_cast<size_t>((num_ctx + 1023) / 1024) + 1));
+    o = align256(o + sizeof(int64_t) * static_cast<size_t>((static_cast<int64_t>(num_ctx) + 1023) / 1024));
     p.off_drop = o;
     o = align256(o + sizeof(int64_t));
     p.bytes = o;
@@ -4354,13 +4490,12 @@ int f2_group_rows(const int32_t* ctx_id, const uint64_t* rows, int32_t row_strid
     g.qc = p.qc;
     g.hist = reinterpret_cast<int32_t*>(ws + p.off_hist);
     g.total = reinterpret_cast<int32_t*>(ws + p.off_total);
-    g.first = reinterpret_cast<int32_t*>(ws + p.off_first);
-    g.count = reinterpret_cast<int32_t*>(ws + p.off_count);
+    g.bound = reinterpret_cast<int2*>(ws + p.off_bound);
     g.blk = reinterpret_cast<int64_t*>(ws + p.off_blk);
     g.rows_out = rows_out;
     g.row_off = row_off_out;
     g.dropped = reinterpret_cast<int64_t*>(ws + p.off_drop);
-    int2* bufs[2] = {reinterpret_cast<int2*>(ws + p.off_a), reinterpret_cast<int2*>(ws + p.off_b)};
+    int32_t* bufs[2] = {reinterpret_cast<int32_t*>(ws + p.off_a), reinterpret_cast<int32_t*>(ws + p.off_b)};
     // passes: kGrpDigitBits bits of the key (0 .. num_ctx) each
     int bits = 1;
     while ((int64_t{1} << bits) <= num_ctx) ++bits;
@@ -4372,34 +4507,38 @@ int f2_group_rows(const int32_t* ctx_id, const uint64_t* rows, int32_t row_strid
     cs.hist = g.hist;
     cs.total = g.total;
     g.in = nullptr;
-    if (num_rows > 0) {
-        for (int k = 0; k < passes; ++k) {
-            g.shift = kGrpDigitBits * k;
-            g.out = bufs[k & 1];
-            hipLaunchKernelGGL(k_grp_count, dim3(p.blocks), dim3(kGrpThreads), 0, s, g);
-            hipLaunchKernelGGL(k_enc_colscan, dim3((kGrpBins + 63) / 64), dim3(64 * kColWaves), 0, s, cs);
-            hipLaunchKernelGGL(k_grp_scatter, dim3(p.blocks), dim3(kGrpThreads), 0, s, g);
-            g.in = g.out;
-        }
+    g.in_row = nullptr;
+    g.out = nullptr;
+    g.out_row = nullptr;
+    if (num_ctx == 0) {
+        hipLaunchKernelGGL(k_grp_none, dim3(1), dim3(64), 0, s, num_rows, row_off_out, dropped_out);
+        return hipGetLastError() == hipSuccess ? F2_OK : F2_EDEVICE;
     }
-    const unsigned cb = static_cast<unsigned>((num_ctx + 255) / 256);
-    if (num_ctx > 0) hipLaunchKernelGGL(k_grp_clear, dim3(cb), dim3(256), 0, s, g);
-    else hipLaunchKernelGGL(k_grp_clear, dim3(1), dim3(256), 0, s, g);
+    // (without rows one count clears what the bounds would write)
+    for (int k = 0; k < (num_rows > 0 ? passes : 1); ++k) {
+        g.shift = kGrpDigitBits * k;
+        g.out = bufs[k & 1];
+        g.out_row = g.out + num_rows;
+        hipLaunchKernelGGL(k_grp_count, dim3(p.blocks), dim3(kGrpThreads), 0, s, g);
+        if (num_rows == 0) break;
+        hipLaunchKernelGGL(k_enc_colscan, dim3((kGrpBins + 63) / 64), dim3(64 * kColWaves), 0, s, cs);
+        hipLaunchKernelGGL(k_grp_scatter, dim3(p.blocks), dim3(kGrpThreads), 0, s, g);
+        g.in = g.out;
+        g.in_row = g.out_row;
+    }
     if (num_rows > 0)
-        hipLaunchKernelGGL(k_grp_bounds, dim3(static_cast<unsigned>((num_rows + 255) / 256)), dim3(256), 0, s, g);
+        hipLaunchKernelGGL(k_grp_bounds, dim3(static_cast<unsigned>((num_rows + 1023) / 1024)), dim3(256), 0, s, g);
     const unsigned kb = static_cast<unsigned>((num_ctx + 1023) / 1024);
-    if (num_ctx > 0) {
-        hipLaunchKernelGGL(k_grp_words, dim3(kb), dim3(1024), 0, s, g);
-        hipLaunchKernelGGL(k_grp_scan, dim3(1), dim3(1024), 0, s, g);
-        hipLaunchKernelGGL(k_grp_offsets, dim3(kb), dim3(1024), 0, s, g);
-    } else {
-        hipLaunchKernelGGL(k_grp_scan, dim3(1), dim3(1024), 0, s, g);  // row_off[0] = 0 below
+    hipLaunchKernelGGL(k_grp_words, dim3(kb), dim3(1024), 0, s, g);
+    if (kb > kGrpSumBlocks) hipLaunchKernelGGL(k_grp_scan, dim3(1), dim3(1024), 0, s, g);
+    hipLaunchKernelGGL(k_grp_offsets, dim3(kb), dim3(1024), 0, s, g, kb > kGrpSumBlocks, dropped_out);
+    if (num_rows > 0) {
+        const dim3 grid(static_cast<unsigned>((num_rows + 255) / 256));
+        if (row_stride_words <= 4)
+            hipLaunchKernelGGL(k_grp_copy<4>, grid, dim3(256), 0, s, g);
+        else
+            hipLaunchKernelGGL(k_grp_copy<8>, grid, dim3(256), 0, s, g);
     }
-    if (num_rows > 0 && num_ctx > 0)
-        hipLaunchKernelGGL(k_grp_copy,
-                           dim3(static_cast<unsigned>(std::min<int64_t>((num_rows + kGrpCopyRowsPerBlock - 1) / kGrpCopyRowsPerBlock, 1 << 20))),
-                           dim3(256), 0, s, g);
-    hipLaunchKernelGGL(k_grp_finish, dim3(1), dim3(64), 0, s, g, dropped_out, num_ctx == 0 ? 1 : 0);
     return hipGetLastError() == hipSuccess ? F2_OK : F2_EDEVICE;
 }
 
