@@ -3510,15 +3510,41 @@ __global__ __launch_bounds__(1024) void k_pool_scan(PoolArgs P) {
     if (tid == 0) P.blk[nblk] = carry > P.rows_cap ? -1 : carry;
 }
 
-// the pools' row offsets: their block's offset plus the scan within the block
-__global__ __launch_bounds__(256) void k_pool_offsets(PoolArgs P) {
-    __shared__ int64_t sWave[4];
+// the pools' row offsets: the blocks before their own, plus the scan within the block.  Up to
+// kPoolSumBlocks blocks (262,144 pools) each sums the others' words itself: at most four
+// loads per thread, against the 4.4 us of a launch of the scan; beyond, the sums would grow with
+// the square of the pools.
+constexpr int kPoolSumBlocks = 1024;
+__global__ __launch_bounds__(256) void k_pool_offsets(PoolArgs P, bool scanned) {
+    __shared__ int64_t sWave[4], sBase[4], sTotal[4];
     const int tid = threadIdx.x, lane = tid & 63;
     const int p = blockIdx.x * 256 + tid;
     const int nblk = (P.num_pools + 255) / 256;
     const bool live = p < P.num_pools;
     const int64_t v = live ? P.row_off[p] : 0;
-    const int64_t total = P.blk[nblk], base = P.blk[blockIdx.x];
+    int64_t total = 0, base = 0;
+    if (scanned) {
+        total = P.blk[nblk];
+        base = P.blk[blockIdx.x];
+    } else {
+        for (int b = tid; b < nblk; b += 256) {
+            const int64_t w = P.blk[b];
+            total += w;
+            base += b < static_cast<int>(blockIdx.x) ? w : 0;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            total += __shfl_down(total, o);
+            base += __shfl_down(base, o);
+        }
+        if (lane == 0) {
+            sTotal[tid >> 6] = total;
+            sBase[tid >> 6] = base;
+        }
+        __syncthreads();
+        total = sTotal[0] + sTotal[1] + sTotal[2] + sTotal[3];
+        base = sBase[0] + sBase[1] + sBase[2] + sBase[3];
+        if (total > P.rows_cap) total = -1;
+    }
     int64_t x = v;
     for (int o = 1; o < 64; o <<= 1) {
         const int64_t t = __shfl_up(x, o);
@@ -3536,18 +3562,28 @@ __global__ __launch_bounds__(256) void k_pool_offsets(PoolArgs P) {
     if (p == P.num_pools - 1) P.row_off[P.num_pools] = over ? 0 : total;
 }
 
+__device__ __forceinline__ int64_t readlane64(int64_t v, int i) {
+    return (static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int32_t>(v >> 32), i)) << 32) |
+           static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int32_t>(v), i));
+}
+
 // one wavefront per pool: the members' basis rows, in member order, each in its
-// stored order.  Up to 64 members at a time, one per lane (their ranks and
+// stored order.  Bound by the latency of a wavefront's loads: four words per lane in flight
+// took the copy of 80,000 pools of 4 from 83 to 56 us (one word at a time before).  Up to 64 members at a time, one per lane (their ranks and
 // offsets loaded together); every lane then copies words of the group's output,
 // the member of each word found among the lanes' prefixes.
 __global__ __launch_bounds__(256) void k_pool_copy(PoolArgs P) {
     const int lane = threadIdx.x & 63;
     const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (p >= P.num_pools) return;
-    if (P.pool_flags[p] & kPoolNoRows) return;
+    // (loaded together: a wavefront's life is its chain of loads)
+    const uint32_t fl = P.pool_flags[p];
     const int64_t lo = P.pool_off[p], hi = P.pool_off[p + 1];
-    const int64_t W = feat_words(P.pooled_n[p]) + F2_Y_WORDS;
+    const int n = P.pooled_n[p];
     int64_t dst = P.row_off[p];
+    asm volatile("" ::"v"(fl), "v"(lo), "v"(hi), "v"(n), "v"(dst));
+    if (fl & kPoolNoRows) return;
+    const int64_t W = feat_words(n) + F2_Y_WORDS;
     for (int64_t e0 = lo; e0 < hi; e0 += 64) {
         const int64_t e = e0 + lane;
         int64_t words = 0, src = 0;
@@ -3564,23 +3600,27 @@ __global__ __launch_bounds__(256) void k_pool_copy(PoolArgs P) {
         const int64_t pre = x - words;
         const int64_t total = __shfl(x, 63);
         const int nm = hi - e0 < 64 ? static_cast<int>(hi - e0) : 64;
-        for (int64_t k = lane; k < total; k += 64) {
-            // the member holding output word k: the last with prefix <= k (its prefix
-            // and source offset read from its lane by readlane, which, unlike a
-            // permute, also reads lanes this loop has left inactive)
-            int64_t ps = 0;
-            int64_t ss = (static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int32_t>(src >> 32), 0)) << 32) |
-                         (static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int32_t>(src), 0)));
+        // U words per lane at a time, their loads in flight together.  The member holding
+        // output word k is the last with prefix <= k (its prefix and source offset, as
+        // source - prefix, read from its lane by readlane, which, unlike a permute, also
+        // reads lanes that a loop has left inactive).
+        constexpr int U = 4;
+        const int64_t from = src - pre;
+        for (int64_t k0 = lane; k0 < total; k0 += U * 64) {
+            int64_t at[U];
+            uint64_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) at[u] = readlane64(from, 0);
             for (int i = 1; i < nm; ++i) {
-                const int64_t pi = (static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int32_t>(pre >> 32), i)) << 32) |
-                                   (static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int32_t>(pre), i)));
-                if (k >= pi) {
-                    ps = pi;
-                    ss = (static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int32_t>(src >> 32), i)) << 32) |
-                         (static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int32_t>(src), i)));
-                }
+                const int64_t pi = readlane64(pre, i), fi = readlane64(from, i);
+#pragma unroll
+                for (int u = 0; u < U; ++u) at[u] = k0 + u * 64 >= pi ? fi : at[u];
             }
-            P.rows[dst + k] = P.basis[ss + (k - ps)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = k0 + u * 64 < total ? P.basis[at[u] + k0 + u * 64] : 0ull;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k0 + u * 64 < total) P.rows[dst + k0 + u * 64] = v[u];
         }
         dst += total;
     }
@@ -4582,8 +4622,8 @@ int f2_pool_bases(const f2_model* members_model, const uint64_t* out_mask, const
     A.blk = reinterpret_cast<int64_t*>(ws + off_blk);
     int32_t* plan = reinterpret_cast<int32_t*>(ws + off_blk + align256(sizeof(int64_t) * (static_cast<size_t>(pb) + 1)));
     hipLaunchKernelGGL(k_pool_count, dim3(pb), dim3(256), 0, s, A);
-    hipLaunchKernelGGL(k_pool_scan, dim3(1), dim3(1024), 0, s, A);
-    hipLaunchKernelGGL(k_pool_offsets, dim3(pb), dim3(256), 0, s, A);
+    if (pb > kPoolSumBlocks) hipLaunchKernelGGL(k_pool_scan, dim3(1), dim3(1024), 0, s, A);
+    hipLaunchKernelGGL(k_pool_offsets, dim3(pb), dim3(256), 0, s, A, pb > kPoolSumBlocks);
     hipLaunchKernelGGL(k_pool_copy, dim3(static_cast<unsigned>((P + 3) / 4)), dim3(256), 0, s, A);
     launch_fit(fit_args(A.rows, A.rows_cap, A.row_off, pooled, plan), s);
     hipLaunchKernelGGL(k_pool_finish, dim3(pb), dim3(256), 0, s, A);
