@@ -185,39 +185,50 @@ __device__ __forceinline__ void write_bad_context(const FitArgs& a, const CtxDes
 // fit plan.  Contexts are validated (an invalid one gets rank 0 and its flag
 // here), assigned to the kernel of their class, and each class list is sorted
 // by an estimate of the elimination work, largest first:
-//   class 0: fw <= 3, at most kLongRows rows  -> register basis, one wavefront
-//   class 1: fw 4-8, at most kLongRows rows   -> LDS basis, kPivWaves wavefronts
-//   class 2: fw <= 8, more than kLongRows rows -> LDS basis, kPivWaves wavefronts
-//   class 3: fw > 8                           -> large-context kernel
+//   short: fw <= 3 and few rows, or rows x columns small   -> one wavefront
+//   long:  fw <= 3, rows x columns moderate                -> one wavefront beside many short
+//          ones, else kPivWaves wavefronts
+//   one:   fw = 4, likewise                                -> one wavefront with a larger basis
+//   group: fw <= 8, whatever is longer or wider            -> kPivWaves wavefronts
+//   large: fw > 8                                          -> large-context kernel
+// (which kernel takes the middle three depends on their numbers: piv_lists)
 // A class kernel with G workgroups deals its list out in stripes of G entries,
 // alternating direction from stripe to stripe, so that every workgroup gets a
 // similar share of the work and the longest contexts start first.  The sort is
 // a counting sort over (class, cost bucket) bins in two kernels (per-block
 // histograms; a scatter that scans them) with no device-wide atomics: on a chip
 // of eight dies those serialise far from the compute units.
-// Workspace (int32): [0, 5) list offsets per class, [kPivNext] the work counter
+// Workspace (int32): [0, kNumCls] list offsets per class, [kPivNext] the work counter
 // of the LDS-basis kernel, [kBarHead, kPlanHead) progress of the wide kernel's
 // workgroups, [kPlanHead, kPlanHead + C) the lists, then C sort keys and a
 // kPlanBins histogram per plan block.
 // ---------------------------------------------------------------------------
 constexpr int kRegMaxFW = 3;
 constexpr int kPivMaxFW = 8;
-constexpr int kLongRows = 256;  // contexts with more rows take the multi-wavefront kernel
-enum { kClsReg = 0, kClsPiv = 1, kClsPivLong = 2, kClsLarge = 3, kNumCls = 4 };
+constexpr int kLongRows = 4096;  // contexts with more rows are the work of several wavefronts
+// One wavefront's time grows with rows x columns (each block of 64 rows is reduced against up to
+// `columns` records).  Up to kShortRows rows or kShortWork it is the better path in any batch
+// (8,000 contexts of 300 rows, 41 columns: 114 us, by four wavefronts 190); up to kLongWork it
+// ends before a batch of short contexts does (80,000 contexts of a corpus, 353 us with the
+// line at 65,536, 213 us at 131,072 and 275 us at 262,144, where the longest end last).
+constexpr int kShortRows = 256, kShortWork = 16384, kLongWork = 131072;
+enum { kClsShort = 0, kClsLong = 1, kClsOne = 2, kClsGroup = 3, kClsLarge = 4, kNumCls = 5 };
 constexpr int kPivNext = 8;                 // plan word: next list position for the LDS-basis kernel
+constexpr int kRegNext = 9;                 // and for the shared tail of the one-wavefront kernel's list
 constexpr int kBarHead = 16;                // plan words kBarHead ..: progress of the wide kernel's workgroups (64 bits each)
 constexpr int kMaxMembers = 256;
 constexpr int kPlanHead = kBarHead + 2 * kMaxMembers;
-constexpr int kBuckets = 256;
-constexpr int kPlanBins = kNumCls * kBuckets;
+constexpr int kBuckets = 204;
+constexpr int kPlanBins = 1024;
 constexpr int kPlanThreads = 1024;  // one context per thread; one bin per thread in the scan
-static_assert(kPlanBins == kPlanThreads, "the scan gives one bin to each thread");
+static_assert(kNumCls * kBuckets <= kPlanBins && kPlanBins == kPlanThreads, "the scan gives one bin to each thread");
 
-__device__ __forceinline__ int fit_class(const CtxDesc& ds) {
+__device__ __forceinline__ int fit_class(const CtxDesc& ds, int long_rows = kLongRows) {
     const int fw = feat_words(ds.n);
     if (fw > kPivMaxFW) return kClsLarge;
-    if (ds.m > kLongRows) return kClsPivLong;
-    return fw <= kRegMaxFW ? kClsReg : kClsPiv;
+    const int64_t work = ds.m > kShortRows ? ds.m * (ds.n + 1) : 0;  // (m is at most 2^60)
+    if (ds.m > long_rows || fw > kRegMaxFW + 1 || work > kLongWork) return kClsGroup;
+    return fw == kRegMaxFW + 1 ? kClsOne : work > kShortWork ? kClsLong : kClsShort;
 }
 
 // log-scale bucket (4 per octave) of rows x min(rows, d) x row words
@@ -255,7 +266,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(FitArgs a) {
     sBin[tid] = 0;
     __syncthreads();
     if (blockIdx.x == 0 && tid < 2 * kMaxMembers) a.plan[kBarHead + tid] = 0;
-    if (blockIdx.x == 0 && tid == 0) a.plan[kPivNext] = 0;
+    if (blockIdx.x == 0 && tid < 2) a.plan[kPivNext + tid] = 0;
     const int64_t c = static_cast<int64_t>(blockIdx.x) * kPlanThreads + tid;
     if (c < a.num_ctx) {
         const CtxDesc ds = load_desc(a, c);
@@ -316,7 +327,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(FitArgs a, int bl
     for (int w = 0; w < (tid >> 6); ++w) base += sWave[w];
     const int excl = base + x - total;
     if (g0 == 0) {
-        if (tid % kBuckets == 0) P.cls_off[tid / kBuckets] = excl;
+        if (tid % kBuckets == 0 && tid < kNumCls * kBuckets) P.cls_off[tid / kBuckets] = excl;
         if (tid == kPlanThreads - 1) P.cls_off[kNumCls] = excl + total;
     }
     sBin[tid] = excl + before;
@@ -361,25 +372,19 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // ---------------------------------------------------------------------------
-// register-basis fit (fw <= 3): one wavefront per context.  Lane s of register
-// set k holds retained row 64k + s (fw + 2 words and its pivot); the rows of
-// the current block are one per lane.  An LDS mirror of the retained rows
-// feeds the block reduce with broadcast reads.
+// one-wavefront fit (fw <= 4): the rows pass through in blocks of 64, one row per
+// lane; the basis row of pivot p lies in LDS record p (fw feature words, 2 output
+// words), the basis fully reduced at the end of every block.  (Basis rows kept in
+// registers where they stood took every later pivot's step once per earlier block and held
+// contexts to 256 rows.)
 // ---------------------------------------------------------------------------
 template <int FW>
 __device__ __forceinline__ uint64_t word_at(const uint64_t (&f)[FW], int wi) {
-    // branch-free select of word wi (wi is usually wavefront-uniform)
-    if constexpr (FW == 1) {
-        return f[0];
-    } else if constexpr (FW == 2) {
-        const uint64_t s1 = 0ull - static_cast<uint64_t>(wi == 1);
-        return f[0] ^ ((f[0] ^ f[1]) & s1);
-    } else {
-        static_assert(FW == 3, "register basis holds at most 3 feature words");
-        const uint64_t s1 = 0ull - static_cast<uint64_t>(wi == 1);
-        const uint64_t s2 = 0ull - static_cast<uint64_t>(wi == 2);
-        return f[0] ^ ((f[0] ^ f[1]) & s1) ^ ((f[0] ^ f[2]) & s2);
-    }
+    // word wi (uniform), by masks: a chain of selects becomes an indexed load, and f an array in scratch
+    uint64_t v = f[0];
+#pragma unroll
+    for (int k = 1; k < FW; ++k) v ^= (f[0] ^ f[k]) & (0ull - static_cast<uint64_t>(wi == k));
+    return v;
 }
 
 // all-ones when bit b of w is set, else zero (32-bit: one mask serves both halves)
@@ -392,20 +397,29 @@ __device__ __forceinline__ uint32_t bit_mask(uint64_t w, int b) {
 // lane f holds bit f of every row (bit b of the result = bit f of row b).  Six
 // rounds that swap the off-diagonal blocks of size 32, 16, .., 1 with the partner
 // lane (lane xor j).
-template <int J, uint64_t M>
-__device__ __forceinline__ uint64_t transpose_round(uint64_t v, int lane) {
-    const uint32_t plo = static_cast<uint32_t>(__shfl_xor(static_cast<int>(static_cast<uint32_t>(v)), J));
-    const uint32_t phi = static_cast<uint32_t>(__shfl_xor(static_cast<int>(static_cast<uint32_t>(v >> 32)), J));
-    const uint64_t p = (static_cast<uint64_t>(phi) << 32) | plo;
-    return (lane & J) ? ((v & ~M) | ((p & ~M) >> J)) : ((v & M) | ((p & M) << J));
+// (All in registers: a swap of the halves between lanes 32 apart, then per half a row
+// swap, DPP moves, and byte permutes or a rotate and a bit select.  About 35 VALU
+// instructions; rounds of ds_bpermute took 70 and 12 LDS permutes.)
+__device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);  // [0] even rows' values, [1] odd rows'
+    x = __builtin_amdgcn_perm(r[1], r[0], (lane & 16) ? 0x07060302u : 0x05040100u);
+    uint32_t p = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), 0x128, 0xf, 0xf, true));  // lane ^ 8
+    x = __builtin_amdgcn_perm(p, x, (lane & 8) ? 0x03070105u : 0x06020400u);
+    p = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), 0x141, 0xf, 0xf, true));           // lane ^ 7
+    p = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(p), 0x1b, 0xf, 0xf, true));            // and ^ 3
+    const auto mix = [](uint32_t x, uint32_t p, uint32_t rot, uint32_t m) {  // bits m from p rotated right
+        p = __builtin_amdgcn_alignbit(p, p, rot);
+        return (p & m) | (x & ~m);
+    };
+    x = mix(x, p, (lane & 4) ? 4u : 28u, (lane & 4) ? 0x0f0f0f0fu : 0xf0f0f0f0u);
+    p = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), 0x4e, 0xf, 0xf, true));            // lane ^ 2
+    x = mix(x, p, (lane & 2) ? 2u : 30u, (lane & 2) ? 0x33333333u : 0xccccccccu);
+    p = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), 0xb1, 0xf, 0xf, true));            // lane ^ 1
+    return mix(x, p, (lane & 1) ? 1u : 31u, (lane & 1) ? 0x55555555u : 0xaaaaaaaau);
 }
 __device__ __forceinline__ uint64_t transpose64(uint64_t v, int lane) {
-    v = transpose_round<32, 0x00000000ffffffffull>(v, lane);
-    v = transpose_round<16, 0x0000ffff0000ffffull>(v, lane);
-    v = transpose_round<8, 0x00ff00ff00ff00ffull>(v, lane);
-    v = transpose_round<4, 0x0f0f0f0f0f0f0f0full>(v, lane);
-    v = transpose_round<2, 0x3333333333333333ull>(v, lane);
-    return transpose_round<1, 0x5555555555555555ull>(v, lane);
+    const auto r = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(v), static_cast<uint32_t>(v >> 32), false, false);
+    return (static_cast<uint64_t>(transpose32(r[1], lane)) << 32) | transpose32(r[0], lane);
 }
 
 // f ^ (m & d) with m a 32-bit all-ones/zero mask: one v_bitop3 per half
@@ -425,284 +439,374 @@ __device__ __forceinline__ uint64_t xor3(uint64_t a, uint64_t b, uint64_t c) {
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-constexpr int kRecWords = 6;  // LDS record: fw feature words, 2 output words, pivot (<= 6 words)
+struct RegRows {  // row words of a block in flight, per lane
+    uint64_t w0, w1, w2, w3, w4, w5;  // (named: an array handed through calls ends in scratch memory)
+    __device__ __forceinline__ uint64_t word(int w) const {
+        return w == 0 ? w0 : w == 1 ? w1 : w == 2 ? w2 : w == 3 ? w3 : w == 4 ? w4 : w5;
+    }
+};
+constexpr int reg_words(int fw) { return 64 * fw * (fw + F2_Y_WORDS); }  // LDS words of a wavefront's basis
+constexpr int kRegRec = reg_words(kRegMaxFW);
 
-template <int FW>
-__device__ __forceinline__ void fit_ctx_reg(const FitArgs& a, const CtxDesc& ds, uint64_t* sRec, int16_t* sPos) {
-    constexpr int W = FW + F2_Y_WORDS;
-    constexpr int NB = kLongRows / 64;  // blocks of a context in this class
+// 8-byte aligned words, moved 16 bytes at a time at a 32-bit offset from a uniform base
+typedef unsigned long long u64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
+template <int W>
+__device__ __forceinline__ void load_words(const uint64_t* base, uint32_t bytes, uint64_t (&v)[W]) {
+    const char* p = reinterpret_cast<const char*>(base) + bytes;
+#pragma unroll
+    for (int w = 0; w + 1 < W; w += 2) {
+        const u64x2_a8 q = *reinterpret_cast<const u64x2_a8*>(p + 8 * w);
+        v[w] = q.x;
+        v[w + 1] = q.y;
+    }
+    if constexpr (W & 1) v[W - 1] = *reinterpret_cast<const uint64_t*>(p + 8 * (W - 1));
+}
+template <int W>
+__device__ __forceinline__ void store_words(uint64_t* base, uint32_t bytes, const uint64_t (&v)[W]) {
+    char* p = reinterpret_cast<char*>(base) + bytes;
+#pragma unroll
+    for (int w = 0; w + 1 < W; w += 2) *reinterpret_cast<u64x2_a8*>(p + 8 * w) = u64x2_a8{v[w], v[w + 1]};
+    if constexpr (W & 1) *reinterpret_cast<uint64_t*>(p + 8 * (W - 1)) = v[W - 1];
+}
+
+// the 64 rows from i0 on, one per lane (zero past row m <= kLongRows): W words each
+template <int W>
+__device__ __forceinline__ RegRows load_rows(const uint64_t* R, int m, int i0) {
+    const int i = i0 + static_cast<int>(threadIdx.x & 63);
+    RegRows r{0, 0, 0, 0, 0, 0};
+    if (i < m) {
+        uint64_t v[W];
+        load_words<W>(R, static_cast<uint32_t>(i) * (8 * W), v);
+        r.w0 = v[0];
+        r.w1 = v[1];
+        r.w2 = v[2];
+        if constexpr (W > 3) r.w3 = v[3];
+        if constexpr (W > 4) r.w4 = v[4];
+        if constexpr (W > 5) r.w5 = v[5];
+    }
+    return r;
+}
+
+// feature words of a context: of its only word just the low half where NARROW (at most 31
+// inputs); every high half is then a known zero and takes no instruction
+template <bool NARROW>
+__device__ __forceinline__ uint64_t feat_xor_and(uint64_t f, uint32_t m, uint64_t d) {
+    if constexpr (NARROW)
+        return static_cast<uint32_t>(__builtin_amdgcn_bitop3_b32(static_cast<int>(static_cast<uint32_t>(f)), static_cast<int>(m),
+                                                                 static_cast<int>(static_cast<uint32_t>(d)), 0x78));
+    else
+        return xor_and(f, m, d);
+}
+template <bool NARROW>
+__device__ __forceinline__ uint64_t feat_readlane(uint64_t f, int j) {
+    if constexpr (NARROW) return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(f), j));
+    else return readlane64(f, j);
+}
+template <bool NARROW>
+__device__ __forceinline__ uint32_t feat_mask(uint64_t f, int b) {
+    if constexpr (NARROW) return static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(static_cast<uint32_t>(f)), b, 1));
+    else return bit_mask(f, b);
+}
+
+// elimination in stream order of a block of 64 rows, one per lane (those of `pending`): the
+// earliest row with a nonzero feature residual becomes a basis row where it stands, and its
+// pivot is cleared from every other row, so that the new rows end fully reduced among
+// themselves; the others end with zero features.  newp: the new pivots.  Bound by a
+// pivot's chain (ballot, row to scalar registers, first set bit, mask, additions, ballot).
+template <int FW, bool NARROW = false>
+__device__ __forceinline__ void eliminate_block(uint64_t (&f)[FW], uint64_t& y0, uint64_t& y1, uint64_t pending, int n,
+                                                const uint64_t (&xm)[FW], uint64_t (&newp)[FW]) {
     const int lane = threadIdx.x & 63;
-    const int c = ds.c, n = ds.n, d = n + 1;
-    const int64_t m = ds.m;  // at most kLongRows
-    const uint64_t* R = a.rows + ds.row0;
+#pragma unroll
+    for (int w = 0; w < FW; ++w) newp[w] = 0;
+    const auto nonzero = [&]() {
+        uint64_t any = f[0];
+#pragma unroll
+        for (int w = 1; w < FW; ++w) any |= f[w];
+        return __ballot(any != 0) & pending;
+    };
+    uint64_t nz = nonzero();
+    while (nz) {
+        const int j = ffs64(nz);
+        uint64_t F[FW];
+#pragma unroll
+        for (int w = 0; w < FW; ++w) F[w] = feat_readlane<NARROW>(f[w], j);
+        const uint64_t Y0 = readlane64(y0, j), Y1 = readlane64(y1, j);
+        // pivot: highest-priority set feature bit (x_{n-1} .. x_0, else the
+        // constant: the row is nonzero)
+        int pw = FW == 1 ? 0 : n >> 6, pb = n & 63;
+#pragma unroll
+        for (int w = 0; w < FW; ++w) {
+            const uint64_t v = F[w] & xm[w];
+            // (undefined for zero, where it is not taken)
+            const int b = NARROW ? 31 ^ __builtin_clz(static_cast<uint32_t>(v)) : 63 ^ __builtin_clzll(v);
+            pb = v ? b : pb;
+            if (FW > 1) pw = v ? w : pw;
+        }
+        const uint32_t mb = feat_mask<NARROW>(word_at<FW>(f, pw), pb);
+        const uint32_t mm = lane == j ? 0u : mb;
+#pragma unroll
+        for (int w = 0; w < FW; ++w) f[w] = feat_xor_and<NARROW>(f[w], mm, F[w]);
+        y0 = xor_and(y0, mm, Y0);
+        y1 = xor_and(y1, mm, Y1);
+#pragma unroll
+        for (int w = 0; w < FW; ++w) newp[w] |= FW == 1 || w == pw ? 1ull << pb : 0ull;
+        pending &= ~(1ull << j);
+        nz = nonzero();
+    }
+}
+
+// first set bit of a row (in pivot order), where it has one: a new basis row's pivot
+template <int FW>
+__device__ __forceinline__ int row_pivot(const uint64_t (&f)[FW], const uint64_t (&xm)[FW], int n) {
+    int p = n;
+#pragma unroll
+    for (int w = 0; w < FW; ++w) {
+        const uint64_t v = f[w] & xm[w];
+        p = v ? 64 * w + msb64(v) : p;
+    }
+    return p;
+}
+
+// where a wavefront's lanes store a context's scalars, a dword each: rank, n_contra, the
+// halves of first_contra, ctx_flags (one store of five lanes instead of four with an address each)
+struct RegScalars {
+    char* at;
+    uint32_t step;  // bytes per context
+};
+__device__ __forceinline__ RegScalars reg_scalars(const FitArgs& a) {
+    const int lane = threadIdx.x & 63;
+    RegScalars r;
+    r.at = reinterpret_cast<char*>(lane == 0   ? a.rank
+                                   : lane == 1 ? a.n_contra
+                                   : lane < 4  ? reinterpret_cast<int32_t*>(a.first_contra) + (lane - 2)
+                                               : reinterpret_cast<int32_t*>(a.ctx_flags));
+    r.step = lane == 2 || lane == 3 ? 8 : 4;
+    return r;
+}
+
+// One context: c of width n with m <= kLongRows rows from R on.  raw holds its first block's rows
+// on entry; `next(raw)` is called once, when the last block's rows have been taken, and fills raw
+// with the rows to be fitted after it; `next.offsets` gives the context's output offsets.
+template <int FW, bool NARROW = false, typename Next>
+__device__ __forceinline__ void fit_ctx_reg(const FitArgs& a, const RegScalars& sc, int c, int n, int m, const uint64_t* R,
+                                            uint64_t* sRec, RegRows& raw, Next& next) {
+    constexpr int W = FW + F2_Y_WORDS;
+    const int lane = threadIdx.x & 63;
+    const int d = n + 1;
     const uint64_t tmask = top_mask(n, FW);
     const int cw = n >> 6;
     const uint64_t cbit = 1ull << (n & 63);
-    const uint64_t lane_lt = (1ull << lane) - 1;
-
-    // block b's rows in register set b, one per lane; every row is loaded up front
-    uint64_t f[NB][FW], y0[NB], y1[NB];
-    int bp[NB];         // pivot of this lane's row, where the row is a basis row
-    uint64_t piv[NB];   // lanes of set b that hold basis rows (uniform)
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int64_t i = 64 * b + lane;
-        const bool valid = i < m;
-#pragma unroll
-        for (int w = 0; w < FW; ++w) f[b][w] = valid ? R[i * W + w] : 0ull;
-        f[b][FW - 1] &= tmask;
-        y0[b] = valid ? R[i * W + FW] : 0ull;
-        y1[b] = valid ? R[i * W + FW + 1] : 0ull;
-        bp[b] = 0;
-        piv[b] = 0;
-    }
     uint64_t xm[FW];  // the x columns of each feature word (the constant column cleared)
+    uint64_t pm[FW];  // pivots of the basis
 #pragma unroll
-    for (int w = 0; w < FW; ++w) xm[w] = (w == cw) ? ~cbit : ~0ull;
-    int rank = 0, ncontra = 0;
-    int64_t first = -1;
+    for (int w = 0; w < FW; ++w) {
+        xm[w] = (w == cw) ? ~cbit : ~0ull;
+        pm[w] = 0;
+    }
+    int ncontra = 0, first = -1;
 
-    // dense copy of the basis rows (record = fw words, 2 output words, pivot) for
-    // the broadcast reads of the block reduce; sPos[p] = record of pivot p
-    auto store_mirror = [&](int nsets, bool positions) {
-        int base = 0;
+    for (int b0 = 0;; b0 += 64) {
+        uint64_t f[FW], y0, y1;
 #pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            if (k < nsets) {
-                if ((piv[k] >> lane) & 1ull) {
-                    const int s = base + __popcll(piv[k] & lane_lt);
-                    uint64_t* rec = sRec + s * kRecWords;
+        for (int w = 0; w < FW; ++w) f[w] = raw.word(w);
+        f[FW - 1] &= tmask;
+        if constexpr (NARROW) f[0] = static_cast<uint32_t>(f[0]);
+        y0 = raw.word(FW);
+        y1 = raw.word(FW + 1);
+        const bool last = b0 + 64 >= m;
+        if (last) next(raw);
+        else raw = load_rows<W>(R, m, b0 + 64);
+        // (1) reduce against the basis: it is fully reduced, so the row's own (unreduced)
+        //     bits at the pivot columns select the records to add; the selection masks do
+        //     not depend on one another
+        uint64_t f0[FW];
 #pragma unroll
-                    for (int w = 0; w < FW; ++w) rec[w] = f[k][w];
-                    rec[FW] = y0[k];
-                    rec[FW + 1] = y1[k];
-                    rec[W] = static_cast<uint64_t>(bp[k]);
-                    if (positions) sPos[bp[k]] = static_cast<int16_t>(s);
-                }
-                base += __popcll(piv[k]);
+        for (int w = 0; w < FW; ++w) f0[w] = f[w];
+#pragma unroll
+        for (int h = 0; h < (NARROW ? 1 : 2 * FW); ++h) {
+            uint32_t ps = static_cast<uint32_t>(pm[h / 2] >> (32 * (h & 1)));
+            const int own = static_cast<int>(static_cast<uint32_t>(f0[h / 2] >> (32 * (h & 1))));
+            const uint64_t* base = sRec + 32 * h * W;
+            auto add = [&](int b, const uint64_t (&rv)[W]) {
+                const uint32_t mm = static_cast<uint32_t>(__builtin_amdgcn_sbfe(own, b, 1));
+#pragma unroll
+                for (int w = 0; w < FW; ++w) f[w] = feat_xor_and<NARROW>(f[w], mm, rv[w]);
+                y0 = xor_and(y0, mm, rv[FW]);
+                y1 = xor_and(y1, mm, rv[FW + 1]);
+            };
+            while (ps & (ps - 1)) {  // two records at a time
+                const int b = __ffs(ps) - 1, b2 = __ffs(ps & (ps - 1)) - 1;
+                ps &= ps - 1;
+                ps &= ps - 1;
+                uint64_t rv[W], rw[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) rv[w] = base[b * W + w];
+#pragma unroll
+                for (int w = 0; w < W; ++w) rw[w] = base[b2 * W + w];
+                add(b, rv);
+                add(b2, rw);
             }
-        }
-    };
-
+            if (ps) {
+                const int b = __ffs(ps) - 1;
+                uint64_t rv[W];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        if (64 * b >= m) break;
-        const bool valid = 64 * b + lane < m;
-        // (1) reduce against the basis of the earlier blocks: it is fully reduced,
-        //     so the row's own (unreduced) bits at the pivot columns select the
-        //     records to add; the selection masks do not depend on one another
-        if (rank > 0) {
-            uint64_t f0[FW];
-#pragma unroll
-            for (int w = 0; w < FW; ++w) f0[w] = f[b][w];
-            constexpr int U = FW >= 3 ? 1 : FW == 2 ? 2 : 4;  // records read ahead (register budget)
-            int s = 0;
-            for (; s + U <= rank; s += U) {
-                uint64_t rv[U][W];
-                int pv[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const uint64_t* rec = sRec + (s + u) * kRecWords;
-#pragma unroll
-                    for (int w = 0; w < W; ++w) rv[u][w] = rec[w];
-                    pv[u] = static_cast<int>(rec[W]);
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const uint32_t mm = bit_mask(word_at<FW>(f0, pv[u] >> 6), pv[u] & 63);
-#pragma unroll
-                    for (int w = 0; w < FW; ++w) f[b][w] = xor_and(f[b][w], mm, rv[u][w]);
-                    y0[b] = xor_and(y0[b], mm, rv[u][FW]);
-                    y1[b] = xor_and(y1[b], mm, rv[u][FW + 1]);
-                }
-            }
-            for (; s < rank; ++s) {
-                const uint64_t* rec = sRec + s * kRecWords;
-                const int p = static_cast<int>(rec[W]);
-                const uint32_t mm = bit_mask(word_at<FW>(f0, p >> 6), p & 63);
-#pragma unroll
-                for (int w = 0; w < FW; ++w) f[b][w] = xor_and(f[b][w], mm, rec[w]);
-                y0[b] = xor_and(y0[b], mm, rec[FW]);
-                y1[b] = xor_and(y1[b], mm, rec[FW + 1]);
+                for (int w = 0; w < W; ++w) rv[w] = base[b * W + w];
+                add(b, rv);
             }
         }
 
-        // (2) elimination in stream order: the earliest row with a nonzero
-        //     feature residual becomes a basis row where it stands; its pivot is
-        //     cleared from the later rows of the block and from the basis rows
-        //     of this and the earlier blocks (the basis stays fully reduced)
-        uint64_t pending = __ballot(valid);
-        for (;;) {
-            uint64_t any = f[b][0];
+        // (2) elimination in stream order: the earliest row with a nonzero feature
+        //     residual becomes a basis row where it stands, and its pivot is cleared
+        //     from every other row of the block, so that the new rows end fully reduced
+        //     among themselves (and hold no older pivot)
+        const uint64_t valid = m - b0 >= 64 ? ~0ull : m > b0 ? (1ull << (m - b0)) - 1 : 0ull;
+        uint64_t newp[FW];
+        eliminate_block<FW, NARROW>(f, y0, y1, valid, n, xm, newp);
+        // (3) the rows that are left have zero features: redundant, or contradictory
+        //     when their output is nonzero (Eq. 8)
+        uint64_t any = f[0], grown = newp[0], old = pm[0];
 #pragma unroll
-            for (int w = 1; w < FW; ++w) any |= f[b][w];
-            const uint64_t nz = __ballot(any != 0) & pending;
-            if (!nz) break;
-            const int j = ffs64(nz);
-            uint64_t F[FW];
-#pragma unroll
-            for (int w = 0; w < FW; ++w) F[w] = readlane64(f[b][w], j);
-            const uint64_t Y0 = readlane64(y0[b], j), Y1 = readlane64(y1[b], j);
-            // pivot: highest-priority set feature bit (x_{n-1} .. x_0, else the
-            // constant: the row is nonzero)
-            int p = n;
-#pragma unroll
-            for (int w = 0; w < FW; ++w) {
-                const uint64_t v = F[w] & xm[w];
-                p = v ? 64 * w + msb64(v) : p;
-            }
-            const int pw = p >> 6, pb = p & 63;
-            {  // this block: every row holding bit p except the new basis row itself
-                const uint32_t mm = bit_mask(word_at<FW>(f[b], pw), pb) & (lane == j ? 0u : ~0u);
-#pragma unroll
-                for (int w = 0; w < FW; ++w) f[b][w] = xor_and(f[b][w], mm, F[w]);
-                y0[b] = xor_and(y0[b], mm, Y0);
-                y1[b] = xor_and(y1[b], mm, Y1);
-            }
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {  // earlier blocks: only their basis rows are nonzero
-                if (k < b && piv[k]) {
-                    const uint32_t mm = bit_mask(word_at<FW>(f[k], pw), pb);
-#pragma unroll
-                    for (int w = 0; w < FW; ++w) f[k][w] = xor_and(f[k][w], mm, F[w]);
-                    y0[k] = xor_and(y0[k], mm, Y0);
-                    y1[k] = xor_and(y1[k], mm, Y1);
-                }
-            }
-            if (lane == j) bp[b] = p;
-            piv[b] |= 1ull << j;
-            pending &= ~(1ull << j);
-            ++rank;
+        for (int w = 1; w < FW; ++w) {
+            any |= f[w];
+            grown |= newp[w];
+            old |= pm[w];
         }
-        // (3) every other row of the block now has zero features: redundant, or
-        //     contradictory when its output is nonzero (Eq. 8)
-        const uint64_t cm = __ballot(valid && !((piv[b] >> lane) & 1ull) && (y0[b] | y1[b]) != 0);
+        const uint64_t cm = __ballot(any == 0 && (y0 | y1) != 0) & valid;
         if (cm) {
-            if (ncontra == 0) first = 64 * b + ffs64(cm);
+            if (ncontra == 0) first = b0 + ffs64(cm);
             ncontra += __popcll(cm);
         }
-        if (piv[b] && 64 * (b + 1) < m) {
-            store_mirror(b + 1, false);
+        // (4) the new rows join the basis; the older rows lose the new pivots (whose rows hold
+        //     no other new pivot: an older row's bits, read once, select what to add)
+        if (grown) {
+            if (any != 0) {
+                uint64_t* rec = sRec + row_pivot<FW>(f, xm, n) * W;
+#pragma unroll
+                for (int w = 0; w < FW; ++w) rec[w] = f[w];
+                rec[FW] = y0;
+                rec[FW + 1] = y1;
+            }
             wave_sync();
+            if (old) {
+#pragma unroll
+                for (int k = 0; k < FW; ++k) {
+                    if (!pm[k]) continue;
+                    uint64_t* rec = sRec + (64 * k + lane) * W;
+                    uint64_t v[W], v0[FW];
+#pragma unroll
+                    for (int w = 0; w < W; ++w) v[w] = rec[w];
+#pragma unroll
+                    for (int w = 0; w < FW; ++w) v0[w] = v[w];
+#pragma unroll
+                    for (int w = 0; w < FW; ++w) {
+                        uint64_t q = newp[w];
+                        while (q) {
+                            const int b = ffs64(q);
+                            q &= q - 1;
+                            const uint64_t* nr = sRec + (64 * w + b) * W;
+                            const uint32_t mm = feat_mask<NARROW>(v0[w], b);
+#pragma unroll
+                            for (int u = 0; u < W; ++u) v[u] = u < FW ? feat_xor_and<NARROW>(v[u], mm, nr[u]) : xor_and(v[u], mm, nr[u]);
+                        }
+                    }
+                    if ((pm[k] >> lane) & 1ull) {
+#pragma unroll
+                        for (int w = 0; w < W; ++w) rec[w] = v[w];
+                    }
+                }
+                wave_sync();
+            }
+#pragma unroll
+            for (int w = 0; w < FW; ++w) pm[w] |= newp[w];
         }
+        if (last) break;
     }
 
-    // outputs: basis rows and pivots in descending priority, canonical map, scalars
-    for (int j = lane; j < d; j += 64) sPos[j] = -1;
-    wave_sync();
-    store_mirror(NB, true);
-    wave_sync();
-    uint64_t pm[FW];  // pivot columns (uniform): the positions that received a record
+    // what is to be fitted next has arrived before the outputs are stored: a load is waited
+    // for together with the stores issued after it
+    next.arrived(raw);
+
+    // outputs: basis rows and pivots in descending priority, canonical map, parity-check
+    // rows, scalars
+    int rank = 0;
 #pragma unroll
-    for (int w = 0; w < FW; ++w) pm[w] = __ballot(64 * w + lane < d && sPos[64 * w + lane] >= 0);
-    const int64_t bo = ds.bo, po = ds.po, mo = ds.mo;
+    for (int w = 0; w < FW; ++w) rank += __popcll(pm[w]);
+    int64_t bo, po, mo;
+    next.offsets(bo, po, mo);
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        if ((piv[k] >> lane) & 1ull) {
-            const int p = bp[k];
+    for (int k = 0; k < FW; ++k) {
+        const int p = 64 * k + lane;
+        const bool present = (pm[k] >> lane) & 1ull;
+        uint64_t v[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) v[w] = present ? sRec[p * W + w] : 0ull;
+        if (p < d) {
+            const uint64_t y[2] = {v[FW], v[FW + 1]};
+            store_words<2>(a.maps + mo, static_cast<uint32_t>(p) * 16, y);
+        }
+        if (present) {
             int kout = rank - 1;
             if (p != n) {  // pivots of higher priority: x bits above p
-                kout = 0;
+                kout = __popcll((pm[k] & xm[k]) >> lane) - 1;
 #pragma unroll
-                for (int w = 0; w < FW; ++w) {
-                    uint64_t v = pm[w];
-                    if (w == cw) v &= ~cbit;
-                    if (w < (p >> 6)) v = 0;
-                    if (w == (p >> 6)) v &= ((p & 63) == 63) ? 0ull : (~0ull << ((p & 63) + 1));
-                    kout += __popcll(v);
-                }
+                for (int w = k + 1; w < FW; ++w) kout += __popcll(pm[w] & xm[w]);
             }
-            uint64_t* out = a.basis + bo + static_cast<int64_t>(kout) * W;
-#pragma unroll
-            for (int w = 0; w < FW; ++w) out[w] = f[k][w];
-            out[FW] = y0[k];
-            out[FW + 1] = y1[k];
-            a.pivots[po + kout] = p;
+            store_words<W>(a.basis + bo, static_cast<uint32_t>(kout) * (8 * W), v);
+            (a.pivots + po)[static_cast<uint32_t>(kout)] = p;
         }
     }
-    for (int j = lane; j < d; j += 64) {
-        const int sl = sPos[j];
-        a.maps[mo + 2 * j] = sl >= 0 ? sRec[sl * kRecWords + FW] : 0ull;
-        a.maps[mo + 2 * j + 1] = sl >= 0 ? sRec[sl * kRecWords + FW + 1] : 0ull;
-    }
-    // parity-check rows of the free columns (sRec holds the final rows, sPos their
-    // records).  Word v of the row of free column fc = 64 w + f holds, at bit b, bit fc
-    // of the basis row of pivot 64 v + b: with lane b holding word w of that basis row
-    // (zero for a free column), a bit-matrix transpose across the wavefront gives lane
-    // f exactly that word; the free lanes then store their rows in ascending order.
+    // Word v of the parity-check row of free column 64 w + f holds, at bit b, bit f of word w
+    // of the basis row of pivot 64 v + b: with lane b holding word w of that basis row (zero
+    // for a free column), a bit-matrix transpose across the wavefront gives lane f exactly
+    // that word; the free lanes then store their rows in ascending order.
     uint64_t* H = a.tables + bo;
     if (has_parity_rows(d, rank)) {
-        // (no arrays indexed by the loop counters: where these loops stay rolled,
-        // such an array would live in scratch memory)
         int base = 0;  // free columns in the words before w
 #pragma unroll
         for (int w = 0; w < FW; ++w) {
-            const int sw = (64 * w + lane < d) ? sPos[64 * w + lane] : -1;
-            const uint64_t fr = ~__ballot(sw >= 0) & (w == FW - 1 ? tmask : ~0ull);
+            const uint64_t fr = ~pm[w] & (w == FW - 1 ? tmask : ~0ull);
             if (!fr) continue;  // no free column in this word (full rank: none at all)
             const bool mine = (fr >> lane) & 1ull;
-            const int64_t i = base + __popcll(fr & lane_lt);
+            const uint32_t i = base + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(fr >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(fr), 0));
 #pragma unroll
             for (int v = 0; v < FW; ++v) {
-                const int sv = (64 * v + lane < d) ? sPos[64 * v + lane] : -1;
-                const uint64_t col = transpose64(sv >= 0 ? sRec[sv * kRecWords + w] : 0ull, lane);
+                const bool piv = (pm[v] >> lane) & 1ull;
+                const uint64_t col = transpose64(piv ? sRec[(64 * v + lane) * W + w] : 0ull, lane);
                 if (mine) H[i * FW + v] = col | (v == w ? (1ull << lane) : 0ull);
             }
             base += __popcll(fr);
         }
     }
-    if (lane == 0) {
-        a.rank[c] = rank;
-        a.n_contra[c] = ncontra;
-        a.first_contra[c] = first;
-        a.ctx_flags[c] = ncontra ? F2_CTX_CONTRADICTION : 0u;
+    if (lane < 5) {
+        const int v = lane == 0   ? rank
+                      : lane == 1 ? ncontra
+                      : lane == 2 ? first
+                      : lane == 3 ? first >> 31
+                                  : static_cast<int>(ncontra ? F2_CTX_CONTRADICTION : 0u);
+        *reinterpret_cast<int32_t*>(sc.at + static_cast<uint64_t>(static_cast<uint32_t>(c)) * sc.step) = v;
     }
     wave_sync();
 }
 
-// One workgroup of kRegWaves wavefronts per compute unit, each wavefront fitting
-// its own contexts in its own LDS region.  The workgroup's share of the class
-// list (dealt in snake order, so shares carry similar work) starts with one
-// context per wavefront in snake order over the four SIMDs (wavefront w runs on
-// SIMD w mod 4), largest first; then wavefronts take the next context of the
-// share as they finish, through a counter in LDS.
-constexpr int kRegWaves = 16;
-
-__global__ __launch_bounds__(64 * kRegWaves) void k_fit_reg(FitArgs a) {
-    __shared__ __align__(16) uint64_t sRec[kRegWaves][64 * kRegMaxFW * kRecWords];
-    __shared__ int16_t sPos[kRegWaves][64 * kRegMaxFW];
-    __shared__ int sNext;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    if (tid == 0) sNext = kRegWaves;
-    __syncthreads();
-    const int r = wave >> 2, simd = wave & 3;
-    // the share's list positions (the class bounds read once)
-    const int lo = a.plan[kClsReg], cnt = a.plan[kClsReg + 1] - lo;
-    const int G = static_cast<int>(gridDim.x), g = static_cast<int>(blockIdx.x);
-    auto ctx_at = [&](int i) {  // context at position i of the share, or num_ctx past its end
-        const int64_t e = static_cast<int64_t>(i) * G + ((i & 1) ? G - 1 - g : g);
-        return __builtin_amdgcn_readfirstlane(e < cnt ? a.plan[kPlanHead + lo + static_cast<int>(e)] : a.num_ctx);
-    };
-    auto next_pos = [&]() {
-        int nk = 0;
-        if (lane == 0) nk = atomicAdd(&sNext, 1);
-        return __builtin_amdgcn_readfirstlane(nk);
-    };
-    // a two-deep pipeline: while a context is fitted, the next one's descriptor
-    // and the one after's id are already loading
-    CtxDesc ds = readlane_desc(load_desc(a, ctx_at(4 * r + ((r & 1) ? 3 - simd : simd))), 0);
-    int c1 = ctx_at(next_pos());
-    while (ds.c >= 0) {
-        const CtxDesc dn = readlane_desc(load_desc(a, c1), 0);
-        const int c2 = ctx_at(next_pos());
-        switch (feat_words(ds.n)) {
-            case 1: fit_ctx_reg<1>(a, ds, sRec[wave], sPos[wave]); break;
-            case 2: fit_ctx_reg<2>(a, ds, sRec[wave], sPos[wave]); break;
-            default: fit_ctx_reg<3>(a, ds, sRec[wave], sPos[wave]); break;
+// a context with none after it
+template <int FW>
+__device__ __forceinline__ void fit_ctx_alone(const FitArgs& a, const CtxDesc& ds, uint64_t* sRec) {
+    struct {
+        const CtxDesc& ds;
+        __device__ __forceinline__ void operator()(RegRows&) {}
+        __device__ __forceinline__ void arrived(RegRows&) {}
+        __device__ __forceinline__ void offsets(int64_t& bo, int64_t& po, int64_t& mo) {
+            bo = ds.bo;
+            po = ds.po;
+            mo = ds.mo;
         }
-        ds = dn;
-        c1 = c2;
-    }
+    } none{ds};
+    const uint64_t* R = a.rows + ds.row0;
+    const int m = static_cast<int>(ds.m);
+    RegRows raw = load_rows<FW + F2_Y_WORDS>(R, m, 0);
+    fit_ctx_reg<FW>(a, reg_scalars(a), ds.c, ds.n, m, R, sRec, raw, none);
 }
 
 // ---------------------------------------------------------------------------
@@ -723,14 +827,6 @@ constexpr int kPivCap = 64 * kPivMaxFW;          // d <= 512
 constexpr int kPivWaves = 4;
 constexpr int kPivThreads = 64 * kPivWaves;
 
-template <int FW>
-__device__ __forceinline__ uint64_t sel_word(const uint64_t (&f)[FW], int wi) {
-    uint64_t v = f[0];
-#pragma unroll
-    for (int k = 1; k < FW; ++k) v ^= (f[k] ^ f[0]) & (0ull - static_cast<uint64_t>(wi == k));
-    return v;
-}
-
 // Four-Russians tables for contexts of up to 4 feature words (d <= 256): their
 // records use rec[0, 256), and the tables take the rest of rec plus tabx (the
 // two are adjacent): table g holds the 16 XOR combinations of the retained rows
@@ -743,7 +839,6 @@ constexpr int kPivTabMinRows = 512;  // tables are built only with two rounds of
 struct alignas(16) PivShared {  // 16-byte aligned: the tables are read 16 bytes at a time
     uint64_t rec[kPivCap][kPivRec];
     uint64_t tabx[kPivTabExtra];  // continues rec (tables)
-    int ntab;                     // valid tables (positions [0, 4 ntab)), 0: none
     uint64_t pm[kPivMaxFW];   // pivot columns of the retained rows
     uint64_t npm[kPivMaxFW];  // pivot columns of the rows the current round added
     int flag[8];  // per wavefront (up to 8)
@@ -753,7 +848,7 @@ struct alignas(16) PivShared {  // 16-byte aligned: the tables are read 16 bytes
 
 // all threads: the tables of the first positions (as many as fit) from the records
 template <int FW, int NW>
-__device__ __forceinline__ void piv_build_tables(PivShared& S, int d) {
+__device__ __forceinline__ int piv_build_tables(PivShared& S, int d) {
     constexpr int W = FW + F2_Y_WORDS;
     constexpr int cap = kPivTabWords / (16 * W);
     const int nt = (d + 3) / 4 < cap ? (d + 3) / 4 : cap;
@@ -770,7 +865,7 @@ __device__ __forceinline__ void piv_build_tables(PivShared& S, int d) {
             for (int k = 0; k < (1 << b); ++k) e[((1 << b) + k) * W] = e[k * W] ^ r;
         }
     }
-    if (threadIdx.x == 0) S.ntab = nt;
+    return nt;
 }
 
 // one table entry of W words from LDS, 16 bytes per read where W is even (the
@@ -794,7 +889,7 @@ __device__ __forceinline__ void load_entry(const uint64_t* e, uint64_t (&v)[W]) 
 // reduce this wavefront's block rows against the retained basis (one pass: the
 // basis is fully reduced).  Positions [0, 4 ntab) by table lookups: the row's own
 // 4 bits at positions 4g .. 4g+3, masked to the pivots, select entry of table g.
-template <int FW>
+template <int FW, bool FAR>
 __device__ __forceinline__ void piv_reduce(PivShared& S, int fw, int ntab, uint64_t (&f)[FW], uint64_t& y0,
                                            uint64_t& y1) {
     constexpr int W = FW + F2_Y_WORDS;
@@ -838,23 +933,22 @@ __device__ __forceinline__ void piv_reduce(PivShared& S, int fw, int ntab, uint6
         uint64_t pm = S.pm[pw];
         if (pw == (done >> 6) && (done & 63)) pm &= ~0ull << (done & 63);
         if (!pm) continue;
-        const uint64_t ow = sel_word<FW>(f0, pw);  // unreduced word pw of this lane's row
+        const uint64_t ow = word_at<FW>(f0, pw);  // unreduced word pw of this lane's row
+        // U records at a time (past the last record, record 0 of the word with an empty mask)
+        constexpr int U = FW <= 5 || FAR ? 4 : 2;
         while (pm) {
-            int bb[4];
+            int bb[U];
+            uint64_t rv[U][FW + 2];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 bb[u] = pm ? ffs64(pm) : -1;
                 pm &= pm - 1;
-            }
-            uint64_t rv[4][FW + 2];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
                 const uint64_t* rec = S.rec[64 * pw + (bb[u] < 0 ? 0 : bb[u])];
 #pragma unroll
                 for (int w = 0; w < FW + 2; ++w) rv[u][w] = rec[w];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const uint32_t mk = bb[u] < 0 ? 0u : bit_mask(ow, bb[u]);
 #pragma unroll
                 for (int w = 0; w < FW; ++w) f[w] = xor_and(f[w], mk, rv[u][w]);
@@ -865,76 +959,43 @@ __device__ __forceinline__ void piv_reduce(PivShared& S, int fw, int ntab, uint6
     }
 }
 
-// in-block elimination of one wavefront's block, in registers: the earliest row
-// with a nonzero feature residual becomes a new basis row and stays in its lane;
-// its pivot is cleared from every other row of the block, earlier new rows
-// included, so the new rows end fully reduced among themselves (and hold no
-// retained pivot: the block was reduced first).  Rows before it with a zero
-// residual are classified on the way.  The new rows then go to their records,
-// their pivots to npm and their count to nnew; the retained rows are cleared of
-// the new pivots afterwards by all wavefronts (piv_backsub).
+// in-block elimination of one wavefront's block, in registers.  The block was reduced first,
+// so the new rows hold no retained pivot.  The rows that are left are classified; the new
+// rows go to their records, their pivots to npm and their count to nnew; the retained rows
+// are cleared of the new pivots afterwards by all wavefronts (piv_backsub).
 template <int FW>
-__device__ void piv_insert(PivShared& S, int n, int64_t b0, bool valid, uint64_t (&f)[FW], uint64_t& y0, uint64_t& y1,
-                           int& ncon, long long& firstc) {
+__device__ __forceinline__ void piv_insert(PivShared& S, int n, int64_t b0, bool valid, uint64_t (&f)[FW], uint64_t& y0,
+                                           uint64_t& y1, int& ncon, long long& firstc) {
     const int lane = threadIdx.x & 63;
     const int cw = n >> 6;
     const uint64_t cbit = 1ull << (n & 63);
     uint64_t xm[FW];  // the x columns of each feature word (the constant column cleared)
 #pragma unroll
     for (int w = 0; w < FW; ++w) xm[w] = (w == cw) ? ~cbit : ~0ull;
-    if (lane < FW) S.npm[lane] = 0;
-    uint64_t pending = __ballot(valid);
-    uint64_t ins = 0;  // lanes holding new basis rows
-    int mypiv = 0;     // this lane's pivot, where it holds a new basis row
-    while (pending) {
-        uint64_t any = f[0];
+    uint64_t newp[FW];
+    eliminate_block<FW>(f, y0, y1, __ballot(valid), n, xm, newp);
+    uint64_t any = f[0];
 #pragma unroll
-        for (int w = 1; w < FW; ++w) any |= f[w];
-        const uint64_t nz = __ballot(any != 0) & pending;
-        // pending rows before the earliest nonzero one have zero residuals
-        const uint64_t zr = nz ? pending & ((nz & (0ull - nz)) - 1) : pending;
-        if (zr) {
-            const uint64_t cm = __ballot((y0 | y1) != 0) & zr;
-            if (cm) {
-                if (ncon == 0) firstc = b0 + ffs64(cm);
-                ncon += __popcll(cm);
-            }
-            pending &= ~zr;
-        }
-        if (!nz) break;
-        const int j = ffs64(nz);
-        uint64_t F[FW];
-#pragma unroll
-        for (int w = 0; w < FW; ++w) F[w] = readlane64(f[w], j);
-        const uint64_t Y0 = readlane64(y0, j), Y1 = readlane64(y1, j);
-        // pivot: the highest-priority set feature bit, x_{n-1} .. x_0, else the
-        // constant (the row is nonzero)
-        int p = n;
-#pragma unroll
-        for (int w = 0; w < FW; ++w) {
-            const uint64_t v = F[w] & xm[w];
-            p = v ? 64 * w + msb64(v) : p;
-        }
-        const int pw = p >> 6, pb = p & 63;
-        const uint32_t mm = bit_mask(sel_word<FW>(f, pw), pb) & (lane == j ? 0u : ~0u);
-#pragma unroll
-        for (int w = 0; w < FW; ++w) f[w] = xor_and(f[w], mm, F[w]);
-        y0 = xor_and(y0, mm, Y0);
-        y1 = xor_and(y1, mm, Y1);
-        if (lane == j) mypiv = p;
-        ins |= 1ull << j;
-        pending &= ~(1ull << j);
+    for (int w = 1; w < FW; ++w) any |= f[w];
+    const uint64_t cm = __ballot(valid && any == 0 && (y0 | y1) != 0);
+    if (cm) {
+        firstc = b0 + ffs64(cm);
+        ncon = __popcll(cm);
     }
-    wave_sync();  // npm cleared before the new pivots are added
-    if ((ins >> lane) & 1ull) {
-        uint64_t* rec = S.rec[mypiv];
+    if (valid && any != 0) {
+        uint64_t* rec = S.rec[row_pivot<FW>(f, xm, n)];
 #pragma unroll
         for (int w = 0; w < FW; ++w) rec[w] = f[w];
         rec[FW] = y0;
         rec[FW + 1] = y1;
-        atomicOr(reinterpret_cast<unsigned long long*>(&S.npm[mypiv >> 6]), 1ull << (mypiv & 63));
     }
-    if (lane == 0) S.nnew = __popcll(ins);
+    int nnew = 0;
+#pragma unroll
+    for (int w = 0; w < FW; ++w) {
+        nnew += __popcll(newp[w]);
+        if (lane == w) S.npm[w] = newp[w];
+    }
+    if (lane == 0) S.nnew = nnew;
 }
 
 // clear the round's new pivots from the retained rows (records of S.pm), one
@@ -955,13 +1016,38 @@ __device__ __forceinline__ void piv_backsub(PivShared& S, int d, int fw) {
         for (int w = 0; w < FW; ++w) {
             if (w >= fw) break;
             uint64_t m = S.npm[w];
-            while (m) {
-                const int b = ffs64(m);
+            auto fetch = [&](int& b, uint64_t (&r)[FW + 2]) {
+                b = ffs64(m);
                 m &= m - 1;
-                const uint32_t mk = bit_mask(R0[w], b);
                 const uint64_t* nr = S.rec[64 * w + b];
 #pragma unroll
-                for (int u = 0; u < FW + 2; ++u) R[u] = xor_and(R[u], mk, nr[u]);
+                for (int u = 0; u < FW + 2; ++u) r[u] = nr[u];
+            };
+            auto add = [&](int b, const uint64_t (&r)[FW + 2]) {
+                const uint32_t mk = bit_mask(R0[w], b);
+#pragma unroll
+                for (int u = 0; u < FW + 2; ++u) R[u] = xor_and(R[u], mk, r[u]);
+            };
+            if (!m) continue;
+            int ba, bb;
+            uint64_t ra[FW + 2], rb[FW + 2];
+            if constexpr (FW > 6) {  // (no registers to read ahead)
+                while (m) {
+                    fetch(ba, ra);
+                    add(ba, ra);
+                }
+                continue;
+            }
+            fetch(ba, ra);
+            for (;;) {  // the next new row is read while this one is added
+                const bool more = m != 0;
+                if (more) fetch(bb, rb);
+                add(ba, ra);
+                if (!more) break;
+                const bool again = m != 0;
+                if (again) fetch(ba, ra);
+                add(bb, rb);
+                if (!again) break;
             }
         }
 #pragma unroll
@@ -969,8 +1055,29 @@ __device__ __forceinline__ void piv_backsub(PivShared& S, int d, int fw) {
     }
 }
 
-template <int FW, int NW>
-__device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds, PivShared& S) {
+// the wavefronts of a workgroup, or some of them, wait for one another
+struct BlockSync {
+    static constexpr bool kFar = true;  // registers for four of the widest records
+    __device__ __forceinline__ void operator()() { __syncthreads(); }
+};
+// NW wavefronts of a larger workgroup: a count in LDS that each adds to once per wait.  Every
+// wavefront of a workgroup is resident and each of the NW passes the same waits, so each wait ends.
+template <int NW>
+struct PartSync {
+    static constexpr bool kFar = false;
+    int* count;   // zero before the first wait
+    int target;
+    __device__ __forceinline__ void operator()() {
+        target += NW;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target) __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+};
+
+template <int FW, int NW, typename Sync>
+__device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds, PivShared& S, Sync& sync) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = ds.c, n = ds.n, d = n + 1;
     const int fw = feat_words(n);  // <= FW; records keep FW feature words, then the two output words
@@ -987,10 +1094,9 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
     if (tid == 0) {
         S.contra = 0;
         S.nnew = 0;
-        S.ntab = 0;
         S.first = -1;
     }
-    __syncthreads();
+    sync();
     // the next round's block is loaded while this round runs, on the guess that
     // the round completes all NW blocks (it does once the basis stops growing);
     // not for the widest records, whose registers it would cost occupancy
@@ -1010,6 +1116,10 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
     uint64_t pre[FW + 2];
     int64_t pre_b0 = -1;
     int rank = 0;
+    // valid tables (positions [0, 4 ntab)), 0: none.  Every wavefront keeps its own count: one in
+    // LDS, set by the first wavefront to have built its part, could keep a late one from the
+    // build and from the wait behind it.
+    int ntab = 0;
     int64_t b0 = 0;
     while (b0 < m) {
         const int64_t bw = b0 + 64 * wave;  // this wavefront's block
@@ -1035,19 +1145,19 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
         y0 = valid ? raw[FW] : 0ull;
         y1 = valid ? raw[FW + 1] : 0ull;
         if constexpr (FW <= 4) {  // a large basis that will serve two rounds or more: tables
-            if (S.ntab == 0 && rank >= kPivTabMinRank && m - b0 >= kPivTabMinRows) {
-                piv_build_tables<FW, NW>(S, d);
-                __syncthreads();
+            if (ntab == 0 && rank >= kPivTabMinRank && m - b0 >= kPivTabMinRows) {
+                ntab = piv_build_tables<FW, NW>(S, d);
+                sync();
             }
         }
-        if (rank > 0) piv_reduce<FW>(S, fw, S.ntab, f, y0, y1);
+        if (rank > 0) piv_reduce<FW, Sync::kFar>(S, fw, ntab, f, y0, y1);
         uint64_t any = f[0];
 #pragma unroll
         for (int w = 1; w < FW; ++w) any |= f[w];
         const bool has_nz = __ballot(valid && any != 0) != 0;
         if (lane == 0) S.flag[wave] = has_nz ? 1 : 0;
         if (tid == 0) S.round_first = 0x7fffffffffffffffll;
-        __syncthreads();
+        sync();
         int wstar = NW;
         for (int w = NW - 1; w >= 0; --w)
             if (S.flag[w]) wstar = w;
@@ -1066,22 +1176,22 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
             atomicAdd(&S.contra, ncon);
             atomicMin(&S.round_first, firstc);
         }
-        __syncthreads();
+        sync();
         if (S.nnew) {  // retained rows lose the new pivots, then the new rows join them
             piv_backsub<FW, NW>(S, d, fw);
-            __syncthreads();
+            sync();
             if (tid < fw) S.pm[tid] |= S.npm[tid];
-            if (tid == 0) S.ntab = 0;  // the tables no longer match the basis
-            __syncthreads();
+            ntab = 0;  // the tables no longer match the basis
+            sync();
         }
         if (tid == 0 && S.first < 0 && S.round_first != 0x7fffffffffffffffll) S.first = S.round_first;
         rank = 0;
         for (int w = 0; w < fw; ++w) rank += __popcll(S.pm[w]);
-        __syncthreads();
+        sync();
         if (tid == 0) S.nnew = 0;
         b0 += 64 * static_cast<int64_t>(wstar < NW ? wstar + 1 : NW);
     }
-    __syncthreads();
+    sync();
 
     // outputs: basis rows and pivots in descending priority, canonical map, encode table, scalars
     const int64_t bo = ds.bo, po = ds.po, mo = ds.mo;
@@ -1137,7 +1247,7 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
         a.first_contra[c] = S.first;
         a.ctx_flags[c] = S.contra ? F2_CTX_CONTRADICTION : 0u;
     }
-    __syncthreads();
+    sync();
 }
 
 // ---------------------------------------------------------------------------
@@ -2189,6 +2299,235 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
     __syncthreads();
 }
 
+// One workgroup of kRegWaves wavefronts per compute unit, each wavefront fitting its own
+// contexts in its own LDS region, largest first.  The first kPivWaves of a workgroup start
+// with contexts that need more: the group ones, one per workgroup, fitted by the four
+// together (their LDS regions are one PivShared), then those of four feature words, one
+// each in a larger region.  These are chains of 100-200 us that once ran in a kernel of their
+// own behind this one and left the chip idle; here the other wavefronts work beside them.
+// A wavefront runs a pipeline over its contexts: while one is in its last block, the next one's
+// first rows, the descriptor of the one after and the list entry of the third are loading.
+// A descriptor is one load, a dword per lane.  Bound by the elimination's chain (some 400
+// cycles a pivot with four wavefronts on a SIMD, half of the time), then by the record by
+// record reduce.  A corpus of 80,000 contexts: 207 us; the former kernels, one after the
+// other, 170 us (contexts of up to 256 rows) and 264 us (the rest).
+constexpr int kRegWaves = 16;
+constexpr int kRegGrid = 256;
+
+// a workgroup's part of the list
+struct RegQueue {
+    unsigned long long tail;  // of the shared tail: the next list index, and in the upper half where the chunk ends
+    int next;                 // next position of the workgroup's share
+    int done;                 // the tail has ended
+};
+// Which kernel takes the long, one and group contexts: k_fit_reg, beside its short ones,
+// unless these are too few to hide behind or the others too many to be under way at once
+// (1,000 contexts of 17-97 columns and 2,000 rows, all long or group: 166 us there, 97 us in
+// k_fit_piv; 1,000 of 201 columns and 240 rows, all one: 117 and 255 us).
+struct PivLists {
+    int short_lo, short_n, long_lo, long_n;      // k_fit_reg: by one wavefront each
+    int one_lo, one_n, group_lo, group_n;        // by its first wavefronts, singly and together
+    int piv_group, piv_one, piv_long;            // k_fit_piv: how many of each, in this order
+};
+__device__ __forceinline__ PivLists piv_lists(const FitArgs& a) {
+    const int G = a.num_ctx < kRegGrid ? a.num_ctx : kRegGrid;  // k_fit_reg's workgroups
+    PivLists p;
+    p.short_lo = a.plan[kClsShort];
+    p.long_lo = a.plan[kClsLong];
+    p.one_lo = a.plan[kClsOne];
+    p.group_lo = a.plan[kClsGroup];
+    p.short_n = p.long_lo - p.short_lo;
+    const int nl = p.one_lo - p.long_lo, no = p.group_lo - p.one_lo, ng = a.plan[kClsLarge] - p.group_lo;
+    const bool beside = nl <= p.short_n / 4;
+    p.long_n = beside ? nl : 0;
+    p.one_n = beside ? no : 0;
+    p.group_n = beside && ng <= G ? ng : 0;
+    p.piv_group = ng - p.group_n;
+    p.piv_one = no - p.one_n;
+    p.piv_long = nl - p.long_n;
+    return p;
+}
+
+__global__ __launch_bounds__(64 * kRegWaves) void k_fit_reg(FitArgs a) {
+    __shared__ union {
+        PivShared piv;
+        uint64_t basis[kPivWaves][reg_words(kRegMaxFW + 1)];
+    } sPart;
+    __shared__ __align__(16) uint64_t sBasis[kRegWaves - kPivWaves][kRegRec];
+    __shared__ RegQueue sQueue;
+    __shared__ int sWait;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    // the first kPivWaves wavefronts first fit contexts of the other classes, where these are
+    // few: long and wide ones together, those of 4 feature words one each
+    const int g = static_cast<int>(blockIdx.x), G = static_cast<int>(gridDim.x);
+    const PivLists pl = piv_lists(a);
+    const int cnt = pl.long_n + pl.short_n;
+    const bool parted = g < pl.group_n || G - 1 - g < pl.one_n;
+    if (!parted && cnt == 0) return;
+    if (tid == 0) {
+        sQueue.next = parted ? kRegWaves - kPivWaves : kRegWaves;
+        sQueue.tail = 0;
+        sQueue.done = 0;
+        sWait = 0;
+    }
+    __syncthreads();
+    // the others start with one context each, in snake order over the four SIMDs
+    // (wavefront w runs on SIMD w mod 4), largest first
+    const int r = (wave >> 2) - (parted ? 1 : 0), simd = wave & 3;
+    int start = 4 * r + ((r & 1) ? 3 - simd : simd);
+    if (wave < kPivWaves && parted) {
+        PartSync<kPivWaves> sync{&sWait, 0};
+        __builtin_amdgcn_s_setprio(3);
+        if (g < pl.group_n) {
+            const int c = __builtin_amdgcn_readfirstlane(a.plan[kPlanHead + pl.group_lo + g]);
+            const CtxDesc ds = readlane_desc(load_desc(a, c), 0);
+            switch (feat_words(ds.n)) {
+                case 1: fit_ctx_piv<1, kPivWaves>(a, ds, sPart.piv, sync); break;
+                case 2: fit_ctx_piv<2, kPivWaves>(a, ds, sPart.piv, sync); break;
+                case 3: case 4: fit_ctx_piv<4, kPivWaves>(a, ds, sPart.piv, sync); break;
+                case 5: fit_ctx_piv<5, kPivWaves>(a, ds, sPart.piv, sync); break;
+                case 6: fit_ctx_piv<6, kPivWaves>(a, ds, sPart.piv, sync); break;
+                default: fit_ctx_piv<8, kPivWaves>(a, ds, sPart.piv, sync); break;
+            }
+        }
+        // (workgroups that had no group context come first)
+        for (int64_t i = wave * G + G - 1 - g; i < pl.one_n; i += kPivWaves * G) {
+            const int c = __builtin_amdgcn_readfirstlane(a.plan[kPlanHead + pl.one_lo + i]);
+            const CtxDesc ds = readlane_desc(load_desc(a, c), 0);
+            fit_ctx_alone<kRegMaxFW + 1>(a, ds, sPart.basis[wave]);
+        }
+        __builtin_amdgcn_s_setprio(0);
+        if (lane == 0) start = atomicAdd(&sQueue.next, 1);
+        start = __builtin_amdgcn_readfirstlane(start);
+    }
+    uint64_t* basis = wave < kPivWaves ? sPart.basis[wave] : sBasis[wave - kPivWaves];
+    // the share's list positions (the class bounds read once)
+    // the list: the long contexts, then the short ones
+    const int32_t* const longs = a.plan + kPlanHead + pl.long_lo;
+    const int32_t* const shorts = a.plan + kPlanHead + pl.short_lo - pl.long_n;
+    auto list = [&](int e) { return (e < pl.long_n ? longs : shorts)[e]; };
+    const RegScalars sc = reg_scalars(a);
+    // lane's dword of a context's descriptor: n; row_off of the context (2) and of the next
+    // (low half: the difference of the class's contexts fits); basis, pivot and map offsets
+    const char* src = reinterpret_cast<const char*>(lane < 1   ? a.n_bits
+                                                    : lane < 3 ? reinterpret_cast<const int32_t*>(a.row_off) + (lane - 1)
+                                                    : lane < 4 ? reinterpret_cast<const int32_t*>(a.row_off) + 2
+                                                    : lane < 6 ? reinterpret_cast<const int32_t*>(a.basis_off) + (lane - 4)
+                                                    : lane < 8 ? reinterpret_cast<const int32_t*>(a.piv_off) + (lane - 6)
+                                                               : reinterpret_cast<const int32_t*>(a.map_off) + (lane & 1));
+    const uint32_t step = lane < 1 ? 4 : 8;
+    // The first half of the list is dealt to the workgroups in snake order; the tail, its
+    // smaller contexts, goes to whichever is free, which evens out what the first wavefronts'
+    // other contexts took: an eighth of a workgroup's part at a time through a counter in memory
+    // (about 5 ns per addition to one address: each wavefront's own additions, four contexts at
+    // a time, cost 20 us on 80,000 contexts), from there one at a time through LDS.
+    const int share = cnt / (2 * G) < kRegWaves ? kRegWaves : cnt / (2 * G);
+    const int tail = share * G < cnt ? share * G : cnt;
+    const int chunk = (cnt - tail) / (8 * G) + 1;
+    auto load = [&](int c) {
+        return *reinterpret_cast<const int32_t*>(src + static_cast<uint64_t>(c < 0 ? 0u : static_cast<uint32_t>(c)) * step);
+    };
+    struct Pipe {
+        int c, n, m;        // the context at hand, then (after the call) the next one
+        const uint64_t* R;
+        int desc;           // its descriptor
+        int out;            // the descriptor of the context at hand: its output offsets
+        int c1, desc1;      // the one after, loading
+        int id, at;         // the list entry of the third, loading; the fourth's position in the share, on its way
+        __device__ __forceinline__ void arrived(RegRows& raw) {
+            asm volatile("" ::"v"(raw.w0), "v"(raw.w1), "v"(raw.w2), "v"(raw.w3), "v"(raw.w4), "v"(desc1), "v"(id));
+        }
+        __device__ __forceinline__ int64_t pair(int v, int l) {
+            return static_cast<int64_t>((static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(v, l + 1))) << 32) |
+                                        static_cast<uint32_t>(__builtin_amdgcn_readlane(v, l)));
+        }
+        __device__ __forceinline__ void offsets(int64_t& bo, int64_t& po, int64_t& mo) {
+            bo = pair(out, 4);
+            po = pair(out, 6);
+            mo = pair(out, 8);
+        }
+        // width, rows and first rows of the context of desc
+        __device__ __forceinline__ void take(const FitArgs& a, RegRows& raw) {
+            if (c < 0) return;
+            n = __builtin_amdgcn_readlane(desc, 0);
+            R = a.rows + pair(desc, 1);
+            const uint32_t words = static_cast<uint32_t>(__builtin_amdgcn_readlane(desc, 3) - __builtin_amdgcn_readlane(desc, 1));
+            switch (feat_words(n)) {
+                case 1: raw = load_rows<3>(R, m = static_cast<int>(words / 3u), 0); break;
+                case 2: raw = load_rows<4>(R, m = static_cast<int>(words / 4u), 0); break;
+                default: raw = load_rows<5>(R, m = static_cast<int>(words / 5u), 0); break;
+            }
+        }
+    };
+    struct Step : Pipe {
+        const FitArgs& a;
+        decltype(load)& ld;
+        decltype(list)& at_list;
+        RegQueue& Q;
+        int lane, G, g, share, tail, chunk, cnt;
+        __device__ __forceinline__ int entry() {  // the next list entry, or -1
+            const int v = __builtin_amdgcn_readfirstlane(this->at);
+            if (v >= share) return tail_entry();
+            if (lane == 0) this->at = atomicAdd(&Q.next, 1);
+            const int e = v * G + ((v & 1) ? G - 1 - g : g);
+            return e < cnt ? at_list(e) : -1;
+        }
+        __device__ __forceinline__ int tail_entry() {
+            if (tail >= cnt) return -1;
+            for (;;) {
+                unsigned long long q = 0;
+                if (lane == 0) q = atomicAdd(&Q.tail, 1ull);
+                const int cur = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(q)));
+                const int end = __builtin_amdgcn_readfirstlane(static_cast<int>(q >> 32));
+                if (cur < end) return at_list(cur);
+                if (cur == end) {  // one wavefront's part: the next chunk, or the news that there is none
+                    uint32_t v = 0;  // (the counter may pass 2^31 by a few chunks)
+                    if (lane == 0) v = static_cast<uint32_t>(atomicAdd(&a.plan[kRegNext], chunk)) + static_cast<uint32_t>(tail);
+                    v = __builtin_amdgcn_readfirstlane(v);
+                    if (v >= static_cast<uint32_t>(cnt)) {
+                        __hip_atomic_store(&Q.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        return -1;
+                    }
+                    const unsigned long long stop = v + chunk < static_cast<uint32_t>(cnt) ? v + chunk : cnt;
+                    __hip_atomic_store(&Q.tail, (stop << 32) | (v + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    return at_list(static_cast<int>(v));
+                }
+                // the wavefront that met the end stores one or the other
+                if (__hip_atomic_load(&Q.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) return -1;
+                __builtin_amdgcn_s_sleep(2);
+            }
+        }
+        __device__ __forceinline__ void operator()(RegRows& raw) {
+            this->out = this->desc;
+            this->c = this->c1;
+            this->desc = this->desc1;
+            this->take(a, raw);
+            this->c1 = __builtin_amdgcn_readfirstlane(this->id);
+            this->desc1 = ld(this->c1);
+            this->id = entry();
+        }
+    };
+    RegRows raw{0, 0, 0, 0, 0, 0};
+    Step P{{}, a, load, list, sQueue, lane, G, g, share, tail, chunk, cnt};
+    P.at = start;
+    P.c = __builtin_amdgcn_readfirstlane(P.entry());
+    P.desc = load(P.c);
+    P.c1 = __builtin_amdgcn_readfirstlane(P.entry());
+    P.desc1 = load(P.c1);
+    P.id = P.entry();
+    P.take(a, raw);
+    while (P.c >= 0) {
+        switch (feat_words(P.n)) {
+            case 1:
+                if (P.n < 32) fit_ctx_reg<1, true>(a, sc, P.c, P.n, P.m, P.R, basis, raw, P);
+                else fit_ctx_reg<1>(a, sc, P.c, P.n, P.m, P.R, basis, raw, P);
+                break;
+            case 2: fit_ctx_reg<2>(a, sc, P.c, P.n, P.m, P.R, basis, raw, P); break;
+            default: fit_ctx_reg<3>(a, sc, P.c, P.n, P.m, P.R, basis, raw, P); break;
+        }
+    }
+}
+
 // contexts of classes 1-2 (fw <= 8 beyond the register kernel): pivot-indexed LDS
 // basis, kPivWaves wavefronts per workgroup, several workgroups per compute unit.
 // The list (largest first) is taken greedily: workgroup g starts at position g,
@@ -2197,17 +2536,24 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
 __global__ __launch_bounds__(kPivThreads, 3) void k_fit_piv(FitArgs a) {
     __shared__ PivShared S;
     __shared__ int sNext;
-    const int lo = a.plan[kClsPiv], cnt = a.plan[kClsPivLong + 1] - lo;
+    const PivLists pl = piv_lists(a);
+    const int g1 = pl.piv_group, g2 = g1 + pl.piv_one, cnt = g2 + pl.piv_long;
+    const int32_t* const order = a.plan + kPlanHead;
+    BlockSync sync;
     for (int i = static_cast<int>(blockIdx.x); i < cnt;) {
-        const int c = __builtin_amdgcn_readfirstlane(a.plan[kPlanHead + lo + i]);
+        const int c = __builtin_amdgcn_readfirstlane(i < g1   ? order[pl.group_lo + i]
+                                                     : i < g2 ? order[pl.one_lo + i - g1]
+                                                              : order[pl.long_lo + i - g2]);
         int next = 0;
         if (threadIdx.x == 0) next = atomicAdd(&a.plan[kPivNext], 1) + static_cast<int>(gridDim.x);
         const CtxDesc ds = readlane_desc(load_desc(a, c), 0);
         switch (feat_words(ds.n)) {
-            case 1: fit_ctx_piv<1, kPivWaves>(a, ds, S); break;
-            case 2: fit_ctx_piv<2, kPivWaves>(a, ds, S); break;
-            case 3: case 4: fit_ctx_piv<4, kPivWaves>(a, ds, S); break;
-            default: fit_ctx_piv<8, kPivWaves>(a, ds, S); break;
+            case 1: fit_ctx_piv<1, kPivWaves>(a, ds, S, sync); break;
+            case 2: fit_ctx_piv<2, kPivWaves>(a, ds, S, sync); break;
+            case 3: case 4: fit_ctx_piv<4, kPivWaves>(a, ds, S, sync); break;
+            case 5: fit_ctx_piv<5, kPivWaves>(a, ds, S, sync); break;
+            case 6: fit_ctx_piv<6, kPivWaves>(a, ds, S, sync); break;
+            default: fit_ctx_piv<8, kPivWaves>(a, ds, S, sync); break;
         }
         if (threadIdx.x == 0) sNext = next;
         __syncthreads();
@@ -2223,11 +2569,9 @@ __global__ __launch_bounds__(kPivThreads, 3) void k_fit_piv(FitArgs a) {
 // and one workgroup per context needs no load balance.  Invalid contexts, and any
 // wider than the declared bound, are flagged here.
 constexpr int kSmallBatch = 64;
+constexpr int kSmallRows = 256;
 union SmallShared {
-    struct {
-        uint64_t rec[64 * kRegMaxFW * kRecWords];
-        int16_t pos[64 * kRegMaxFW];
-    } reg;
+    uint64_t reg[kRegRec];
     PivShared piv;
 };
 
@@ -2240,22 +2584,25 @@ __global__ __launch_bounds__(kSmallThreads) void k_fit_small(FitArgs a) {
         return;
     }
     const int fw = feat_words(ds.n);
-    switch (fit_class(ds)) {
-        case kClsReg:
+    BlockSync sync;
+    switch (fit_class(ds, kSmallRows)) {
+        case kClsShort:
             if (threadIdx.x < 64) {
-                if (fw == 1) fit_ctx_reg<1>(a, ds, U.reg.rec, U.reg.pos);
-                else if (fw == 2) fit_ctx_reg<2>(a, ds, U.reg.rec, U.reg.pos);
-                else fit_ctx_reg<3>(a, ds, U.reg.rec, U.reg.pos);
+                if (fw == 1) fit_ctx_alone<1>(a, ds, U.reg);
+                else if (fw == 2) fit_ctx_alone<2>(a, ds, U.reg);
+                else fit_ctx_alone<3>(a, ds, U.reg);
             }
             break;
         case kClsLarge:  // not launched for a batch that may hold one (the bound is below 512)
             break;
         default:
             switch (fw) {
-                case 1: fit_ctx_piv<1, kSmallWaves>(a, ds, U.piv); break;
-                case 2: fit_ctx_piv<2, kSmallWaves>(a, ds, U.piv); break;
-                case 3: case 4: fit_ctx_piv<4, kSmallWaves>(a, ds, U.piv); break;
-                default: fit_ctx_piv<8, kSmallWaves>(a, ds, U.piv); break;
+                case 1: fit_ctx_piv<1, kSmallWaves>(a, ds, U.piv, sync); break;
+                case 2: fit_ctx_piv<2, kSmallWaves>(a, ds, U.piv, sync); break;
+                case 3: case 4: fit_ctx_piv<4, kSmallWaves>(a, ds, U.piv, sync); break;
+                case 5: fit_ctx_piv<5, kSmallWaves>(a, ds, U.piv, sync); break;
+                case 6: fit_ctx_piv<6, kSmallWaves>(a, ds, U.piv, sync); break;
+                default: fit_ctx_piv<8, kSmallWaves>(a, ds, U.piv, sync); break;
             }
             break;
     }
@@ -4232,7 +4579,7 @@ void launch_fit(FitArgs a, hipStream_t s) {
     const int plan_blocks = static_cast<int>((static_cast<int64_t>(C) + kPlanThreads - 1) / kPlanThreads);
     hipLaunchKernelGGL(k_plan_count, dim3(plan_blocks), dim3(kPlanThreads), 0, s, a);
     hipLaunchKernelGGL(k_plan_scatter, dim3(plan_blocks), dim3(kPlanThreads), 0, s, a, plan_blocks);
-    hipLaunchKernelGGL(k_fit_reg, dim3(fit_grid((C + kRegWaves - 1) / kRegWaves, 256)), dim3(64 * kRegWaves), 0, s, a);
+    hipLaunchKernelGGL(k_fit_reg, dim3(fit_grid(C, kRegGrid)), dim3(64 * kRegWaves), 0, s, a);
     hipLaunchKernelGGL(k_fit_piv, dim3(fit_grid(C, kPivGrid)), dim3(kPivThreads), 0, s, a);
     // a batch whose declared widths stay below 512 holds no wide context (wider
     // ones are rejected by the plan), so the wide kernel is not launched at all
