@@ -300,21 +300,16 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(FitArgs a, int bl
     const int tid = threadIdx.x, lane = tid & 63;
     const int g0 = static_cast<int>(blockIdx.x);
     int total = 0, before = 0;
-    int g = 0;
-    for (; g + 8 <= blocks; g += 8) {  // eight loads in flight
-        int v[8];
+    constexpr int U = 32;  // loads in flight (79 blocks: 8.4 us; 9.0 us with 8)
+    for (int g = 0; g < blocks; g += U) {
+        int v[U];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = P.hist[static_cast<int64_t>(g + k) * kPlanBins + tid];
+        for (int k = 0; k < U; ++k) v[k] = g + k < blocks ? P.hist[static_cast<int64_t>(g + k) * kPlanBins + tid] : 0;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < U; ++k) {
             before += g + k < g0 ? v[k] : 0;
             total += v[k];
         }
-    }
-    for (; g < blocks; ++g) {
-        const int v = P.hist[static_cast<int64_t>(g) * kPlanBins + tid];
-        before += g < g0 ? v : 0;
-        total += v;
     }
     int x = total;
     for (int o = 1; o < 64; o <<= 1) {
@@ -890,8 +885,7 @@ __device__ __forceinline__ void load_entry(const uint64_t* e, uint64_t (&v)[W]) 
 // basis is fully reduced).  Positions [0, 4 ntab) by table lookups: the row's own
 // 4 bits at positions 4g .. 4g+3, masked to the pivots, select entry of table g.
 template <int FW, bool FAR>
-__device__ __forceinline__ void piv_reduce(PivShared& S, int fw, int ntab, uint64_t (&f)[FW], uint64_t& y0,
-                                           uint64_t& y1) {
+__device__ __forceinline__ void piv_reduce(PivShared& S, int ntab, uint64_t (&f)[FW], uint64_t& y0, uint64_t& y1) {
     constexpr int W = FW + F2_Y_WORDS;
     uint64_t f0[FW];
 #pragma unroll
@@ -929,31 +923,32 @@ __device__ __forceinline__ void piv_reduce(PivShared& S, int fw, int ntab, uint6
         }
     }
     const int done = FW <= 4 ? 4 * ntab : 0;  // positions below are reduced
-    for (int pw = done >> 6; pw < fw; ++pw) {
-        uint64_t pm = S.pm[pw];
-        if (pw == (done >> 6) && (done & 63)) pm &= ~0ull << (done & 63);
-        if (!pm) continue;
-        const uint64_t ow = word_at<FW>(f0, pw);  // unreduced word pw of this lane's row
-        // U records at a time (past the last record, record 0 of the word with an empty mask)
+#pragma unroll
+    for (int h = 0; h < 2 * FW; ++h) {  // half a word of pivots at a time
+        if (32 * h + 32 <= done) continue;
+        uint32_t ps = __builtin_amdgcn_readfirstlane(reinterpret_cast<const uint32_t*>(S.pm)[h]);
+        if (32 * h < done) ps &= ~0u << (done & 31);
+        const int own = static_cast<int>(static_cast<uint32_t>(f0[h / 2] >> (32 * (h & 1))));  // unreduced
+        // U records at a time (past the last, record 0 of the half with an empty mask)
         constexpr int U = FW <= 5 || FAR ? 4 : 2;
-        while (pm) {
-            int bb[U];
-            uint64_t rv[U][FW + 2];
+        while (ps) {
+            uint32_t mk[U];
+            uint64_t rv[U][W];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                bb[u] = pm ? ffs64(pm) : -1;
-                pm &= pm - 1;
-                const uint64_t* rec = S.rec[64 * pw + (bb[u] < 0 ? 0 : bb[u])];
+                const int b = ps ? __builtin_ctz(ps) : 0;
+                mk[u] = ps ? static_cast<uint32_t>(__builtin_amdgcn_sbfe(own, b, 1)) : 0u;
+                ps &= ps - 1;
+                const uint64_t* rec = S.rec[32 * h + b];
 #pragma unroll
-                for (int w = 0; w < FW + 2; ++w) rv[u][w] = rec[w];
+                for (int w = 0; w < W; ++w) rv[u][w] = rec[w];
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t mk = bb[u] < 0 ? 0u : bit_mask(ow, bb[u]);
 #pragma unroll
-                for (int w = 0; w < FW; ++w) f[w] = xor_and(f[w], mk, rv[u][w]);
-                y0 = xor_and(y0, mk, rv[u][FW]);
-                y1 = xor_and(y1, mk, rv[u][FW + 1]);
+                for (int w = 0; w < FW; ++w) f[w] = xor_and(f[w], mk[u], rv[u][w]);
+                y0 = xor_and(y0, mk[u], rv[u][FW]);
+                y1 = xor_and(y1, mk[u], rv[u][FW + 1]);
             }
         }
     }
@@ -1150,7 +1145,7 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
                 sync();
             }
         }
-        if (rank > 0) piv_reduce<FW, Sync::kFar>(S, fw, ntab, f, y0, y1);
+        if (rank > 0) piv_reduce<FW, Sync::kFar>(S, ntab, f, y0, y1);
         uint64_t any = f[0];
 #pragma unroll
         for (int w = 1; w < FW; ++w) any |= f[w];
