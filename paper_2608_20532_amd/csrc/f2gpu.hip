@@ -3694,6 +3694,9 @@ constexpr int kStreamThreads = 256;
 // an output word is its index in the workgroup's span times magic = ceil(2^32 / rw)
 // (exact: the span is under 2^15 words and rw <= 66)
 constexpr int kVecRows = 256;
+// words in flight per thread (7.24M rows of 5 values: 199 us with 1, 175 with 2, 166 with 4 = 5.2 TB/s, 164 with 8, which
+// more of a short row's span leaves empty)
+constexpr int kVecStep = 4;
 
 __global__ __launch_bounds__(kStreamThreads) void k_vectorize(const uint64_t* values, const uint64_t* y,
                                                               int64_t num_rows, int k, uint64_t keep0,
@@ -3704,14 +3707,21 @@ __global__ __launch_bounds__(kStreamThreads) void k_vectorize(const uint64_t* va
     const uint64_t* vals = values + r0 * k;
     const uint64_t* yr = y ? y + 2 * r0 : nullptr;
     uint64_t* out = rows + r0 * rw;
-    for (int w = threadIdx.x; w < nr * rw; w += kStreamThreads) {
-        const int r = static_cast<int>(__umulhi(static_cast<uint32_t>(w), magic));
-        const int j = w - r * rw;
-        uint64_t v;
-        if (j < k) v = vals[r * k + j];
-        else if (j == k) v = 1;  // the constant feature
-        else v = yr ? (yr[2 * r + (j - k - 1)] & (j == k + 1 ? keep0 : keep1)) : 0ull;
-        out[w] = v;
+    // kVecStep words per thread at a time, every load in flight before the first store
+    for (int w0 = threadIdx.x; w0 < nr * rw; w0 += kVecStep * kStreamThreads) {
+        uint64_t v[kVecStep];
+#pragma unroll
+        for (int u = 0; u < kVecStep; ++u) {
+            const int w = w0 + u * kStreamThreads;
+            const int r = static_cast<int>(__umulhi(static_cast<uint32_t>(w), magic));
+            const int j = w - r * rw;
+            v[u] = j == k ? 1 : 0;  // the constant feature; without outputs, zeros
+            if (w < nr * rw && j < k) v[u] = vals[r * k + j];
+            else if (w < nr * rw && j > k && yr) v[u] = yr[2 * r + (j - k - 1)] & (j == k + 1 ? keep0 : keep1);
+        }
+#pragma unroll
+        for (int u = 0; u < kVecStep; ++u)
+            if (w0 + u * kStreamThreads < nr * rw) out[w0 + u * kStreamThreads] = v[u];
     }
 }
 
