@@ -258,6 +258,72 @@ __device__ __forceinline__ PlanView plan_view(const FitArgs& a) {
     return v;
 }
 
+// what the fit kernels count in, and where they meet
+__device__ __forceinline__ void plan_clear(const FitArgs& a) {
+    const int tid = threadIdx.x;
+    if (tid < 2 * kMaxMembers) a.plan[kBarHead + tid] = 0;
+    if (tid < 2) a.plan[kPivNext + tid] = 0;
+}
+
+// a context's bin, or -1 and its outputs written where it is invalid
+__device__ __forceinline__ int plan_bin(const FitArgs& a, const CtxDesc& ds) {
+    if (ds.bad) {
+        write_bad_context(a, ds);
+        return -1;
+    }
+    const int cls = fit_class(ds);
+    if (cls == kClsLarge) {  // the workgroups of a wide context add their counts and flags, and share a list
+        a.ctx_flags[ds.c] = 0u;
+        a.n_contra[ds.c] = 0;
+        a.first_contra[ds.c] = -1;
+        a.pivots[ds.po] = 0;
+    }
+    return cls * kBuckets + (kBuckets - 1 - cost_bucket(ds));
+}
+
+// exclusive scan of one bin per thread (sWave: a word per wavefront)
+__device__ __forceinline__ int plan_scan(int total, int* sWave) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    int x = total;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(x, o);
+        if (lane >= o) x += t;
+    }
+    if (lane == 63) sWave[tid >> 6] = x;
+    __syncthreads();
+    int base = 0;
+    for (int w = 0; w < (tid >> 6); ++w) base += sWave[w];
+    return base + x - total;
+}
+__device__ __forceinline__ void plan_offsets(const PlanView& P, int excl, int total) {
+    const int tid = threadIdx.x;
+    if (tid % kBuckets == 0 && tid < kNumCls * kBuckets) P.cls_off[tid / kBuckets] = excl;
+    if (tid == kPlanThreads - 1) P.cls_off[kNumCls] = excl + total;
+}
+
+// the plan of up to kPlanThreads contexts, one per thread, in one launch (a fit of 1,000
+// contexts: 41.9 us, with the two kernels below 45.4 us; four contexts per thread took 12 us on
+// 4,096, the two kernels 9.6 us)
+__global__ __launch_bounds__(kPlanThreads) void k_plan_one(FitArgs a) {
+    __shared__ int sBin[kPlanBins];
+    __shared__ int sWave[kPlanThreads / 64];
+    const PlanView P = plan_view(a);
+    const int tid = threadIdx.x;
+    sBin[tid] = 0;
+    plan_clear(a);
+    const CtxDesc ds = load_desc(a, tid);  // (c = -1 past the end)
+    __syncthreads();
+    const int key = ds.c < 0 ? -1 : plan_bin(a, ds);
+    if (key >= 0) atomicAdd(&sBin[key], 1);
+    __syncthreads();
+    const int total = sBin[tid];
+    const int excl = plan_scan(total, sWave);
+    plan_offsets(P, excl, total);
+    sBin[tid] = excl;
+    __syncthreads();
+    if (key >= 0) P.order[atomicAdd(&sBin[key], 1)] = ds.c;
+}
+
 // (1) per context: validate, class and bin; per block: histogram of the bins
 __global__ __launch_bounds__(kPlanThreads) void k_plan_count(FitArgs a) {
     __shared__ int sBin[kPlanBins];
@@ -265,25 +331,11 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(FitArgs a) {
     const int tid = threadIdx.x;
     sBin[tid] = 0;
     __syncthreads();
-    if (blockIdx.x == 0 && tid < 2 * kMaxMembers) a.plan[kBarHead + tid] = 0;
-    if (blockIdx.x == 0 && tid < 2) a.plan[kPivNext + tid] = 0;
+    if (blockIdx.x == 0) plan_clear(a);
     const int64_t c = static_cast<int64_t>(blockIdx.x) * kPlanThreads + tid;
     if (c < a.num_ctx) {
-        const CtxDesc ds = load_desc(a, c);
-        int k = -1;
-        if (ds.bad) {
-            write_bad_context(a, ds);
-        } else {
-            const int cls = fit_class(ds);
-            k = cls * kBuckets + (kBuckets - 1 - cost_bucket(ds));
-            atomicAdd(&sBin[k], 1);
-            if (cls == kClsLarge) {  // the workgroups of a wide context add their counts and flags, and share a list
-                a.ctx_flags[c] = 0u;
-                a.n_contra[c] = 0;
-                a.first_contra[c] = -1;
-                a.pivots[ds.po] = 0;
-            }
-        }
+        const int k = plan_bin(a, load_desc(a, c));
+        if (k >= 0) atomicAdd(&sBin[k], 1);
         P.key[c] = k;
     }
     __syncthreads();
@@ -297,7 +349,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(FitArgs a, int bl
     __shared__ int sBin[kPlanBins];
     __shared__ int sWave[kPlanThreads / 64];
     const PlanView P = plan_view(a);
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int g0 = static_cast<int>(blockIdx.x);
     int total = 0, before = 0;
     constexpr int U = 32;  // loads in flight (79 blocks: 8.4 us; 9.0 us with 8)
@@ -311,20 +363,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(FitArgs a, int bl
             total += v[k];
         }
     }
-    int x = total;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(x, o);
-        if (lane >= o) x += t;
-    }
-    if (lane == 63) sWave[tid >> 6] = x;
-    __syncthreads();
-    int base = 0;
-    for (int w = 0; w < (tid >> 6); ++w) base += sWave[w];
-    const int excl = base + x - total;
-    if (g0 == 0) {
-        if (tid % kBuckets == 0 && tid < kNumCls * kBuckets) P.cls_off[tid / kBuckets] = excl;
-        if (tid == kPlanThreads - 1) P.cls_off[kNumCls] = excl + total;
-    }
+    const int excl = plan_scan(total, sWave);
+    if (g0 == 0) plan_offsets(P, excl, total);
     sBin[tid] = excl + before;
     __syncthreads();
     const int64_t c = static_cast<int64_t>(g0) * kPlanThreads + tid;
@@ -2316,12 +2356,15 @@ struct RegQueue {
     int done;                 // the tail has ended
 };
 // Which kernel takes the long, one and group contexts: k_fit_reg, beside its short ones,
-// unless these are too few to hide behind or the others too many to be under way at once
+// unless these are too few to hide behind or the others too many to be under way at once.
+// Where the short ones are too few, the long ones are group contexts, and k_fit_reg takes them
+// only if it has a workgroup for each
 // (1,000 contexts of 17-97 columns and 2,000 rows, all long or group: 166 us there, 97 us in
 // k_fit_piv; 1,000 of 201 columns and 240 rows, all one: 117 and 255 us).
 struct PivLists {
     int short_lo, short_n, long_lo, long_n;      // k_fit_reg: by one wavefront each
-    int one_lo, one_n, group_lo, group_n;        // by its first wavefronts, singly and together
+    int one_lo, one_n;                           // by its first wavefronts, singly
+    int group_lo, group_n, group_long;           // and together: of the group list, of the long list
     int piv_group, piv_one, piv_long;            // k_fit_piv: how many of each, in this order
 };
 __device__ __forceinline__ PivLists piv_lists(const FitArgs& a) {
@@ -2334,12 +2377,14 @@ __device__ __forceinline__ PivLists piv_lists(const FitArgs& a) {
     p.short_n = p.long_lo - p.short_lo;
     const int nl = p.one_lo - p.long_lo, no = p.group_lo - p.one_lo, ng = a.plan[kClsLarge] - p.group_lo;
     const bool beside = nl <= p.short_n / 4;
+    const bool few = ng + (beside ? 0 : nl) <= G;
     p.long_n = beside ? nl : 0;
-    p.one_n = beside ? no : 0;
-    p.group_n = beside && ng <= G ? ng : 0;
+    p.one_n = beside || few ? no : 0;
+    p.group_n = few ? ng : 0;
+    p.group_long = few && !beside ? nl : 0;
     p.piv_group = ng - p.group_n;
     p.piv_one = no - p.one_n;
-    p.piv_long = nl - p.long_n;
+    p.piv_long = nl - p.long_n - p.group_long;
     return p;
 }
 
@@ -2357,7 +2402,8 @@ __global__ __launch_bounds__(64 * kRegWaves) void k_fit_reg(FitArgs a) {
     const int g = static_cast<int>(blockIdx.x), G = static_cast<int>(gridDim.x);
     const PivLists pl = piv_lists(a);
     const int cnt = pl.long_n + pl.short_n;
-    const bool parted = g < pl.group_n || G - 1 - g < pl.one_n;
+    const int groups = pl.group_n + pl.group_long;
+    const bool parted = g < groups || G - 1 - g < pl.one_n;
     if (!parted && cnt == 0) return;
     if (tid == 0) {
         sQueue.next = parted ? kRegWaves - kPivWaves : kRegWaves;
@@ -2373,8 +2419,9 @@ __global__ __launch_bounds__(64 * kRegWaves) void k_fit_reg(FitArgs a) {
     if (wave < kPivWaves && parted) {
         PartSync<kPivWaves> sync{&sWait, 0};
         __builtin_amdgcn_s_setprio(3);
-        if (g < pl.group_n) {
-            const int c = __builtin_amdgcn_readfirstlane(a.plan[kPlanHead + pl.group_lo + g]);
+        if (g < groups) {
+            const int c = __builtin_amdgcn_readfirstlane(
+                a.plan[kPlanHead + (g < pl.group_n ? pl.group_lo + g : pl.long_lo + g - pl.group_n)]);
             const CtxDesc ds = readlane_desc(load_desc(a, c), 0);
             switch (feat_words(ds.n)) {
                 case 1: fit_ctx_piv<1, kPivWaves>(a, ds, sPart.piv, sync); break;
@@ -4582,10 +4629,15 @@ void launch_fit(FitArgs a, hipStream_t s) {
         return;
     }
     const int plan_blocks = static_cast<int>((static_cast<int64_t>(C) + kPlanThreads - 1) / kPlanThreads);
-    hipLaunchKernelGGL(k_plan_count, dim3(plan_blocks), dim3(kPlanThreads), 0, s, a);
-    hipLaunchKernelGGL(k_plan_scatter, dim3(plan_blocks), dim3(kPlanThreads), 0, s, a, plan_blocks);
+    if (C <= kPlanThreads) {
+        hipLaunchKernelGGL(k_plan_one, dim3(1), dim3(kPlanThreads), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(k_plan_count, dim3(plan_blocks), dim3(kPlanThreads), 0, s, a);
+        hipLaunchKernelGGL(k_plan_scatter, dim3(plan_blocks), dim3(kPlanThreads), 0, s, a, plan_blocks);
+    }
     hipLaunchKernelGGL(k_fit_reg, dim3(fit_grid(C, kRegGrid)), dim3(64 * kRegWaves), 0, s, a);
-    hipLaunchKernelGGL(k_fit_piv, dim3(fit_grid(C, kPivGrid)), dim3(kPivThreads), 0, s, a);
+    if (C > kRegGrid)  // (else k_fit_reg has a workgroup for every context)
+        hipLaunchKernelGGL(k_fit_piv, dim3(fit_grid(C, kPivGrid)), dim3(kPivThreads), 0, s, a);
     // a batch whose declared widths stay below 512 holds no wide context (wider
     // ones are rejected by the plan), so the wide kernel is not launched at all
     if (a.max_n >= 0 && a.max_n < 512) return;

@@ -39,7 +39,7 @@ def _contexts(rng, shapes, count):
 
 @pytest.mark.parametrize("short,long,one,group", [
     (70, 0, 0, 0), (60, 6, 6, 11), (300, 40, 13, 30), (40, 14, 12, 22), (0, 70, 0, 0), (0, 0, 70, 0), (0, 0, 0, 66), (24, 6, 300, 5),
-    (30, 0, 0, 270)])
+    (30, 0, 0, 270), (10, 260, 6, 11)])
 def test_fit_classes(f2, short, long, one, group):
     rng = np.random.default_rng(short + 7 * long + 11 * one + 13 * group)
     ctx = _contexts(rng, SHORT, short) + _contexts(rng, LONG, long) + _contexts(rng, ONE, one) + _contexts(rng, GROUP, group)
