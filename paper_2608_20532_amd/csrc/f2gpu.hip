@@ -15,12 +15,12 @@
 //      hold that bit and to the retained rows that hold it (back-substitution
 //      keeps the basis fully reduced), and is inserted.
 // A plan kernel validates the contexts and sorts them into classes by feature
-// words and length, each class list in decreasing order of estimated work:
-// contexts of up to 3 feature words keep the basis in registers (one lane per
-// retained row), contexts of 4-8 words keep a pivot-indexed basis in LDS (one
-// wavefront, or eight for long contexts, which reduce eight blocks at once),
-// wider contexts run a workgroup-per-context kernel with the basis in HBM and
-// the rows it needs staged in LDS.
+// words and length, each class list in decreasing order of estimated work.
+// Contexts of up to 8 words keep a pivot-indexed basis in LDS: those of up to 4
+// words that are not too long are fitted by one wavefront each, the others by
+// four together, which reduce four blocks at once; both run side by side in one
+// kernel.  Wider contexts take up to eight workgroups each, with the basis in
+// HBM and the rows it needs staged in LDS.
 //
 // Encode (Sec. 2.3): T(phi) is the XOR of the canonical map columns over the
 // set bits of phi = [x | 1]; the support test checks phi against the
@@ -845,10 +845,9 @@ __device__ __forceinline__ void fit_ctx_alone(const FitArgs& a, const CtxDesc& d
 }
 
 // ---------------------------------------------------------------------------
-// pivot-indexed LDS-basis fit: retained row of pivot p in record p (fw + 2
-// words), a pivot-column bitmask beside it, for contexts of 4-8 feature words
-// and for long contexts of up to 8 feature words.  With NW > 1 wavefronts (the
-// kernel runs kPivWaves) the next NW blocks of 64 rows are reduced
+// fit by several wavefronts: retained row of pivot p in LDS record p (fw + 2
+// words), a pivot-column bitmask beside it, for contexts of 5-8 feature words
+// and for long ones of fewer.  The next NW blocks of 64 rows are reduced
 // in parallel, one per wavefront; the first block (in stream order) that still
 // holds a nonzero feature residual runs the insertion loop in its own
 // wavefront (in registers), the blocks before it are only classified, the
@@ -2570,8 +2569,8 @@ __global__ __launch_bounds__(64 * kRegWaves) void k_fit_reg(FitArgs a) {
     }
 }
 
-// contexts of classes 1-2 (fw <= 8 beyond the register kernel): pivot-indexed LDS
-// basis, kPivWaves wavefronts per workgroup, several workgroups per compute unit.
+// the long, one and group contexts that k_fit_reg leaves: kPivWaves wavefronts per
+// workgroup, several workgroups per compute unit.
 // The list (largest first) is taken greedily: workgroup g starts at position g,
 // then each takes the next free position from a counter as it finishes one (the
 // fetch is issued when a context starts, so its latency hides behind the work).
@@ -2606,8 +2605,8 @@ __global__ __launch_bounds__(kPivThreads, 3) void k_fit_piv(FitArgs a) {
 
 // Small batches (up to kSmallBatch contexts, declared widths below 512): one
 // launch, one workgroup of 8 wavefronts per context, the context's class choosing
-// the path (one wavefront for the register basis, all eight for the LDS basis).
-// No plan: its two launches would cost more than the fit of a batch this size,
+// the path (one wavefront up to kSmallRows rows of up to 3 feature words, else all eight).
+// No plan: its launch would cost more than the fit of a batch this size,
 // and one workgroup per context needs no load balance.  Invalid contexts, and any
 // wider than the declared bound, are flagged here.
 constexpr int kSmallBatch = 64;
@@ -2650,7 +2649,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_fit_small(FitArgs a) {
     }
 }
 
-// Wide contexts (class 3): the fewer there are, the more workgroups fit one together
+// Wide contexts (class large): the fewer there are, the more workgroups fit one together
 // (8, 4 or 2, while every context then has its own).  Under a cooperative launch every
 // workgroup is resident, which the waits for one another need; otherwise every context
 // takes one.  A group's workgroups are blockIdx values congruent mod 8, which the
