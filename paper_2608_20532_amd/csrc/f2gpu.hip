@@ -2945,7 +2945,7 @@ __device__ __forceinline__ uint8_t encode_one(const EncArgs& e, int c, int64_t q
 // ---------------------------------------------------------------------------
 // The lanes of a wavefront take its queries of up to 8 words at once; one after the
 // other those would cost more (1M queries on 80,000 contexts of up to 5 words, 0.05%
-// of the contexts with 5: 188 us per lane, 310 us with a wavefront for each of those).
+// of the contexts with 5: 125 us per lane, 310 us with a wavefront for each of those).
 constexpr int kLaneFW = 8;
 
 __device__ __forceinline__ uint32_t xor_lanes(uint32_t v) {

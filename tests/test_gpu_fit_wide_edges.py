@@ -1,0 +1,38 @@
+"""The wide fit at the edges of its words, blocks and groups, bit for bit against the CPU oracle: widths around 64-bit and
+128-column boundaries, rows around the 64-row blocks, full rank with rows left to check, and batches that give a context
+eight, four, two or one workgroup."""
+import numpy as np
+import pytest
+
+import parity
+import synth
+from test_gpu_parity import _large_context
+
+pytestmark = pytest.mark.gpu
+
+WIDTHS = [512, 513, 574, 575, 576, 639, 640, 703, 767, 1023, 1024, 1087, 2048, 4095]
+
+
+@pytest.mark.parametrize("count,more", [(1, 1), (2, 0), (9, 0), (40, 3), (70, 0), (140, 2)])
+def test_fit_wide_edges(require_gpu, count, more):
+    from paper_2608_20532_amd import f2gpu as f2
+    rng = np.random.default_rng(count)
+    n_bits, rows = [], []
+    for k in range(count):
+        n = WIDTHS[(k * 5 + count) % len(WIDTHS)]
+        m = [65, 64, 0, 1, 129, 63, 2, 200, 127][k % 9]
+        if k % 10 == 0 and n <= 640:
+            m = n + 1 + 90                                 # full rank, then a check of what is left
+        r = _large_context(rng, n, m, "pool" if k % 4 == 3 and m else "uniform")
+        if k % 5 == 1 and m > 3:                           # rows of the constant alone, the second contradictory
+            r[1:3, :] = 0
+            r[1:3, n // 64] = np.uint64(1) << np.uint64(n % 64)
+            r[2, -1] = 5
+        n_bits.append(n)
+        rows.append(r)
+    for k in range(more):                                  # and narrow contexts in the same batch
+        n_bits.insert(k, 30 + 100 * k)
+        rows.insert(k, _large_context(rng, 30 + 100 * k, 90, "uniform"))
+    wl = synth.custom_workload(n_bits, [len(r) for r in rows], rows)
+    ref = parity.oracle_fit_threads(wl.rows, wl.row_off, wl.n_bits)
+    parity.compare_fit(parity.gpu_fit(f2, wl.rows, wl.row_off, wl.n_bits), ref)
