@@ -2457,12 +2457,17 @@ __global__ __launch_bounds__(64 * kRegWaves) void k_fit_reg(FitArgs a) {
                                                     : lane < 8 ? reinterpret_cast<const int32_t*>(a.piv_off) + (lane - 6)
                                                                : reinterpret_cast<const int32_t*>(a.map_off) + (lane & 1));
     const uint32_t step = lane < 1 ? 4 : 8;
-    // The first half of the list is dealt to the workgroups in snake order; the tail, its
-    // smaller contexts, goes to whichever is free, which evens out what the first wavefronts'
-    // other contexts took: an eighth of a workgroup's part at a time through a counter in memory
-    // (about 5 ns per addition to one address: each wavefront's own additions, four contexts at
-    // a time, cost 20 us on 80,000 contexts), from there one at a time through LDS.
-    const int share = cnt / (2 * G) < kRegWaves ? kRegWaves : cnt / (2 * G);
+    // The list is dealt to the workgroups in snake order.  Of a long one only the first half is;
+    // the tail, its smaller contexts, goes to whichever is free, which evens out what the first
+    // wavefronts' other contexts took: an eighth of a workgroup's part at a time through a counter
+    // in memory (about 5 ns per addition to one address: each wavefront's own additions, four
+    // contexts at a time, cost 20 us on 80,000 contexts), from there one at a time through LDS.
+    // A chunk has to be worth the wait of 16 wavefronts for it: up to kTailFrom contexts per
+    // workgroup everything is dealt (contexts of 60 rows, 41 columns: 8,000 70 us with a tail
+    // in chunks of 2, 39 without; 17,000 77 and 63; 30,000 95 and 91; of 50-250 rows, 100-191
+    // columns: 22,000 469 and 473; 30,000 603 and 622).
+    constexpr int kTailFrom = 96;
+    const int share = cnt <= kTailFrom * G ? (cnt + G - 1) / G : cnt / (2 * G);
     const int tail = share * G < cnt ? share * G : cnt;
     const int chunk = (cnt - tail) / (8 * G) + 1;
     auto load = [&](int c) {
