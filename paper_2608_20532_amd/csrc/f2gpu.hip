@@ -3049,6 +3049,23 @@ __device__ __forceinline__ bool wide_ctx(const EncArgs& e, int c) {
     return c >= 0 && c < e.num_ctx && !(e.ctx_flags[c] & kBadCtx) && feat_words(e.n_bits[c]) > kLaneFW;
 }
 
+// the queries of the lanes in `todo` (context c, query q), a wavefront each; out is written in those lanes
+__device__ __forceinline__ uint8_t encode_each(const EncArgs& e, uint64_t todo, int c, int64_t q, Word2& out) {
+    uint8_t fl = 0;
+    for (; todo; todo &= todo - 1) {
+        const int j = ffs64(todo);
+        const int cj = __builtin_amdgcn_readlane(c, j);
+        uint64_t z0, z1;
+        const bool in = encode_wave(e, cj, static_cast<int64_t>(readlane64(static_cast<uint64_t>(q), j)), z0, z1);
+        if ((threadIdx.x & 63) == j) {
+            fl = ((e.ctx_flags[cj] & F2_CTX_CONTRADICTION) ? F2_Q_CTX_CONTRADICTORY : 0) | (in ? 0 : F2_Q_OUT_OF_SPAN);
+            out.x = in ? z0 : 0;
+            out.y = in ? z1 : 0;
+        }
+    }
+    return fl;
+}
+
 // one query per live lane (context c, query q), the wide ones a wavefront each (no lane may be inactive here)
 template <bool WIDE>
 __device__ __forceinline__ uint8_t encode_lanes(const EncArgs& e, bool live, int c, int64_t q, Word2& out) {
@@ -3056,33 +3073,50 @@ __device__ __forceinline__ uint8_t encode_lanes(const EncArgs& e, bool live, int
     const bool wide = WIDE && live && wide_ctx(e, c);
     if (live && !wide) fl = encode_one(e, c, q, out.x, out.y);
     if constexpr (WIDE) {
-        for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
-            const int j = ffs64(todo);
-            const int cj = __builtin_amdgcn_readlane(c, j);
-            uint64_t z0, z1;
-            const bool in = encode_wave(e, cj, static_cast<int64_t>(readlane64(static_cast<uint64_t>(q), j)), z0, z1);
-            if ((threadIdx.x & 63) == j) {
-                fl = ((e.ctx_flags[cj] & F2_CTX_CONTRADICTION) ? F2_Q_CTX_CONTRADICTORY : 0) | (in ? 0 : F2_Q_OUT_OF_SPAN);
-                out.x = in ? z0 : 0;
-                out.y = in ? z1 : 0;
-            }
-        }
+        const uint8_t fw = encode_each(e, __ballot(wide), c, q, out);
+        if (wide) fl = fw;
     }
     return fl;
 }
 
-// small batches that may hold wide contexts: qpw queries per wavefront, few enough
-// that the chip is full of wavefronts (each takes its wide queries one by one)
+// Small batches that may hold wide contexts.  The first lane_blocks workgroups take a query per
+// lane and leave the wide ones; in the others `parts` wavefronts look at the same 64 queries
+// and share out their wide ones, so many that the chip is full of wavefronts when all
+// are wide, and gone at once when none is.  (A wavefront that took 1-64 queries of
+// either kind left most of its lanes empty on narrow ones.  100,000 queries of 40 bits on 300
+// contexts, no width declared: 18.4 us so, 7.8 now, 7.6 where the widths are declared narrow; on
+// 20,000 contexts 24.7, 18.2 and 16.3; 50,000 queries on 96 contexts of 513-1,500 bits: 53 and 52.)
 constexpr int kWideWaves = 8192;  // eight per SIMD
-__global__ __launch_bounds__(kEncThreads) void k_encode_wide(EncArgs e, int qpw) {
+__global__ __launch_bounds__(kEncThreads) void k_encode_wide(EncArgs e, int lane_blocks, int parts) {
     const int lane = threadIdx.x & 63;
-    const int64_t q0 = (static_cast<int64_t>(blockIdx.x) * (kEncThreads / 64) + (threadIdx.x >> 6)) * qpw;
-    const int64_t q = q0 + lane;
-    const bool live = lane < qpw && q < e.nq;
+    const int b = static_cast<int>(blockIdx.x);
     Word2 out;
-    out.x = out.y = 0;
-    const uint8_t fl = encode_lanes<true>(e, live, live ? e.ctx_id[q] : -1, q, out);
-    if (!live) return;
+    if (b < lane_blocks) {
+        const int64_t q = static_cast<int64_t>(b) * kEncThreads + threadIdx.x;
+        if (q >= e.nq) return;
+        const int c = e.ctx_id[q];
+        if (wide_ctx(e, c)) return;
+        const uint8_t fl = encode_one(e, c, q, out.x, out.y);
+        *reinterpret_cast<Word2*>(e.words + 2 * q) = out;
+        e.qflags[q] = fl;
+        return;
+    }
+    // which of the 64 are wide: each of the workgroup's wavefronts looks at 16 of them
+    __shared__ uint16_t sWide[kEncThreads / 64];
+    const int wave = threadIdx.x >> 6, shares = parts / (kEncThreads / 64);
+    const int part = (b - lane_blocks) % shares * (kEncThreads / 64) + wave;
+    const int64_t q0 = static_cast<int64_t>((b - lane_blocks) / shares) * 64, q = q0 + lane;
+    const int c = q < e.nq ? e.ctx_id[q] : -1;
+    const uint64_t some = __ballot(lane / 16 == wave && wide_ctx(e, c));
+    if (lane == 0) sWide[wave] = static_cast<uint16_t>(some >> (16 * wave));
+    __syncthreads();
+    uint64_t all = 0;
+    for (int w = 0; w < kEncThreads / 64; ++w) all |= static_cast<uint64_t>(sWide[w]) << (16 * w);
+    const bool wide = (all >> lane) & 1ull;
+    const int rank = __popcll(all & ((1ull << lane) - 1));
+    const bool mine = wide && (rank & (parts - 1)) == part;
+    const uint8_t fl = encode_each(e, __ballot(mine), c, q, out);
+    if (!mine) return;
     *reinterpret_cast<Word2*>(e.words + 2 * q) = out;
     e.qflags[q] = fl;
 }
@@ -4845,13 +4879,15 @@ int encode_range(const f2_model* m, const int32_t* ctx_id, const uint64_t* x, in
     const int64_t blocks = (num_queries + kEncThreads - 1) / kEncThreads;
     if (blocks > 0x7fffffff) return F2_EINVAL;
     EncPlan p = encode_workspace(m->num_ctx, num_queries);
-    e.wide = m->max_n_bits < 0 || feat_words(m->max_n_bits) > kLaneFW;
+    e.wide = m->max_n_bits < 0 || m->max_n_bits >= 64 * kLaneFW;
     if (!p.sorted && e.wide) {
-        int qpw = 1;
-        while (qpw < 64 && num_queries / (2 * qpw) >= kWideWaves) qpw *= 2;
-        const int64_t per_block = static_cast<int64_t>(kEncThreads / 64) * qpw;
-        hipLaunchKernelGGL(k_encode_wide, dim3(static_cast<unsigned>((num_queries + per_block - 1) / per_block)),
-                           dim3(kEncThreads), 0, s, e, qpw);
+        constexpr int per_block = kEncThreads / 64;
+        int parts = 64;
+        while (parts > per_block && num_queries * parts / 128 >= kWideWaves) parts /= 2;
+        const int64_t wide_blocks = (num_queries + 63) / 64 * (parts / per_block);
+        if (blocks + wide_blocks > 0x7fffffff) return F2_EINVAL;
+        hipLaunchKernelGGL(k_encode_wide, dim3(static_cast<unsigned>(blocks + wide_blocks)), dim3(kEncThreads), 0, s, e,
+                           static_cast<int>(blocks), parts);
         return hipGetLastError() == hipSuccess ? F2_OK : F2_EDEVICE;
     }
     if (!p.sorted) {

@@ -45,3 +45,17 @@ def fit_call(f2, n_bits, m, seed=1, max_n_bits=None):
     def call():
         assert f2.f2_fit_batch(rows, rows.numel(), offd, model, ws, nb) == f2.F2_OK
     return call, model
+
+
+def encode_call(f2, model, ctx, x):
+    """An encode of queries x [nq, stride] (device tensors) against a fitted model, ready to be called."""
+    import torch
+    nq, stride = x.shape
+    words = torch.empty(nq, 2, dtype=torch.int64, device="cuda")
+    qf = torch.empty(nq, dtype=torch.uint8, device="cuda")
+    nb = f2.f2_encode_workspace_bytes(model, nq)
+    ws = f2.workspace(nb)
+
+    def call():
+        assert f2.f2_encode_batch(model, ctx, x, stride, nq, words, qf, ws, nb) == f2.F2_OK
+    return call
