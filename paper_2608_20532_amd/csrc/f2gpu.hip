@@ -185,13 +185,15 @@ __device__ __forceinline__ void write_bad_context(const FitArgs& a, const CtxDes
 // fit plan.  Contexts are validated (an invalid one gets rank 0 and its flag
 // here), assigned to the kernel of their class, and each class list is sorted
 // by an estimate of the elimination work, largest first:
-//   short: fw <= 3 and few rows, or rows x columns small   -> one wavefront
-//   long:  fw <= 3, rows x columns moderate                -> one wavefront beside many short
-//          ones, else kPivWaves wavefronts
-//   one:   fw = 4, likewise                                -> one wavefront with a larger basis
-//   group: fw <= 8, whatever is longer or wider            -> kPivWaves wavefronts
-//   large: fw > 8                                          -> large-context kernel
-// (which kernel takes the middle three depends on their numbers: piv_lists)
+//   short:    fw <= 3 and few rows, or rows x columns small  -> one wavefront
+//   long:     fw <= 3, rows x columns moderate               -> kPivWaves wavefronts, or one beside
+//             many short ones
+//   one long: fw = 4, likewise                               -> kPivWaves wavefronts, or one with a
+//             larger basis
+//   one:      fw = 4, few rows                               -> one wavefront with a larger basis
+//   group:    fw <= 8, whatever is longer or wider           -> kPivWaves wavefronts
+//   large:    fw > 8                                         -> large-context kernel
+// (which kernel takes the middle four depends on their numbers: piv_lists)
 // A class kernel with G workgroups deals its list out in stripes of G entries,
 // alternating direction from stripe to stripe, so that every workgroup gets a
 // similar share of the work and the longest contexts start first.  The sort is
@@ -208,17 +210,19 @@ constexpr int kPivMaxFW = 8;
 constexpr int kLongRows = 4096;  // contexts with more rows are the work of several wavefronts
 // One wavefront's time grows with rows x columns (each block of 64 rows is reduced against up to
 // `columns` records).  Up to kShortRows rows or kShortWork it is the better path in any batch
-// (8,000 contexts of 300 rows, 41 columns: 114 us, by four wavefronts 190); up to kLongWork it
-// ends before a batch of short contexts does (80,000 contexts of a corpus, 353 us with the
+// (8,000 contexts of 300 rows, 41 columns: 114 us, by four wavefronts 190; 20 among 100 small
+// ones, 181 columns of rank 126: of 300 rows 70 and 75 us, 350 78 and 85, 400 85 and 75, 570 100
+// and 94; 121 columns: 38 and 37, 42 and 36, 45 and 42, 52 and 48); up to kLongWork it
+// ends before a large batch of short contexts does (80,000 contexts of a corpus, 353 us with the
 // line at 65,536, 213 us at 131,072 and 275 us at 262,144, where the longest end last).
-constexpr int kShortRows = 256, kShortWork = 16384, kLongWork = 131072;
-enum { kClsShort = 0, kClsLong = 1, kClsOne = 2, kClsGroup = 3, kClsLarge = 4, kNumCls = 5 };
+constexpr int kShortRows = 320, kShortWork = 16384, kLongWork = 131072;
+enum { kClsShort = 0, kClsLong = 1, kClsOneLong = 2, kClsOne = 3, kClsGroup = 4, kClsLarge = 5, kNumCls = 6 };
 constexpr int kPivNext = 8;                 // plan word: next list position for the LDS-basis kernel
 constexpr int kRegNext = 9;                 // and for the shared tail of the one-wavefront kernel's list
 constexpr int kBarHead = 16;                // plan words kBarHead ..: progress of the wide kernel's workgroups (64 bits each)
 constexpr int kMaxMembers = 256;
 constexpr int kPlanHead = kBarHead + 2 * kMaxMembers;
-constexpr int kBuckets = 204;
+constexpr int kBuckets = 170;
 constexpr int kPlanBins = 1024;
 constexpr int kPlanThreads = 1024;  // one context per thread; one bin per thread in the scan
 static_assert(kNumCls * kBuckets <= kPlanBins && kPlanBins == kPlanThreads, "the scan gives one bin to each thread");
@@ -228,7 +232,8 @@ __device__ __forceinline__ int fit_class(const CtxDesc& ds, int long_rows = kLon
     if (fw > kPivMaxFW) return kClsLarge;
     const int64_t work = ds.m > kShortRows ? ds.m * (ds.n + 1) : 0;  // (m is at most 2^60)
     if (ds.m > long_rows || fw > kRegMaxFW + 1 || work > kLongWork) return kClsGroup;
-    return fw == kRegMaxFW + 1 ? kClsOne : work > kShortWork ? kClsLong : kClsShort;
+    if (fw == kRegMaxFW + 1) return ds.m > kShortRows ? kClsOneLong : kClsOne;
+    return work > kShortWork ? kClsLong : kClsShort;
 }
 
 // log-scale bucket (4 per octave) of rows x min(rows, d) x row words
@@ -2354,36 +2359,47 @@ struct RegQueue {
     int next;                 // next position of the workgroup's share
     int done;                 // the tail has ended
 };
-// Which kernel takes the long, one and group contexts: k_fit_reg, beside its short ones,
-// unless these are too few to hide behind or the others too many to be under way at once.
-// Where the short ones are too few, the long ones are group contexts, and k_fit_reg takes them
-// only if it has a workgroup for each
-// (1,000 contexts of 17-97 columns and 2,000 rows, all long or group: 166 us there, 97 us in
-// k_fit_piv; 1,000 of 201 columns and 240 rows, all one: 117 and 255 us).
+// Which kernel takes the long, one and group contexts.
+// - Where k_fit_reg has a workgroup for each, its first wavefronts fit them together: beside
+//   short contexts that end sooner, a long one by one wavefront would be the batch's time (4,000 contexts of 60
+//   rows, 41 columns and 20 of 4,000 rows, 31 columns: 67 us, with one wavefront for each of the 20 107).
+// - Else the long ones go to one wavefront each beside the short ones (1,000 long ones of 500 rows, 98 columns among 4,000:
+//   73 us, in k_fit_piv behind them 114), unless k_fit_piv holds all of them at once and the
+//   short ones are too few to fill k_fit_reg (400 of 4,000 rows, 31 columns among 1,600: 77 us there,
+//   117 beside them; a corpus of 7,000, the same question with 4,096 short ones or more: 203 and 150 us),
+//   or they are too many for the short ones to hide them (1,000 contexts of 17-97 columns and 2,000 rows: 166 us beside, 97 in k_fit_piv).
+// - Those of four words go singly with them (1,000 of 201 columns and 240 rows: 117 us, 255 in k_fit_piv).
+// - Of more group contexts than workgroups, k_fit_reg takes the largest where it is full of short ones anyway (a
+//   corpus of 200,000: 550 us, 620 with all of them in k_fit_piv), else none (600 of 301 columns: 144 us in k_fit_piv, where three workgroups share a compute unit).
 struct PivLists {
-    int short_lo, short_n, long_lo, long_n;      // k_fit_reg: by one wavefront each
-    int one_lo, one_n;                           // by its first wavefronts, singly
-    int group_lo, group_n, group_long;           // and together: of the group list, of the long list
-    int piv_group, piv_one, piv_long;            // k_fit_piv: how many of each, in this order
+    int short_lo, short_n, long_lo, long_n;            // k_fit_reg: by one wavefront each
+    int one_lo, one_n;                                 // by its first wavefronts, singly
+    int group_lo, group_n, chain_lo, chain_n;          // and together: of the group list, of the long lists
+    int piv_group_lo, piv_group, piv_one, piv_long;    // k_fit_piv: how many of each, in this order
 };
 __device__ __forceinline__ PivLists piv_lists(const FitArgs& a) {
     const int G = a.num_ctx < kRegGrid ? a.num_ctx : kRegGrid;  // k_fit_reg's workgroups
     PivLists p;
     p.short_lo = a.plan[kClsShort];
-    p.long_lo = a.plan[kClsLong];
-    p.one_lo = a.plan[kClsOne];
+    p.chain_lo = a.plan[kClsLong];
     p.group_lo = a.plan[kClsGroup];
-    p.short_n = p.long_lo - p.short_lo;
-    const int nl = p.one_lo - p.long_lo, no = p.group_lo - p.one_lo, ng = a.plan[kClsLarge] - p.group_lo;
-    const bool beside = nl <= p.short_n / 4;
-    const bool few = ng + (beside ? 0 : nl) <= G;
-    p.long_n = beside ? nl : 0;
-    p.one_n = beside || few ? no : 0;
-    p.group_n = few ? ng : 0;
-    p.group_long = few && !beside ? nl : 0;
+    const int four_lo = a.plan[kClsOneLong], one_lo = a.plan[kClsOne];
+    p.short_n = p.chain_lo - p.short_lo;
+    const int nl = four_lo - p.chain_lo, nf = one_lo - four_lo, no = p.group_lo - one_lo, ng = a.plan[kClsLarge] - p.group_lo;
+    const bool each = ng + nl + nf <= G, busy = p.short_n >= kRegWaves * G;
+    p.chain_n = each ? nl + nf : 0;
+    p.long_lo = p.chain_lo;  // (one list or the other)
+    const int rest = each ? 0 : nl;
+    const bool beside = rest == 0 || (rest <= p.short_n / 4 && (busy || rest > 3 * G));
+    p.group_n = !beside ? 0 : ng <= G ? ng : busy ? G : 0;
+    p.long_n = beside ? rest : 0;
+    p.one_lo = each ? one_lo : four_lo;
+    const int ones = each ? no : nf + no;
+    p.one_n = beside ? ones : 0;
+    p.piv_group_lo = p.group_lo + p.group_n;
     p.piv_group = ng - p.group_n;
-    p.piv_one = no - p.one_n;
-    p.piv_long = nl - p.long_n - p.group_long;
+    p.piv_one = ones - p.one_n;
+    p.piv_long = rest - p.long_n;
     return p;
 }
 
@@ -2401,7 +2417,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void k_fit_reg(FitArgs a) {
     const int g = static_cast<int>(blockIdx.x), G = static_cast<int>(gridDim.x);
     const PivLists pl = piv_lists(a);
     const int cnt = pl.long_n + pl.short_n;
-    const int groups = pl.group_n + pl.group_long;
+    const int groups = pl.group_n + pl.chain_n;
     const bool parted = g < groups || G - 1 - g < pl.one_n;
     if (!parted && cnt == 0) return;
     if (tid == 0) {
@@ -2420,7 +2436,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void k_fit_reg(FitArgs a) {
         __builtin_amdgcn_s_setprio(3);
         if (g < groups) {
             const int c = __builtin_amdgcn_readfirstlane(
-                a.plan[kPlanHead + (g < pl.group_n ? pl.group_lo + g : pl.long_lo + g - pl.group_n)]);
+                a.plan[kPlanHead + (g < pl.group_n ? pl.group_lo + g : pl.chain_lo + g - pl.group_n)]);
             const CtxDesc ds = readlane_desc(load_desc(a, c), 0);
             switch (feat_words(ds.n)) {
                 case 1: fit_ctx_piv<1, kPivWaves>(a, ds, sPart.piv, sync); break;
@@ -2587,7 +2603,7 @@ __global__ __launch_bounds__(kPivThreads, 3) void k_fit_piv(FitArgs a) {
     const int32_t* const order = a.plan + kPlanHead;
     BlockSync sync;
     for (int i = static_cast<int>(blockIdx.x); i < cnt;) {
-        const int c = __builtin_amdgcn_readfirstlane(i < g1   ? order[pl.group_lo + i]
+        const int c = __builtin_amdgcn_readfirstlane(i < g1   ? order[pl.piv_group_lo + i]
                                                      : i < g2 ? order[pl.one_lo + i - g1]
                                                               : order[pl.long_lo + i - g2]);
         int next = 0;

@@ -32,3 +32,46 @@ def test_time_of_8000_contexts(f2):
     half, whole = (timing.fit_call(f2, np.full(C, 40), np.full(C, 60))[0] for C in (4000, 8000))
     t_half, t_whole = timing.medians([half, whole])
     assert t_whole < 2.1 * t_half, (t_half, t_whole)
+
+
+def _mix(rng, shapes):
+    """(n, m) of every context, shuffled, from (count, widths, rows) entries."""
+    n = np.concatenate([rng.choice(w, size=c) for c, w, _ in shapes])
+    m = np.concatenate([rng.choice(r, size=c) for c, _, r in shapes])
+    p = rng.permutation(len(n))
+    return n[p].astype(np.int32), m[p]
+
+
+SHORT, LONG, FOUR_LONG, FOUR, GROUP = ([3, 30, 62], [2, 20, 40]), ([20, 60], [400, 700]), ([193, 255], [321, 400]), ([192, 250], [30, 320]), ([300, 40], [130, 4100])
+
+
+@pytest.mark.parametrize("short,long,four_long,four,group", [
+    (0, 65, 0, 0, 0), (0, 0, 65, 0, 0), (300, 100, 100, 3, 56), (300, 100, 100, 3, 57), (300, 70, 190, 9, 2), (1200, 280, 0, 5, 3),
+    (1200, 280, 9, 300, 3), (4096, 250, 5, 5, 5), (4096, 250, 5, 5, 1), (4095, 250, 2, 5, 5), (4095, 769, 2, 0, 1), (4096, 4, 0, 2, 257), (4096, 260, 3, 300, 257),
+    (4095, 4, 0, 2, 257), (100, 200, 0, 300, 60)])
+def test_division_at_its_lines(f2, short, long, four_long, four, group):
+    """A workgroup for each long and group context, or one too few; long ones beside short ones or behind them; more
+    group contexts than workgroups."""
+    rng = np.random.default_rng(short + 3 * long + 5 * four_long + 7 * four + 11 * group)
+    n, m = _mix(rng, [(c, *k) for c, k in zip((short, long, four_long, four, group), (SHORT, LONG, FOUR_LONG, FOUR, GROUP))])
+    off = np.concatenate([[0], np.cumsum(m * ((n.astype(np.int64) + 64) // 64 + 2))])
+    rows = rng.integers(0, 2 ** 63, size=max(int(off[-1]), 1), dtype=np.uint64) * np.uint64(2) + np.uint64(1)
+    ref = parity.oracle_fit_threads(rows, off, n)
+    parity.compare_fit(parity.gpu_fit(f2, rows, off, n), ref)
+
+
+def test_time_of_a_few_long_contexts(f2):
+    """20 long contexts beside 4,000 short ones take little more than by themselves (67 us against 59; 107 us with one
+    wavefront for each), and 400 beside 1,600 no more than one batch after the other (77 against 24 + 62; 117 us so)."""
+    few, alone, mixed, short, long = (
+        timing.fit_call(f2, np.repeat([40, 30], c), np.repeat([60, 4000], c))[0] for c in ((4000, 20), (0, 65), (1600, 400), (1600, 0), (0, 400)))
+    t = timing.medians([few, alone, mixed, short, long])
+    assert t[0] < 1.45 * t[1], t
+    assert t[2] < 1.15 * (t[3] + t[4]), t
+
+
+def test_time_of_long_contexts_of_four_words(f2):
+    """65 contexts of 221 columns and 500 rows take little more than 64, which have a workgroup of eight wavefronts each
+    (measured 129 us; 166 us with one wavefront for each)."""
+    t = timing.medians([timing.fit_call(f2, np.full(C, 220), np.full(C, 500))[0] for C in (64, 65)])
+    assert t[1] < 1.2 * t[0], t
