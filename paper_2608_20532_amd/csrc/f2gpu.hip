@@ -1310,6 +1310,15 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
 // pivots, with the block they come from, in the context's pivots area; both are final
 // outputs only later.
 //
+// A round takes rows of one batch alone, so a stream that adds a few rows per block would cost
+// a round for each few rows.  Whoever completes a chunk of 32 list rows that holds the
+// ends of four batches or more reduces its rows among themselves, into the chunk's place in the context's
+// basis area, before its block counts as done: a batch like any other, with the pivots and the span of
+// those it replaces.  Every member comes to the same from the list's entries, and reads the chunk
+// there; at the end the merged chunks are copied into the list.  One new row per
+// block of 64: 128 contexts of 601 columns and rank 256 6.8 ms, 52 ms round by round; 8 of
+// 2,048 columns and rank 1,024 22 and 201 ms.  (Chunks of 16: 6.2 and 22 ms, and dense contexts 3% slower.)
+//
 //   (1) block reduce, 32 basis rows (half a batch) per round, with Four-Russians tables
 //       (the method of Arlazarov, Dinic, Kronrod and Faradzev): four rows give a
 //       16-entry LDS table of their XOR combinations, and a row's four bits at their
@@ -1340,6 +1349,9 @@ constexpr int kWdRows = 64;                   // rows per block
 constexpr int kWdMaxBlocks = (1 << 19) - 2;   // block numbers in a pivot's tag; contexts of more rows take one member
 constexpr int kWdBar = 1 << 30;               // progress values from here on: past the blocks
 constexpr int kPivLast = 1 << 12;             // the last pivot of a batch
+constexpr int kPivMerged = 1 << 13;           // the first pivot of a merged chunk (in LDS only)
+constexpr int kChunk = 32;                    // list rows that are merged where they came in small batches
+constexpr int kChunkEnds = 4;                 // from as many batch ends within the chunk
 constexpr int kRowPitch = 33;                 // elimination: 16-byte units per row in LDS (33: no bank conflicts down a column)
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -1360,6 +1372,7 @@ struct WideShared {
     int more;                          // a pending row holds a bit: another panel follows
     int any[2];                        // nonzero residuals in the block (alternating)
     int nrows, next;                   // list length; every block below `next` is done
+    int merged;                        // the list holds merged chunks
     int timeout;                       // a wait of this context gave up
 };
 
@@ -1454,6 +1467,30 @@ __device__ __forceinline__ int take_entries(WideShared& L, const int32_t* ent, i
     }
 }
 
+// one wavefront: does chunk q (whole) hold many small batches?  (The flags inside a chunk are as published until it is marked.)
+__device__ __forceinline__ bool chunk_small(const WideShared& L, int q) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t ends = __ballot(lane < kChunk - 1 && (L.piv[kChunk * q + (lane & (kChunk - 1))] & kPivLast));
+    return __popcll(ends) >= kChunkEnds;
+}
+// one wavefront: the chunks that list rows from .. to - 1 completed become a batch of their own where they are merged
+__device__ __forceinline__ void mark_chunks(WideShared& L, int from, int to) {
+    const int lane = threadIdx.x & 63;
+    wave_sync();
+    for (int q = from / kChunk; q < to / kChunk; ++q) {
+        if (!chunk_small(L, q)) continue;
+        if (lane < kChunk) {
+            uint16_t* e = &L.piv[kChunk * q + lane];
+            *e = static_cast<uint16_t>((*e & (kPivLast - 1)) | (lane == 0 ? kPivMerged : lane == kChunk - 1 ? kPivLast : 0));
+        }
+        if (lane == 0) {
+            if (q) L.piv[kChunk * q - 1] |= kPivLast;
+            L.merged = 1;
+        }
+        wave_sync();
+    }
+}
+
 // the basis rows of one round: wavefront t takes rows 4 t .. 4 t + 3 of it
 struct RoundRows {
     u32x4 f[2];  // two words per lane of row 2 i + h in half wavefront h
@@ -1492,11 +1529,12 @@ struct BlockRows {
 // rows [start, start + cnt) of the list: half `half` of the batch of K rows at pos; cnt 0: none
 struct Round {
     int pos, K, half, cnt;
+    int merged;  // a merged chunk: its rows are in Y
 };
 
 // reduce the block by list rows pos .. nrows - 1 (pos < nrows starts a batch)
-__device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_t X, int W, int fw, int pos, int nrows,
-                                            BlockRows& b) {
+__device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_t X, __amdgpu_buffer_rsrc_t Y, int W, int fw,
+                                            int pos, int nrows, BlockRows& b) {
     const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5;
     const int t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int voff = 16 * (2 * j < fw ? j : 0);
@@ -1507,13 +1545,13 @@ __device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_
         return static_cast<int>(L.piv[i < nrows ? i : nrows - 1]);
     };
     auto after = [&](const Round& r, int e) {
-        if (r.half == 0 && r.K > 32) return Round{r.pos, r.K, 1, r.K - 32};
+        if (r.half == 0 && r.K > 32) return Round{r.pos, r.K, 1, r.K - 32, 0};
         const int p0 = r.pos + r.K;
-        if (p0 >= nrows) return Round{p0, 0, 0, 0};
+        if (p0 >= nrows) return Round{p0, 0, 0, 0, 0};
         const uint64_t last = __ballot(p0 + lane < nrows && (e & kPivLast));
         const int left = nrows - p0 < 64 ? nrows - p0 : 64;
         const int k = last ? ffs64(last) + 1 : 64, K = k < left ? k : left;
-        return Round{p0, K, 0, K < 32 ? K : 32};
+        return Round{p0, K, 0, K < 32 ? K : 32, __builtin_amdgcn_readfirstlane(e) & kPivMerged};
     };
     // always the same number of loads (past the list, its last row): the wait for one
     // round's rows then leaves the next round's in flight
@@ -1521,8 +1559,9 @@ __device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_
         const int start = r.cnt ? r.pos + 32 * r.half : nrows - 1, cnt = r.cnt ? r.cnt : 1;
         // the first rows of a batch may share a cache line with the batch before it, read
         // before they were written
-        if (r.half == 0 && t == 0) load_rows<true>(X, W, fw, start, cnt, t, voff, lane, rr);
-        else load_rows<false>(X, W, fw, start, cnt, t, voff, lane, rr);
+        const __amdgpu_buffer_rsrc_t S = r.merged ? Y : X;
+        if (r.half == 0 && t == 0) load_rows<true>(S, W, fw, start, cnt, t, voff, lane, rr);
+        else load_rows<false>(S, W, fw, start, cnt, t, voff, lane, rr);
     };
     // absent rows are never selected, and entry 0 of an absent table must be zero
     auto store_tables = [&](int buf, const RoundRows& r) {
@@ -1610,7 +1649,7 @@ __device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_
     // `nn` fetched in this step.  Each SIMD holds one wavefront that builds the next tables
     // before it applies the current ones and one that builds them after, so that the
     // table reads of the one (LDS bandwidth) overlap the other's latencies.
-    Round cur = after(Round{pos, 0, 0, 0}, entry_after(Round{pos, 0, 0, 0}));
+    Round cur = after(Round{pos, 0, 0, 0, 0}, entry_after(Round{pos, 0, 0, 0, 0}));
     Round nxt = after(cur, entry_after(cur));
     Round nn = after(nxt, entry_after(nxt));
     RoundRows ra, rb;
@@ -1825,12 +1864,13 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
     const uint64_t tmask = top_mask(n, fw), cbit = 1ull << (n & 63);
     uint64_t* Xp = a.tables + ds.bo;
     const __amdgpu_buffer_rsrc_t X = dev_rsrc(Xp, static_cast<uint32_t>(8 * d * W));
+    const __amdgpu_buffer_rsrc_t Y = dev_rsrc(a.basis + ds.bo, static_cast<uint32_t>(8 * d * W));  // merged chunks
     int32_t* ent = a.pivots + ds.po;
     constexpr long long kNone = 0x7fffffffffffffffll;
     const int nblk = m > static_cast<int64_t>(kWdMaxBlocks) * kWdRows ? 0x7fffffff : static_cast<int>((m + kWdRows - 1) / kWdRows);
     if (nblk > kWdMaxBlocks) {  // block numbers past the tags: one member, which reads no tags
         if (g != 0) {
-            if (tid == 0) put_progress(prog, g, seq, kWdBar + 2);
+            if (tid == 0) put_progress(prog, g, seq, kWdBar + 3);
             return;
         }
         G = 1;
@@ -1858,14 +1898,16 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
         L.next = 0;
         L.any[0] = L.any[1] = 0;
         L.more = 0;
+        L.merged = 0;
     }
     __syncthreads();
     int nrows = 0;
     int ncon = 0;
     long long firstc = kNone;
     int flip = 0;
-    // one pass of this loop: a block of this member (phase 0), then, below full rank, a
-    // batch of the list (phase 1) to be reduced by the later ones
+    // one pass of this loop: a block of this member (phase 0), a chunk of the list that its new
+    // rows completed, to be merged (phase 2), then, below full rank, a batch of the list
+    // (phase 1) to be reduced by the later ones
     int phase = 0, bpos = 0, bidx = 0, bK = 0;
     int64_t blk = g;
     bool full = false;
@@ -1897,20 +1939,43 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                 if (!ok && lane == 0) L.timeout = 1;
             }
             if (bar) open = 0x7fffffff;
-            if (bar != 2) {
+            if (bar < 2) {
                 const int k = take_entries(L, ent, nrows, d, open);
+                mark_chunks(L, nrows, k);
                 if (lane == 0) L.nrows = k;
             }
         }
         __syncthreads();
         nrows = __builtin_amdgcn_readfirstlane(L.nrows);
     };
+    auto end_block = [&]() {
+        blk += G;
+        if (G > 1 && tid == 0) put_progress(prog, g, seq, static_cast<int>((blk - g) / G));
+        if (blk < blocks) load_block(blk, nextb);
+    };
     for (;;) {
         if (phase == 0 && (blk >= blocks || nrows >= d)) {
+            bpos = 0;
             if (G > 1) {  // every member past its blocks: the list is complete
                 __syncthreads();
                 if (tid == 0) put_progress(prog, g, seq, kWdBar + 1);
                 wait_for(0, 1);
+            }
+            if (__builtin_amdgcn_readfirstlane(L.merged)) {  // merged chunks to their places in the list (the outputs go where they are)
+                const uint64_t* const Yp = a.basis + ds.bo;
+                for (int q = 0; q < nrows / kChunk; ++q) {
+                    if (!(L.piv[kChunk * q] & kPivMerged)) continue;
+                    if (q % G == g)
+                        for (int i = kChunk * q * W + tid; i < kChunk * (q + 1) * W; i += kWdThreads)
+                            put_dev(Xp + i, __hip_atomic_load(Yp + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                }
+                __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                for (int q = tid; q < nrows / kChunk; q += kWdThreads) L.piv[kChunk * q] &= ~kPivMerged;
+                if (G > 1) {
+                    if (tid == 0) put_progress(prog, g, seq, kWdBar + 2);
+                    wait_for(0, 2);
+                }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // no line of the list read before it was whole is read again
             phase = 1;
@@ -1954,7 +2019,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
             if (!found) break;
         }
         BlockRows b;
-        const int nb = phase == 1 ? bK : (m - blk * kWdRows < kWdRows ? static_cast<int>(m - blk * kWdRows) : kWdRows);
+        const int nb = phase ? bK : (m - blk * kWdRows < kWdRows ? static_cast<int>(m - blk * kWdRows) : kWdRows);
         if (phase == 0) {
             b = nextb;
         } else {
@@ -1970,10 +2035,23 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
 #pragma unroll
         for (int i = 0; i < kWdPairs; ++i) b.acc[i] &= vm & (8 * wave + 2 * i + h < nb ? ~0u : 0u);
         b.y &= lane < 8 && 8 * wave + lane < nb ? ~0u : 0u;
+        // phase 2: a row without its own pivot's bit selects the later rows of the chunk alone
+        auto flip_own = [&]() {
+#pragma unroll
+            for (int i = 0; i < kWdPairs; ++i) {
+                const int r = 8 * wave + 2 * i + h;
+                const int p = L.piv[bpos + (r < nb ? r : 0)] & (kPivLast - 1);
+                const uint32_t bit = r < nb && (p >> 7) == j ? 1u << (p & 31) : 0u;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) b.acc[i][k] ^= ((p >> 5) & 3) == k ? bit : 0u;
+            }
+        };
+        if (phase == 2) flip_own();
         if (phase == 0 && G > 1) {  // what the other members have added meanwhile
             if (wave == 0) {
                 const int open = lowest_open(prog, G, g, seq, static_cast<int>(blk));
                 const int k = take_entries(L, ent, nrows, d, open);
+                mark_chunks(L, nrows, k);
                 if (lane == 0) {
                     L.nrows = k;
                     L.next = open;
@@ -1982,12 +2060,13 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
             __syncthreads();
             nrows = __builtin_amdgcn_readfirstlane(L.nrows);
         }
-        int pos = phase == 1 ? bpos + bK : 0;
+        int pos = phase == 1 ? bpos + bK : phase == 2 ? bpos : 0;
+        const int past = bpos + bK;  // phase 2: the end of the chunk
         int open = G > 1 && phase == 0 ? __builtin_amdgcn_readfirstlane(L.next) : 0x7fffffff;
         bool anynz = false;
         for (;;) {
             if (pos < nrows) {
-                wide_reduce(L, X, W, fw, pos, nrows, b);
+                wide_reduce(L, X, Y, W, fw, pos, phase == 2 ? past : nrows, b);
                 pos = nrows;
             } else {
 #pragma unroll
@@ -1995,7 +2074,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
             }
 #pragma unroll
             for (int i = 0; i < kWdPairs; ++i) b.acc[i] &= vm;  // (the lanes past the row collected other words)
-            if (phase == 1) break;
+            if (phase) break;
             bool mine = false;
 #pragma unroll
             for (int i = 0; i < kWdPairs; ++i) mine |= any4(b.acc[i]);
@@ -2009,6 +2088,29 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
             open = 0x7fffffff;
             if (pos == nrows) break;
             b.y &= lane < 8 ? ~0u : 0u;
+            // (a chunk merged since the block was reduced by its first rows: whole, which these no longer select)
+            const int q = pos / kChunk;
+            if (__builtin_amdgcn_readfirstlane(L.piv[kChunk * q]) & kPivMerged) pos = kChunk * q;
+        }
+        if (phase == 2) {
+            flip_own();
+#pragma unroll
+            for (int i = 0; i < kWdPairs; ++i) {
+                const int r = 8 * wave + 2 * i + h;
+                const int off = (bpos + r) * W * 8 + 16 * j;
+                if (r < nb) {
+                    if (2 * j + 1 < fw) __builtin_amdgcn_raw_buffer_store_b128(b.acc[i], Y, off, 0, kDevScope);
+                    else if (2 * j < fw) __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{b.acc[i].x, b.acc[i].y}, Y, off, 0, kDevScope);
+                }
+            }
+            const int r = 8 * wave + lane;
+            if (lane < 8 && r < nb) __builtin_amdgcn_raw_buffer_store_b128(b.y, Y, ((bpos + r) * W + fw) * 8, 0, kDevScope);
+            __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (wave == 0) mark_chunks(L, bpos, nrows);
+            __syncthreads();
+            phase = 0;
+            end_block();
+            continue;
         }
         if (phase == 1) {  // fully reduced rows to their final places
 #pragma unroll
@@ -2051,6 +2153,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
             continue;
         }
         // (3) elimination in stream order on panels
+        const int before = nrows;
         uint64_t ins = 0;
         if (anynz && nrows < d) {
             u32x4* const Rm = &L.tab[0][0][0];                         // [64][kRowPitch]
@@ -2255,9 +2358,14 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
         }
         if (tid == 0) L.nrows = nrows;
         __syncthreads();
-        blk += G;
-        if (G > 1 && tid == 0) put_progress(prog, g, seq, static_cast<int>((blk - g) / G));
-        if (blk < blocks) load_block(blk, nextb);
+        const int q = before / kChunk;  // (further chunks that the new rows completed hold them alone)
+        if (nrows / kChunk > q && chunk_small(L, q)) {
+            bpos = kChunk * q;
+            bK = kChunk;
+            phase = 2;
+        } else {
+            end_block();
+        }
     }
     // outputs
     const int64_t po = ds.po, mo = ds.mo;
@@ -2281,8 +2389,8 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (G > 1) {
-        if (tid == 0) put_progress(prog, g, seq, kWdBar + 2);
-        wait_for(0, 2);
+        if (tid == 0) put_progress(prog, g, seq, kWdBar + 3);
+        wait_for(0, 3);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (full) {
