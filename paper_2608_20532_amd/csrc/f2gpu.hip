@@ -1533,8 +1533,9 @@ struct Round {
 };
 
 // reduce the block by list rows pos .. nrows - 1 (pos < nrows starts a batch)
-__device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_t X, __amdgpu_buffer_rsrc_t Y, int W, int fw,
+__device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_t X, __amdgpu_buffer_rsrc_t Y, int W, int d,
                                             int pos, int nrows, BlockRows& b) {
+    const int fw = W - F2_Y_WORDS;
     const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5;
     const int t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int voff = 16 * (2 * j < fw ? j : 0);
@@ -1557,10 +1558,11 @@ __device__ __forceinline__ void wide_reduce(WideShared& L, __amdgpu_buffer_rsrc_
     // round's rows then leaves the next round's in flight
     auto fetch = [&](const Round& r, RoundRows& rr) {
         const int start = r.cnt ? r.pos + 32 * r.half : nrows - 1, cnt = r.cnt ? r.cnt : 1;
-        // the first rows of a batch may share a cache line with the batch before it, read
-        // before they were written
+        // The first rows of a batch may share a cache line with the batch before it, read
+        // before they were written; so may the last two rows that the area holds with the first
+        // of the area behind it, another context's, which another group may read on the same die.
         const __amdgpu_buffer_rsrc_t S = r.merged ? Y : X;
-        if (r.half == 0 && t == 0) load_rows<true>(S, W, fw, start, cnt, t, voff, lane, rr);
+        if ((r.half == 0 && t == 0) || start + cnt > d - 2) load_rows<true>(S, W, fw, start, cnt, t, voff, lane, rr);
         else load_rows<false>(S, W, fw, start, cnt, t, voff, lane, rr);
     };
     // absent rows are never selected, and entry 0 of an absent table must be zero
@@ -2066,7 +2068,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
         bool anynz = false;
         for (;;) {
             if (pos < nrows) {
-                wide_reduce(L, X, Y, W, fw, pos, phase == 2 ? past : nrows, b);
+                wide_reduce(L, X, Y, W, d, pos, phase == 2 ? past : nrows, b);
                 pos = nrows;
             } else {
 #pragma unroll
@@ -2782,7 +2784,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_fit_small(FitArgs a) {
 // (8, 4 or 2, while every context then has its own).  Under a cooperative launch every
 // workgroup is resident, which the waits for one another need; otherwise every context
 // takes one.  A group's workgroups are blockIdx values congruent mod 8, which the
-// dispatcher places on one die (a shared L2 for the list they all read).
+// dispatcher places on one die (a shared L2 for the list they all read): for speed alone, the
+// list is exchanged at device scope.
 __global__ __launch_bounds__(kWdThreads) void k_fit_wide(FitArgs a) {
     __shared__ WideShared U;
     const int nl = a.plan[kClsLarge + 1] - a.plan[kClsLarge];

@@ -36,3 +36,24 @@ def test_fit_wide_edges(require_gpu, count, more):
     wl = synth.custom_workload(n_bits, [len(r) for r in rows], rows)
     ref = parity.oracle_fit_threads(wl.rows, wl.row_off, wl.n_bits)
     parity.compare_fit(parity.gpu_fit(f2, wl.rows, wl.row_off, wl.n_bits), ref)
+
+
+@pytest.mark.parametrize("count", [5, 20, 70])
+def test_full_rank_of_neighbours_of_other_widths(require_gpu, count):
+    """Adjacent contexts of different widths at full rank (their areas meet within a cache line), groups of eight, four and
+    two workgroups; some a few columns short of it, so that the whole basis is written."""
+    from paper_2608_20532_amd import f2gpu as f2
+    rng = np.random.default_rng(count)
+    widths = ([641, 1023, 702, 1100, 831] * count)[:count] if count < 50 else rng.integers(600, 700, size=count)
+    n_bits, rows = [], []
+    for k, n in enumerate(widths):
+        m = int(n) + 1 + [70, 0, 130, -1, 64, -3, 200][k % 7]
+        r = _large_context(rng, int(n), m, "uniform")
+        if k % 3 == 1:
+            r[-2, -1] ^= np.uint64(3)
+        n_bits.append(int(n))
+        rows.append(r)
+    wl = synth.custom_workload(n_bits, [len(r) for r in rows], rows)
+    ref = parity.oracle_fit_threads(wl.rows, wl.row_off, wl.n_bits)
+    parity.compare_fit(parity.gpu_fit(f2, wl.rows, wl.row_off, wl.n_bits), ref)
+    assert (ref.rank == np.asarray(n_bits) + 1).any()
