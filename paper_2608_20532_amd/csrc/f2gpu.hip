@@ -219,9 +219,9 @@ constexpr int kShortRows = 320, kShortWork = 16384, kLongWork = 131072;
 enum { kClsShort = 0, kClsLong = 1, kClsOneLong = 2, kClsOne = 3, kClsGroup = 4, kClsLarge = 5, kNumCls = 6 };
 constexpr int kPivNext = 8;                 // plan word: next list position for the LDS-basis kernel
 constexpr int kRegNext = 9;                 // and for the shared tail of the one-wavefront kernel's list
-constexpr int kBarHead = 16;                // plan words kBarHead ..: progress of the wide kernel's workgroups (64 bits each)
+constexpr int kBarHead = 16;                // plan words kBarHead ..: progress of the wide kernel's workgroups
 constexpr int kMaxMembers = 256;
-constexpr int kPlanHead = kBarHead + 2 * kMaxMembers;
+constexpr int kPlanHead = kBarHead + kMaxMembers;
 constexpr int kBuckets = 170;
 constexpr int kPlanBins = 1024;
 constexpr int kPlanThreads = 1024;  // one context per thread; one bin per thread in the scan
@@ -266,7 +266,7 @@ __device__ __forceinline__ PlanView plan_view(const FitArgs& a) {
 // what the fit kernels count in, and where they meet
 __device__ __forceinline__ void plan_clear(const FitArgs& a) {
     const int tid = threadIdx.x;
-    if (tid < 2 * kMaxMembers) a.plan[kBarHead + tid] = 0;
+    if (tid < kMaxMembers) a.plan[kBarHead + tid] = 0;
     if (tid < 2) a.plan[kPivNext + tid] = 0;
 }
 
@@ -377,18 +377,6 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(FitArgs a, int bl
         const int k = P.key[c];
         if (k >= 0) P.order[atomicAdd(&sBin[k], 1)] = static_cast<int32_t>(c);
     }
-}
-
-// the i-th context of classes cls .. cls_last (adjacent lists) dealt to taker g
-// of G (snake order), or -1; by default the takers are the workgroups
-__device__ __forceinline__ int class_ctx(const FitArgs& a, int cls, int i, int cls_last = -1, int G = -1, int g = -1) {
-    const int lo = a.plan[cls], cnt = a.plan[(cls_last < 0 ? cls : cls_last) + 1] - lo;
-    if (G < 0) {
-        G = static_cast<int>(gridDim.x);
-        g = static_cast<int>(blockIdx.x);
-    }
-    const int64_t e = static_cast<int64_t>(i) * G + ((i & 1) ? G - 1 - g : g);
-    return e < cnt ? a.plan[kPlanHead + lo + static_cast<int>(e)] : -1;
 }
 
 // ---------------------------------------------------------------------------
@@ -1419,22 +1407,20 @@ __device__ __forceinline__ void put_dev32(uint32_t* p, uint32_t v) {
 // v with the rows of `rows` flipped where row q's bit is set (a column per lane)
 __device__ __forceinline__ uint64_t xor_sel(uint64_t v, int q, uint64_t rows) { return xor_and(v, bit_mask(v, q), rows); }
 
-// progress of a group's members: (context sequence number, blocks done, or kWdBar + k
-// past barrier k), one 64-bit word per member, stored only by it
-__device__ __forceinline__ void put_progress(uint64_t* prog, int g, int seq, int done) {
-    __hip_atomic_store(prog + g, (static_cast<uint64_t>(static_cast<uint32_t>(seq)) << 32) | static_cast<uint32_t>(done),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// progress of a group's members: blocks done, or kWdBar + k past barrier k; one word per member,
+// cleared by the plan and stored only by it.  A group fits one context (k_fit_wide), so the
+// words serve once.
+__device__ __forceinline__ void put_progress(int32_t* prog, int g, int done) {
+    __hip_atomic_store(prog + g, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // one wavefront: the lowest block not known to be done (own blocks below blk are)
-__device__ __forceinline__ int lowest_open(const uint64_t* prog, int G, int g, int seq, int blk) {
+__device__ __forceinline__ int lowest_open(const int32_t* prog, int G, int g, int blk) {
     const int lane = threadIdx.x & 63;
     int nb = 0x7fffffff;
     if (lane < G && lane != g) {
-        const uint64_t v = __hip_atomic_load(prog + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int s = static_cast<int>(v >> 32), dn = static_cast<int>(v);
-        if (s < seq) nb = lane;
-        else if (s == seq && dn < kWdBar) nb = lane + G * dn;
+        const int dn = __hip_atomic_load(prog + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (dn < kWdBar) nb = lane + G * dn;
     }
     if (lane == g) nb = blk;
     for (int o = 4; o > 0; o >>= 1) {  // G <= 8
@@ -1855,9 +1841,8 @@ __device__ __forceinline__ void check_rows(const FitArgs& a, const CtxDesc& ds, 
     }
 }
 
-// member g of the G workgroups that fit context ds together; seq numbers the group's contexts from 1
-__device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds, WideShared& L, int G, int g, uint64_t* prog,
-                                             int seq) {
+// member g of the G workgroups that fit context ds together
+__device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds, WideShared& L, int G, int g, int32_t* prog) {
     const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = ds.c, n = ds.n, d = n + 1, fw = feat_words(n), W = fw + F2_Y_WORDS, cw = n >> 6;
@@ -1871,10 +1856,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
     constexpr long long kNone = 0x7fffffffffffffffll;
     const int nblk = m > static_cast<int64_t>(kWdMaxBlocks) * kWdRows ? 0x7fffffff : static_cast<int>((m + kWdRows - 1) / kWdRows);
     if (nblk > kWdMaxBlocks) {  // block numbers past the tags: one member, which reads no tags
-        if (g != 0) {
-            if (tid == 0) put_progress(prog, g, seq, kWdBar + 3);
-            return;
-        }
+        if (g != 0) return;
         G = 1;
     }
     const int64_t blocks = (m + kWdRows - 1) / kWdRows;
@@ -1926,13 +1908,11 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                     if (bar) {
                         bool behind = false;
                         if (lane < G && lane != g) {
-                            const uint64_t v = __hip_atomic_load(prog + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            const int s = static_cast<int>(v >> 32);
-                            behind = s < seq || (s == seq && static_cast<int>(v) < kWdBar + bar);
+                            behind = __hip_atomic_load(prog + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < kWdBar + bar;
                         }
                         ok = __ballot(behind) == 0;
                     } else {
-                        open = lowest_open(prog, G, g, seq, static_cast<int>(until));
+                        open = lowest_open(prog, G, g, static_cast<int>(until));
                         ok = open >= until;
                     }
                     if (ok) break;
@@ -1952,7 +1932,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
     };
     auto end_block = [&]() {
         blk += G;
-        if (G > 1 && tid == 0) put_progress(prog, g, seq, static_cast<int>((blk - g) / G));
+        if (G > 1 && tid == 0) put_progress(prog, g, static_cast<int>((blk - g) / G));
         if (blk < blocks) load_block(blk, nextb);
     };
     for (;;) {
@@ -1960,7 +1940,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
             bpos = 0;
             if (G > 1) {  // every member past its blocks: the list is complete
                 __syncthreads();
-                if (tid == 0) put_progress(prog, g, seq, kWdBar + 1);
+                if (tid == 0) put_progress(prog, g, kWdBar + 1);
                 wait_for(0, 1);
             }
             if (__builtin_amdgcn_readfirstlane(L.merged)) {  // merged chunks to their places in the list (the outputs go where they are)
@@ -1975,7 +1955,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
                 __syncthreads();
                 for (int q = tid; q < nrows / kChunk; q += kWdThreads) L.piv[kChunk * q] &= ~kPivMerged;
                 if (G > 1) {
-                    if (tid == 0) put_progress(prog, g, seq, kWdBar + 2);
+                    if (tid == 0) put_progress(prog, g, kWdBar + 2);
                     wait_for(0, 2);
                 }
             }
@@ -2051,7 +2031,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
         if (phase == 2) flip_own();
         if (phase == 0 && G > 1) {  // what the other members have added meanwhile
             if (wave == 0) {
-                const int open = lowest_open(prog, G, g, seq, static_cast<int>(blk));
+                const int open = lowest_open(prog, G, g, static_cast<int>(blk));
                 const int k = take_entries(L, ent, nrows, d, open);
                 mark_chunks(L, nrows, k);
                 if (lane == 0) {
@@ -2391,7 +2371,7 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (G > 1) {
-        if (tid == 0) put_progress(prog, g, seq, kWdBar + 3);
+        if (tid == 0) put_progress(prog, g, kWdBar + 3);
         wait_for(0, 3);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -2795,11 +2775,12 @@ __global__ __launch_bounds__(kWdThreads) void k_fit_wide(FitArgs a) {
         for (int k = 2; k <= 8 && k * nl <= nwg && nwg % (8 * k) == 0; k *= 2) G = k;
     const int x = static_cast<int>(blockIdx.x), idx = x / 8;
     const int g = idx % G, grp = (x % 8) + 8 * (idx / G), ngrp = nwg / G;
-    uint64_t* prog = reinterpret_cast<uint64_t*>(a.plan + kBarHead) + (G > 1 ? grp * G : 0);
+    // the list is dealt to the groups in snake order: one context each where G > 1 (G * nl <= nwg)
     for (int i = 0;; ++i) {
-        const int c = __builtin_amdgcn_readfirstlane(class_ctx(a, kClsLarge, i, -1, ngrp, grp));
-        if (c < 0) break;
-        fit_ctx_wide(a, readlane_desc(load_desc(a, c), 0), U, G, g, prog, i + 1);
+        const int64_t e = static_cast<int64_t>(i) * ngrp + ((i & 1) ? ngrp - 1 - grp : grp);
+        if (e >= nl) break;
+        const int c = __builtin_amdgcn_readfirstlane(a.plan[kPlanHead + a.plan[kClsLarge] + static_cast<int>(e)]);
+        fit_ctx_wide(a, readlane_desc(load_desc(a, c), 0), U, G, g, a.plan + kBarHead + (G > 1 ? grp * G : 0));
     }
 }
 
