@@ -57,3 +57,27 @@ def test_full_rank_of_neighbours_of_other_widths(require_gpu, count):
     ref = parity.oracle_fit_threads(wl.rows, wl.row_off, wl.n_bits)
     parity.compare_fit(parity.gpu_fit(f2, wl.rows, wl.row_off, wl.n_bits), ref)
     assert (ref.rank == np.asarray(n_bits) + 1).any()
+
+
+def test_more_blocks_than_the_tags_hold(require_gpu):
+    """A context of more blocks than a list entry can name is one workgroup's: 2^19 blocks of rows that repeat seven, then
+    a new row and a contradictory one, against the oracle's fit of the rows that differ."""
+    import torch
+    import oracle
+    from paper_2608_20532_amd import f2gpu as f2
+    rng = np.random.default_rng(9)
+    n, m = 512, (1 << 19) * 64 + 100
+    few = _large_context(rng, n, 8, "uniform")
+    last = few[3:4].copy()
+    last[0, -1] ^= np.uint64(1)
+    rows = torch.empty((m, few.shape[1]), dtype=torch.int64, device="cuda")
+    rows.copy_(parity.to_dev(few[:7])[torch.arange(m, device="cuda") % 7])
+    rows[m - 40] = parity.to_dev(few[7])
+    rows[m - 2] = parity.to_dev(last[0])
+    wl = synth.custom_workload([n], [9], [np.concatenate([few, last])])
+    ref = parity.oracle_fit_threads(wl.rows, wl.row_off, wl.n_bits)
+    assert ref.rank[0] == 8 and ref.first_contra[0] == 8
+    ref.first_contra[0] = m - 2
+    model = f2.fit(rows.reshape(-1), torch.tensor([0, rows.numel()], device="cuda"), np.array([n], np.int32))
+    torch.cuda.synchronize()
+    parity.compare_fit(model, ref)
