@@ -212,10 +212,11 @@ constexpr int kLongRows = 4096;  // contexts with more rows are the work of seve
 // `columns` records).  Up to kShortRows rows or kShortWork it is the better path in any batch
 // (8,000 contexts of 300 rows, 41 columns: 114 us, by four wavefronts 190; 20 among 100 small
 // ones, 181 columns of rank 126: of 300 rows 70 and 75 us, 350 78 and 85, 400 85 and 75, 570 100
-// and 94; 121 columns: 38 and 37, 42 and 36, 45 and 42, 52 and 48); up to kLongWork it
+// and 94; 121 columns: 38 and 37, 42 and 36, 45 and 42, 52 and 48; 31 columns, 570 rows: 20 and
+// 18, 800 rows 24 and 20); up to kLongWork it
 // ends before a large batch of short contexts does (80,000 contexts of a corpus, 353 us with the
 // line at 65,536, 213 us at 131,072 and 275 us at 262,144, where the longest end last).
-constexpr int kShortRows = 320, kShortWork = 16384, kLongWork = 131072;
+constexpr int kShortRows = 320, kShortWork = 20480, kLongWork = 131072;
 enum { kClsShort = 0, kClsLong = 1, kClsOneLong = 2, kClsOne = 3, kClsGroup = 4, kClsLarge = 5, kNumCls = 6 };
 constexpr int kPivNext = 8;                 // plan word: next list position for the LDS-basis kernel
 constexpr int kRegNext = 9;                 // and for the shared tail of the one-wavefront kernel's list
@@ -2451,21 +2452,28 @@ struct RegQueue {
 };
 // Which kernel takes the long, one and group contexts.
 // - Where k_fit_reg has a workgroup for each, its first wavefronts fit them together: beside
-//   short contexts that end sooner, a long one by one wavefront would be the batch's time (4,000 contexts of 60
-//   rows, 41 columns and 20 of 4,000 rows, 31 columns: 67 us, with one wavefront for each of the 20 107).
-// - Else the long ones go to one wavefront each beside the short ones (1,000 long ones of 500 rows, 98 columns among 4,000:
-//   73 us, in k_fit_piv behind them 114), unless k_fit_piv holds all of them at once and the
-//   short ones are too few to fill k_fit_reg (400 of 4,000 rows, 31 columns among 1,600: 77 us there,
-//   117 beside them; a corpus of 7,000, the same question with 4,096 short ones or more: 203 and 150 us),
-//   or they are too many for the short ones to hide them (1,000 contexts of 17-97 columns and 2,000 rows: 166 us beside, 97 in k_fit_piv).
+//   short contexts that end sooner, a long one by one wavefront would be the batch's time
+//   (4,000 contexts of 60 rows, 41 columns and 20 of 4,000 rows, 31 columns: 67 us, with one
+//   wavefront for each of the 20 107).
+// - Else the long ones go to one wavefront each beside the others, if four-word contexts, the longest
+//   chains of one wavefront, run there anyway and k_fit_reg is full (3,000 contexts of 60-250 columns, 180 of
+//   them long, 819 of four words: 295 us, in k_fit_piv 385; a corpus of 7,000: 150 and 203), or
+//   if they are more than k_fit_piv holds at once (1,000 of 500 rows, 98 columns among 4,000: 73
+//   us, in k_fit_piv behind them 114).  Otherwise they would end last (300 of 1,300 rows, 98
+//   columns among 8,000: 143 us beside them, 81 in k_fit_piv), also where the short ones are too few
+//   (1,000 contexts of 17-97 columns and 2,000 rows: 166 and 97 us).
 // - Those of four words go singly with them (1,000 of 201 columns and 240 rows: 117 us, 255 in k_fit_piv).
-// - Of more group contexts than workgroups, k_fit_reg takes the largest where it is full of short ones anyway (a
-//   corpus of 200,000: 550 us, 620 with all of them in k_fit_piv), else none (600 of 301 columns: 144 us in k_fit_piv, where three workgroups share a compute unit).
+// - Of more group contexts than workgroups, up to twice as many, k_fit_reg takes the largest where it is
+//   full anyway (a corpus of 200,000, 384 of them: 550 us, 620 with all in k_fit_piv), else none (600
+//   of 301 columns: 144 us in k_fit_piv, where three workgroups share a compute unit; 7,400 among 15,000:
+//   970 and 797 us).
+// - A few short ones go to k_fit_piv with the rest (500 contexts of 17-97 columns, 20 rows a
+//   column, 75 of them short: 53 us, 70 with the short ones before the others).
 struct PivLists {
     int short_lo, short_n, long_lo, long_n;            // k_fit_reg: by one wavefront each
     int one_lo, one_n;                                 // by its first wavefronts, singly
     int group_lo, group_n, chain_lo, chain_n;          // and together: of the group list, of the long lists
-    int piv_group_lo, piv_group, piv_one, piv_long;    // k_fit_piv: how many of each, in this order
+    int piv_group_lo, piv_group, piv_one, piv_long, piv_short;  // k_fit_piv: how many of each, in this order
 };
 __device__ __forceinline__ PivLists piv_lists(const FitArgs& a) {
     const int G = a.num_ctx < kRegGrid ? a.num_ctx : kRegGrid;  // k_fit_reg's workgroups
@@ -2476,12 +2484,12 @@ __device__ __forceinline__ PivLists piv_lists(const FitArgs& a) {
     const int four_lo = a.plan[kClsOneLong], one_lo = a.plan[kClsOne];
     p.short_n = p.chain_lo - p.short_lo;
     const int nl = four_lo - p.chain_lo, nf = one_lo - four_lo, no = p.group_lo - one_lo, ng = a.plan[kClsLarge] - p.group_lo;
-    const bool each = ng + nl + nf <= G, busy = p.short_n >= kRegWaves * G;
+    const bool each = ng + nl + nf <= G, busy = p.short_n + kPivWaves * (nf + no) >= kRegWaves * G;
     p.chain_n = each ? nl + nf : 0;
     p.long_lo = p.chain_lo;  // (one list or the other)
     const int rest = each ? 0 : nl;
-    const bool beside = rest == 0 || (rest <= p.short_n / 4 && (busy || rest > 3 * G));
-    p.group_n = !beside ? 0 : ng <= G ? ng : busy ? G : 0;
+    const bool beside = rest == 0 || (rest <= p.short_n / 4 && (rest > 3 * G || (busy && nf + no > 0)));
+    p.group_n = !beside ? 0 : ng <= G ? ng : busy && ng <= 2 * G ? G : 0;
     p.long_n = beside ? rest : 0;
     p.one_lo = each ? one_lo : four_lo;
     const int ones = each ? no : nf + no;
@@ -2490,6 +2498,8 @@ __device__ __forceinline__ PivLists piv_lists(const FitArgs& a) {
     p.piv_group = ng - p.group_n;
     p.piv_one = ones - p.one_n;
     p.piv_long = rest - p.long_n;
+    p.piv_short = !beside && p.short_n <= (ng + nl + nf + no) / 4 ? p.short_n : 0;
+    p.short_n -= p.piv_short;
     return p;
 }
 
@@ -2689,13 +2699,14 @@ __global__ __launch_bounds__(kPivThreads, 3) void k_fit_piv(FitArgs a) {
     __shared__ PivShared S;
     __shared__ int sNext;
     const PivLists pl = piv_lists(a);
-    const int g1 = pl.piv_group, g2 = g1 + pl.piv_one, cnt = g2 + pl.piv_long;
+    const int g1 = pl.piv_group, g2 = g1 + pl.piv_one, g3 = g2 + pl.piv_long, cnt = g3 + pl.piv_short;
     const int32_t* const order = a.plan + kPlanHead;
     BlockSync sync;
     for (int i = static_cast<int>(blockIdx.x); i < cnt;) {
         const int c = __builtin_amdgcn_readfirstlane(i < g1   ? order[pl.piv_group_lo + i]
                                                      : i < g2 ? order[pl.one_lo + i - g1]
-                                                              : order[pl.long_lo + i - g2]);
+                                                     : i < g3 ? order[pl.long_lo + i - g2]
+                                                              : order[pl.short_lo + i - g3]);
         int next = 0;
         if (threadIdx.x == 0) next = atomicAdd(&a.plan[kPivNext], 1) + static_cast<int>(gridDim.x);
         const CtxDesc ds = readlane_desc(load_desc(a, c), 0);

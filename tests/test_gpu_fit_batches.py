@@ -48,7 +48,8 @@ SHORT, LONG, FOUR_LONG, FOUR, GROUP = ([3, 30, 62], [2, 20, 40]), ([20, 60], [40
 @pytest.mark.parametrize("short,long,four_long,four,group", [
     (0, 65, 0, 0, 0), (0, 0, 65, 0, 0), (300, 100, 100, 3, 56), (300, 100, 100, 3, 57), (300, 70, 190, 9, 2), (1200, 280, 0, 5, 3),
     (1200, 280, 9, 300, 3), (4096, 250, 5, 5, 5), (4096, 250, 5, 5, 1), (4095, 250, 2, 5, 5), (4095, 769, 2, 0, 1), (4096, 4, 0, 2, 257), (4096, 260, 3, 300, 257),
-    (4095, 4, 0, 2, 257), (100, 200, 0, 300, 60)])
+    (4095, 4, 0, 2, 257), (100, 200, 0, 300, 60),
+    (40, 300, 20, 3, 60), (96, 300, 20, 3, 60), (1700, 280, 3, 600, 3), (1690, 280, 3, 599, 3), (4096, 4, 0, 2, 513), (0, 260, 0, 0, 1)])
 def test_division_at_its_lines(f2, short, long, four_long, four, group):
     """A workgroup for each long and group context, or one too few; long ones beside short ones or behind them; more
     group contexts than workgroups."""
@@ -62,12 +63,23 @@ def test_division_at_its_lines(f2, short, long, four_long, four, group):
 
 def test_time_of_a_few_long_contexts(f2):
     """20 long contexts beside 4,000 short ones take little more than by themselves (67 us against 59; 107 us with one
-    wavefront for each), and 400 beside 1,600 no more than one batch after the other (77 against 24 + 62; 117 us so)."""
-    few, alone, mixed, short, long = (
-        timing.fit_call(f2, np.repeat([40, 30], c), np.repeat([60, 4000], c))[0] for c in ((4000, 20), (0, 65), (1600, 400), (1600, 0), (0, 400)))
-    t = timing.medians([few, alone, mixed, short, long])
+    wavefront for each), and 400 beside 1,600 or 8,000 no more than one batch after the other (77 against 24 + 62, 94 against 38 + 65; 117 and 138 us so)."""
+    few, alone, mixed, short, long, many, shorts = (
+        timing.fit_call(f2, np.repeat([40, 30], c), np.repeat([60, 4000], c))[0]
+        for c in ((4000, 20), (0, 65), (1600, 400), (1600, 0), (0, 400), (8000, 400), (8000, 0)))
+    t = timing.medians([few, alone, mixed, short, long, many, shorts])
     assert t[0] < 1.45 * t[1], t
     assert t[2] < 1.15 * (t[3] + t[4]), t
+    assert t[5] < 1.15 * (t[6] + t[4]), t
+
+
+def test_time_of_a_few_short_contexts(f2):
+    """75 short contexts among 425 long ones take little more than the long ones alone (54 us against 52; 68 us with the
+    short ones in a kernel before the others)."""
+    n = np.random.default_rng(500).integers(40, 98, 425)
+    n2 = np.concatenate([n, np.full(75, 24)])
+    t = timing.medians([timing.fit_call(f2, k, 20 * k)[0] for k in (n, n2)])
+    assert t[1] < 1.2 * t[0], t
 
 
 def test_time_of_long_contexts_of_four_words(f2):
