@@ -3185,20 +3185,35 @@ __device__ __forceinline__ uint8_t encode_each(const EncArgs& e, uint64_t todo, 
     return fl;
 }
 
-// One query per live lane (context c, query q), the wide ones a wavefront each (no lane may be inactive here), but for
-// those of (nearly) full rank where a wavefront holds many: their lanes gather columns of
-// the same map side by side, and read the few parity-check rows together.  A million queries on 100
+// Wide queries of (nearly) full rank are a lane's each where a wavefront holds many: their lanes gather
+// columns of the same map side by side, and read the few parity-check rows together.  A million queries on 100
 // contexts, wavefront each / lane each: 600 bits at full rank 1.04 / 0.52 ms, 16 parity-check rows
 // 1.33 / 0.69; 3,000 bits 2.55 / 1.62, 16 rows 2.86 / 2.55, 32 rows 3.32 / 3.72.  A lane's chain is 8 words' trips to a
 // wavefront's 1 (times the queries): some 14 queries of 600 bits, 21 of 1,500.
 constexpr int kLaneParity = 16, kLaneParityMin = 16;
+
+// whether this lane's query (of context c, if live) is a wavefront's (no lane may be inactive here)
+__device__ __forceinline__ bool for_wavefront(const EncArgs& e, bool live, int c) {
+    const bool wide = live && wide_ctx(e, c);
+    const bool few = wide && e.n_bits[c] + 1 - e.rank[c] <= kLaneParity;
+    return wide && !(__popcll(__ballot(few)) >= kLaneParityMin && few);
+}
+
+// One query per live lane (context c, query q), the wide ones a wavefront each (no lane may be inactive here).
+// With share >= 0 only the wide ones share * kWideShare on, kWideShare of them, and with share 0 the
+// others too; `live` then says which.
+constexpr int kWideShare = 8;
 template <bool WIDE>
-__device__ __forceinline__ uint8_t encode_lanes(const EncArgs& e, bool live, int c, int64_t q, Word2& out) {
+__device__ __forceinline__ uint8_t encode_lanes(const EncArgs& e, bool& live, int c, int64_t q, Word2& out, int share = -1) {
     uint8_t fl = 0;
-    bool wide = WIDE && live && wide_ctx(e, c);
+    bool wide = false;
     if constexpr (WIDE) {
-        const bool few = wide && e.n_bits[c] + 1 - e.rank[c] <= kLaneParity;
-        if (__popcll(__ballot(few)) >= kLaneParityMin) wide = wide && !few;
+        wide = for_wavefront(e, live, c);
+        if (share >= 0) {
+            const int rank = __popcll(__ballot(wide) & ((1ull << (threadIdx.x & 63)) - 1));
+            live = live && (wide ? rank / kWideShare == share : share == 0);
+            wide = wide && live;
+        }
     }
     if (live && !wide) fl = encode_one(e, c, q, out.x, out.y);
     if constexpr (WIDE) {
@@ -3287,6 +3302,7 @@ constexpr int kSortMaxBins = 8192;
 constexpr int kSortMaxBinsLarge = 40000;  // 160,004 bytes of LDS histogram: up to two of 80,000 contexts per bin
 constexpr int64_t kWindowQueries = int64_t{1} << 23;
 
+constexpr int kRestMore = 26;  // (a chunk of 2^30 queries has 2^24 groups)
 struct SortArgs {
     int32_t nb;       // bins, the last one for out-of-range context ids
     int32_t bin_shift;  // 2^bin_shift contexts per bin
@@ -3299,7 +3315,8 @@ struct SortArgs {
     int32_t regroup;  // 1: each chunk of kRegroupChunk positions regrouped by context (k_enc_regroup)
     int32_t staged;   // 1: k_encode_sorted stages the wavefronts' contexts; 0: every position per lane
     uint64_t* rest;   // [ceil(nq / 64)] positions the staged pass left to the second pass (bit per lane; set for the listed groups only)
-    int32_t* rest_list;   // [ceil(nq / 64)] the 64-position groups with such positions, in no order
+    int32_t* rest_list;   // [ceil(nq / 64)] the 64-position groups with such positions, in no order;
+                          // from bit kRestMore on, how many wavefronts more share its wide queries
     int32_t* rest_count;  // [1] entries of rest_list (cleared by the count)
 };
 
@@ -3838,9 +3855,13 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_sorted(EncArgs e, SortAr
         wave_sync();  // the stage is rewritten for the next context
     }
     const uint64_t left = __ballot(!done);  // lanes of further or wider contexts: second pass
-    if (left && (threadIdx.x & 63) == 0) {  // a few percent of the groups (the second pass reads only these)
-        s.rest[i >> 6] = left;
-        s.rest_list[atomicAdd(s.rest_count, 1)] = static_cast<int32_t>(i >> 6);
+    if (left) {  // a few percent of the groups (the second pass reads only these)
+        const int n = e.wide ? __popcll(__ballot(for_wavefront(e, !done, qc.y))) : 0;
+        const int more = n > kWideShare ? (n - 1) / kWideShare : 0;  // further shares of wide queries
+        if ((threadIdx.x & 63) == 0) {
+            s.rest[i >> 6] = left;
+            s.rest_list[atomicAdd(s.rest_count, 1)] = static_cast<int32_t>(i >> 6) | (more << kRestMore);
+        }
     }
     if (!done || !live) return;
     *reinterpret_cast<Word2*>(e.words + 2 * static_cast<int64_t>(qc.x)) = out;
@@ -3855,14 +3876,18 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_sorted(EncArgs e, SortAr
 // per lane.  A fixed grid whose wavefronts take the listed groups in turn: a grid
 // over every position would launch (and allocate the stage for) a workgroup per
 // 256 positions, almost all of them idle (1.2 against 0.42 ms on 100M queries).
+// A group's wide queries are a wavefront's each, kWideShare of them in this wavefront and the rest shared
+// out: a large batch may hold a few such groups, and 64 queries one after the other would be the
+// kernel's time (3M queries on 3,000 narrow contexts and 20 of 700 bits at rank 560: 1,090 us so, 650 now, 742 with
+// a lane for each).
 constexpr int kRestStageLanes = 1;
 constexpr int kRestCtxPerWave = 64;  // contexts of a wavefront considered for the stage (all of them)
 constexpr int kRestGrid = 2048;     // workgroups of the listed-group pass (100M queries: 0.50 ms; 1,024: 0.54)
 
-// one wavefront: the lanes of bits among positions i0 .. i0 + 63
+// one wavefront: the lanes of bits among positions i0 .. i0 + 63 (of the wide queries one share)
 template <bool WIDE>
 __device__ __forceinline__ void rest_group(const EncArgs& e, const SortArgs& s, uint64_t* st, int64_t i0,
-                                           uint64_t bits) {
+                                           uint64_t bits, int share) {
     const int lane = threadIdx.x & 63;
     const int64_t i = i0 + lane;
     const bool live = i < e.nq && ((bits >> lane) & 1ull);
@@ -3870,12 +3895,12 @@ __device__ __forceinline__ void rest_group(const EncArgs& e, const SortArgs& s, 
     const int2 qc = live ? s.perm[i] : make_int2(0, 0);
     const uint64_t* xq = e.x + static_cast<int64_t>(live ? qc.x : 0) * e.stride;
     uint64_t xv[4] = {0, 0, 0, 0};
-    if (live) load_x4(e, xq, xv);
+    if (live && share == 0) load_x4(e, xq, xv);
     Word2 out;
     out.x = out.y = 0;
     uint8_t fl = 0;
     bool done = !live, lane_path = false;
-    for (int k = 0; k < kRestCtxPerWave; ++k) {
+    for (int k = 0; k < (share == 0 ? kRestCtxPerWave : 0); ++k) {
         const uint64_t todo = __ballot(!done && !lane_path);
         if (!todo) break;
         const int c0 = __builtin_amdgcn_readlane(qc.y, ffs64(todo));
@@ -3902,9 +3927,10 @@ __device__ __forceinline__ void rest_group(const EncArgs& e, const SortArgs& s, 
         }
         wave_sync();  // the stage is rewritten for the next context
     }
-    const uint8_t lf = encode_lanes<WIDE>(e, !done, qc.y, qc.x, out);
-    if (!done) fl = lf;
-    if (!live) return;
+    bool mine = !done;
+    const uint8_t lf = encode_lanes<WIDE>(e, mine, qc.y, qc.x, out, share);
+    if (mine) fl = lf;
+    if (!mine && !(live && done)) return;
     *reinterpret_cast<Word2*>(e.words + 2 * static_cast<int64_t>(qc.x)) = out;
     if (fl) e.qflags[qc.x] = fl;
 }
@@ -3917,8 +3943,21 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_rest(EncArgs e, SortArgs
     const int cnt = *s.rest_count;
     const int waves = static_cast<int>(gridDim.x) * (kEncThreads / 64);
     for (int k = static_cast<int>(blockIdx.x) * (kEncThreads / 64) + wave; k < cnt; k += waves) {
-        const int g = __builtin_amdgcn_readfirstlane(s.rest_list[k]);
-        rest_group<WIDE>(e, s, st, static_cast<int64_t>(g) * 64, s.rest[g]);
+        const int g = __builtin_amdgcn_readfirstlane(s.rest_list[k]) & ((1 << kRestMore) - 1);
+        rest_group<WIDE>(e, s, st, static_cast<int64_t>(g) * 64, s.rest[g], 0);
+    }
+    if constexpr (WIDE) {  // the further shares; 64 (group, share) pairs looked at together
+        const int lane = threadIdx.x & 63;
+        const int64_t pairs = static_cast<int64_t>(cnt) * (64 / kWideShare - 1);
+        for (int64_t k0 = static_cast<int64_t>(blockIdx.x) * (kEncThreads / 64) + wave; k0 < pairs; k0 += 64 * static_cast<int64_t>(waves)) {
+            const int64_t k = k0 + static_cast<int64_t>(lane) * waves;
+            const int share = k < pairs ? 1 + static_cast<int>(k / cnt) : 0;
+            const int v = share ? s.rest_list[k % cnt] : 0;
+            for (uint64_t todo = __ballot(share && (v >> kRestMore) >= share); todo; todo &= todo - 1) {
+                const int l = ffs64(todo), g = __builtin_amdgcn_readlane(v, l) & ((1 << kRestMore) - 1);
+                rest_group<true>(e, s, st, static_cast<int64_t>(g) * 64, s.rest[g], __builtin_amdgcn_readlane(share, l));
+            }
+        }
     }
 }
 
@@ -3928,7 +3967,7 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_rest(EncArgs e, SortArgs
 template <bool WIDE>
 __global__ __launch_bounds__(kEncThreads) void k_encode_lanes(EncArgs e, SortArgs s) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kEncThreads + threadIdx.x;
-    const bool live = i < e.nq;
+    bool live = i < e.nq;
     const int2 qc = live ? s.perm[i] : make_int2(0, -1);
     Word2 out;
     const uint8_t fl = encode_lanes<WIDE>(e, live, qc.y, qc.x, out);

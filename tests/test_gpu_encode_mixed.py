@@ -112,3 +112,24 @@ def test_time_of_large_batches_of_wide_queries(f2):
         calls.append(timing.encode_call(f2, model, ctx, x))
     small, large = timing.medians(calls)
     assert large < 1.25 * small * 1_000_000 / 150_000, (small, large)
+
+
+def test_time_of_a_large_batch_with_few_wide_queries(f2):
+    """400,000 queries on 3,000 narrow contexts and 20 of 700 bits: at rank 560 of those (a wavefront for each of their queries)
+    two times what they take at full rank (a lane each; measured 227 us against 114 us; 700 us with 64 such queries one after the other)."""
+    import torch
+    n, nq = np.concatenate([np.full(3000, 40), np.full(20, 700)]), 400_000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    ctx = torch.randint(0, len(n), (nq,), generator=g, device="cuda", dtype=torch.int32)
+    x = torch.randint(-2 ** 63, 2 ** 63 - 1, (nq, 11), generator=g, device="cuda", dtype=torch.int64)
+    wide = ctx[:, None] >= 3000
+    x &= torch.where(wide, torch.full_like(x, -1), torch.zeros_like(x)) | (torch.arange(11, device="cuda") == 0) * (2 ** 40 - 1)
+    x[:, 10] &= 2 ** 60 - 1
+    calls = []
+    for m in (np.where(n == 40, 60, 760), np.where(n == 40, 60, 560)):
+        fit, model = timing.fit_call(f2, n, m)
+        fit()
+        calls.append(timing.encode_call(f2, model, ctx, x))
+    full, part = timing.medians(calls)
+    assert part < 3.5 * full, (full, part)
