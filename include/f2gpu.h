@@ -15,8 +15,9 @@
  * Conventions shared by every entry point
  * ---------------------------------------
  *  - Every pointer argument is DEVICE memory allocated and owned by the
- *    caller unless its name ends in _host.  The library allocates nothing and
- *    keeps no state between calls beyond a per-device cache of how many
+ *    caller unless its name ends in _host.  The library allocates nothing (the
+ *    HIP runtime holds scratch memory of its own for two kernels that spill
+ *    registers, as it does for any such kernel) and keeps no state between calls beyond a per-device cache of how many
  *    workgroups of the wide-context fit can be resident at once (queried on
  *    first use) and the fixed per-device plan array of f2_fit_batch_noalloc
  *    (a file-scope device array, part of the loaded library); concurrent
@@ -92,7 +93,8 @@ enum {
  *                             priority (capacity (n+1)(fw+2) words; rows past
  *                             the rank are scratch, their content unspecified)
  *   pivots[piv_off[c] ...]    rank[c] storage bit indices, same order
- *                             (capacity n+1 entries)
+ *                             (capacity n+1 entries; those past the rank are
+ *                             scratch as well)
  *   maps[map_off[c] ...]      the canonical dense map: n+1 columns of 2 words,
  *                             column j = storage bit j; column p = z_p for every
  *                             pivot p and 0 for every other column (one linear
@@ -103,8 +105,11 @@ enum {
  *                             plus e_p for every pivot p whose basis row holds
  *                             bit f (t rows, within the basis capacity).  phi lies
  *                             in the span exactly when every row has even overlap
- *                             with it.  When t > rank the region is not written
- *                             and encoding reduces phi by the basis rows instead.
+ *                             with it.  When t > rank there are none and encoding
+ *                             reduces phi by the basis rows instead.  What lies
+ *                             past the t rows (all of the region when t > rank) is
+ *                             scratch: the fit of a context of more than 8 feature
+ *                             words writes there, its content is unspecified
  *   rank[c], ctx_flags[c], n_contra[c] (rows flagged contradictory),
  *   first_contra_row[c] (index within the context's segment, -1 if none).
  * For a contradictory context the stored map is defined by the rows kept in

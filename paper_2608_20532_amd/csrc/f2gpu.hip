@@ -16,16 +16,15 @@
 //      keeps the basis fully reduced), and is inserted.
 // A plan kernel validates the contexts and sorts them into classes by feature
 // words and length, each class list in decreasing order of estimated work.
-// Contexts of up to 8 words keep a pivot-indexed basis in LDS: those of up to 4
-// words that are not too long are fitted by one wavefront each, the others by
-// four together, which reduce four blocks at once; both run side by side in one
-// kernel.  Wider contexts take up to eight workgroups each, with the basis in
-// HBM and the rows it needs staged in LDS.
+// Contexts of up to 8 words keep a pivot-indexed basis in LDS: short ones of up to 4
+// words are fitted by one wavefront each, the others by four together, which
+// reduce four blocks at once; as far as one can hide behind the other they run side by
+// side in one kernel, else the second kind in a kernel behind it.  Wider contexts take up
+// to eight workgroups each, with the basis in HBM and the rows it needs staged in LDS.
 //
 // Encode (Sec. 2.3): T(phi) is the XOR of the canonical map columns over the
 // set bits of phi = [x | 1]; the support test checks phi against the
-// parity-check rows of the free (non-pivot) columns, which a prepare kernel
-// derives from the fitted basis.
+// parity-check rows of the free (non-pivot) columns, which the fit writes.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -1085,7 +1084,9 @@ __device__ __forceinline__ void piv_backsub(PivShared& S, int d, int fw) {
 
 // the wavefronts of a workgroup, or some of them, wait for one another
 struct BlockSync {
-    static constexpr bool kFar = true;  // registers for four of the widest records
+    // registers for four of the widest records at a time (k_fit_piv: 168, and 24 values that spill
+    // in its outputs and between contexts)
+    static constexpr bool kFar = true;
     __device__ __forceinline__ void operator()() { __syncthreads(); }
 };
 // NW wavefronts of a larger workgroup: a count in LDS that each adds to once per wait.  Every
@@ -1327,11 +1328,13 @@ __device__ __forceinline__ void fit_ctx_piv(const FitArgs& a, const CtxDesc& ds,
 //
 // 64 contexts, n = 4095, 8,192 rows: 10.27 ms with a basis kept fully reduced (groups
 // of 4 workgroups exchanging partial sums), 4.25 ms with 16 wavefronts of 4 rows and
-// loads one round ahead, 3.36 ms.  A round of 32 basis rows takes about 4,200 cycles:
+// loads one round ahead, 3.33 ms.  A round of 32 basis rows takes about 4,200 cycles:
 // 2,700 of LDS bandwidth (a table lookup moves 512 bytes for four basis rows) and 2,000
 // of VALU issue that two wavefronts per SIMD do not overlap further.
 // ---------------------------------------------------------------------------
-constexpr int kWdWaves = 8;  // 256 registers each: loads two rounds ahead
+// 256 registers a wavefront: loads two rounds ahead.  The rounds keep all of theirs; 142 more
+// values spill around them, in the code of a block and of its outputs (440 bytes of scratch a lane).
+constexpr int kWdWaves = 8;
 constexpr int kWdPairs = 64 / kWdWaves / 2;  // pairs of block rows per wavefront
 constexpr int kWdThreads = 64 * kWdWaves;
 constexpr int kWdRows = 64;                   // rows per block
@@ -2437,9 +2440,9 @@ __device__ __forceinline__ void fit_ctx_wide(const FitArgs& a, const CtxDesc& ds
 
 // One workgroup of kRegWaves wavefronts per compute unit, each wavefront fitting its own
 // contexts in its own LDS region, largest first.  The first kPivWaves of a workgroup start
-// with contexts that need more: the group ones, one per workgroup, fitted by the four
-// together (their LDS regions are one PivShared), then those of four feature words, one
-// each in a larger region.  These are chains of 100-200 us that once ran in a kernel of their
+// with contexts that need more: the group ones and the long ones, one per workgroup, fitted by the
+// four together (their LDS regions are one PivShared), then those of four feature words, one
+// each in a larger region (piv_lists).  These are chains of 100-200 us that once ran in a kernel of their
 // own behind this one and left the chip idle; here the other wavefronts work beside them.
 // A wavefront runs a pipeline over its contexts: while one is in its last block, the next one's
 // first rows, the descriptor of the one after and the list entry of the third are loading.
@@ -3878,8 +3881,8 @@ __global__ __launch_bounds__(kEncThreads) void k_encode_sorted(EncArgs e, SortAr
 // (their groups in s.rest_list, their lanes in s.rest).  Each context of the
 // group (up to kEncWideFW feature words) is staged in turn, however few of the
 // group's lanes it holds: on 100M Zipf queries that is 0.55 ms against 0.64 with
-// per-lane gathers for contexts of fewer than 16 lanes; wider and bad contexts go
-// per lane.  A fixed grid whose wavefronts take the listed groups in turn: a grid
+// per-lane gathers for contexts of fewer than 16 lanes; bad contexts, those of 5-8
+// words and wide ones of full rank go per lane.  A fixed grid whose wavefronts take the listed groups in turn: a grid
 // over every position would launch (and allocate the stage for) a workgroup per
 // 256 positions, almost all of them idle (1.2 against 0.42 ms on 100M queries).
 // A group's wide queries are a wavefront's each, kWideShare of them in this wavefront and the rest shared
@@ -4845,8 +4848,6 @@ FitArgs fit_args(const uint64_t* rows, int64_t rows_words, const int64_t* row_of
     return a;
 }
 
-// the fit: plan (two kernels), then the class kernels, each keeping about as
-// many workgroups as fit on the chip at once
 // workgroups of the wide kernel that can be resident at once on the current
 // device, or 0 where cooperative launches are unavailable (queried once per device)
 int wide_resident_workgroups() {
@@ -4869,7 +4870,8 @@ int wide_resident_workgroups() {
     return r;
 }
 
-// the fit: plan (two kernels), then the class kernels.  The wide kernel runs one
+// the fit: the plan (one kernel up to kPlanThreads contexts, else two), then the class
+// kernels, each with about as many workgroups as fit on the chip at once.  The wide kernel runs one
 // workgroup per compute unit as a cooperative launch (so that a group of
 // workgroups can fit one context together), else a plain launch of up to 256.
 constexpr int kPivGrid = 768;  // LDS-basis workgroups: three per compute unit (LDS-bound)
