@@ -61,6 +61,20 @@ def test_division_at_its_lines(f2, short, long, four_long, four, group):
     parity.compare_fit(parity.gpu_fit(f2, rows, off, n), ref)
 
 
+@pytest.mark.parametrize("count", [65, 257, 900])
+def test_lines_between_short_and_long(f2, count):
+    """Contexts on both sides of 320 rows and of 20,480 rows x columns, of one to four words."""
+    shapes = np.array([(63, 320), (63, 321), (39, 512), (39, 513), (31, 640), (31, 641), (127, 320), (127, 321), (191, 320), (191, 321), (255, 320), (255, 321),
+                       (10, 30)])
+    rng = np.random.default_rng(count)
+    n, m = shapes[rng.integers(0, len(shapes), size=count)].T
+    n = n.astype(np.int32)
+    off = np.concatenate([[0], np.cumsum(m * ((n.astype(np.int64) + 64) // 64 + 2))])
+    rows = rng.integers(0, 2 ** 63, size=int(off[-1]), dtype=np.uint64) * np.uint64(2) + np.uint64(1)
+    ref = parity.oracle_fit_threads(rows, off, n)
+    parity.compare_fit(parity.gpu_fit(f2, rows, off, n), ref)
+
+
 def test_time_of_a_few_long_contexts(f2):
     """20 long contexts beside 4,000 short ones take little more than by themselves (67 us against 59; 107 us with one
     wavefront for each), and 400 beside 1,600 or 8,000 no more than one batch after the other (77 against 24 + 62, 94 against 38 + 65; 117 and 138 us so)."""

@@ -17,7 +17,8 @@ def f2(require_gpu):
 
 
 # (inputs, rows): half a word of features and one (31 | 32), one to five words, blocks of 64 rows, the lines between the classes
-# (256 rows; rows x columns of 16,384 and 131,072; 4,096 rows)
+# (256 rows, where small batches change; rows x columns of 16,384 and 131,072; 4,096 rows; the lines at
+# 320 rows and 20,480 are in test_gpu_fit_batches)
 SHORT = [(0, 3), (1, 0), (1, 9), (30, 64), (31, 63), (31, 200), (32, 65), (40, 256), (40, 399), (62, 257), (63, 128), (63, 256), (64, 130), (100, 162),
          (126, 256), (127, 129), (128, 250), (190, 191), (191, 256), (7, 2048)]
 LONG = [(40, 400), (63, 257), (127, 1023), (191, 683), (31, 4096), (190, 300)]
@@ -51,7 +52,7 @@ def test_fit_classes(f2, short, long, one, group):
 
 @pytest.mark.parametrize("C,top", [(4095, 30), (4097, 130), (8193, 31), (30011, 62)])
 def test_fit_shared_tail(f2, C, top):
-    """A workgroup's share is 16 contexts or half the list's part; beyond 256 shares the tail is taken in chunks."""
+    """Lists dealt out whole, around a context per wavefront and two, and one whose second half is taken in chunks."""
     rng = np.random.default_rng(C)
     n = rng.integers(0, top, size=C).astype(np.int32)
     m = np.minimum(rng.geometric(1 / 12, size=C) - 1, 200)

@@ -107,3 +107,26 @@ def test_time_of_many_tiny_contexts(require_gpu):
     from paper_2608_20532_amd import f2gpu as f2
     t = timing.medians([timing.fit_call(f2, np.full(C, 512), np.full(C, m))[0] for C, m in ((64, 64), (2000, 1))])
     assert t[1] < 3 * t[0], t
+
+
+def test_timeout_with_merged_chunks(require_gpu, monkeypatch):
+    """A wait that gives up at once leaves members with different lists: every one still finishes, the contexts are
+    reported, narrow ones are right, and a fit with waits into the same buffers is exact."""
+    import torch
+    from paper_2608_20532_amd import f2gpu as f2
+    rng = np.random.default_rng(5)
+    n_bits = [512, 700, 1023, 40, 575]
+    rows = [_growing(rng, n, PATTERNS[k]) for k, n in enumerate(n_bits)]
+    off = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64)
+    flat = np.concatenate([r.reshape(-1) for r in rows])
+    ref = parity.oracle_fit_threads(flat, off, np.asarray(n_bits, np.int32))
+    monkeypatch.setenv("F2GPU_GROUP_SPIN_LIMIT", "0")
+    model = parity.gpu_fit(f2, flat, off, n_bits)
+    flags = parity.model_to_host(model)["flags"]
+    assert (flags[[0, 1, 2, 4]] & f2.CTX_SYNC_TIMEOUT).all() and flags[3] == ref.flags[3]
+    monkeypatch.delenv("F2GPU_GROUP_SPIN_LIMIT")
+    nb = f2.f2_fit_workspace_bytes(model.num_ctx)
+    ws, dev = f2.workspace(nb), parity.to_dev(flat)
+    assert f2.f2_fit_batch(dev, dev.numel(), parity.to_dev(off), model, ws, nb) == f2.F2_OK
+    torch.cuda.synchronize()
+    parity.compare_fit(model, ref)
