@@ -2471,7 +2471,9 @@ struct RegQueue {
 //   us, in k_fit_piv behind them 114).  Otherwise they would end last (300 of 1,300 rows, 98
 //   columns among 8,000: 143 us beside them, 81 in k_fit_piv), also where the short ones are too few
 //   (1,000 contexts of 17-97 columns and 2,000 rows: 166 and 97 us).
-// - Those of four words go singly with them (1,000 of 201 columns and 240 rows: 117 us, 255 in k_fit_piv).
+// - Those of four words go singly with them (1,000 of 201 columns and 240 rows: 117 us, 255 in
+//   k_fit_piv), but for a batch of mostly long ones that k_fit_piv holds at once (300 of 221
+//   columns and 500 rows: 181 us singly, 145 there; 1,000: 184 and 315).
 // - Of more group contexts than workgroups, up to twice as many, k_fit_reg takes the largest where it is
 //   full anyway (a corpus of 200,000, 384 of them: 550 us, 620 with all in k_fit_piv), else none (600
 //   of 301 columns: 144 us in k_fit_piv, where three workgroups share a compute unit; 7,400 among 15,000:
@@ -2497,7 +2499,8 @@ __device__ __forceinline__ PivLists piv_lists(const FitArgs& a) {
     p.chain_n = each ? nl + nf : 0;
     p.long_lo = p.chain_lo;  // (one list or the other)
     const int rest = each ? 0 : nl;
-    const bool beside = rest == 0 || (rest <= p.short_n / 4 && (rest > 3 * G || (busy && nf + no > 0)));
+    const bool lone = !each && nf > no && ng + nf + no <= 3 * G && p.short_n <= (ng + nl + nf + no) / 4;
+    const bool beside = !lone && (rest == 0 || (rest <= p.short_n / 4 && (rest > 3 * G || (busy && nf + no > 0))));
     p.group_n = !beside ? 0 : ng <= G ? ng : busy && ng <= 2 * G ? G : 0;
     p.long_n = beside ? rest : 0;
     p.one_lo = each ? one_lo : four_lo;
